@@ -2107,10 +2107,11 @@ struct swe_lc_s {
     unsigned short* g[swe::lc::NL] = {};     // dL/dz of each layer (bf16)
     float* y = nullptr;                // labels and mask of a training batch
     float* mask = nullptr;
-    float* part = nullptr;             // weight-gradient partials
-    int part_blocks = 0;
+    float* part = nullptr;             // weight-gradient partials of every layer
+    int nblk[swe::lc::NL] = {};        // partials of the last backward
     double* loss_part = nullptr;
     int loss_blocks = 0;
+    double* loss = nullptr;            // losses of up to LC_RING optimisation steps
     int last_n = 0;                    // crops of the last forward
     int fwd_blocks[swe::lc::NL] = {};  // resident workgroups of each forward kernel
     int net_blocks = 0;                // resident workgroups of the fused inference kernel
@@ -2121,7 +2122,8 @@ struct swe_lc_s {
     float* dM = nullptr;
     int* dT = nullptr;
     int* dmc = nullptr;                // mask ones per crop (collection scratch)
-    int* idx = nullptr;                // minibatch indices
+    int* idx = nullptr;                // minibatch indices of the optimisation steps in flight
+    int idx_cap = 0;
     std::vector<int> mcount;           // mask ones per data-set crop (host)
 };
 
@@ -2132,10 +2134,11 @@ namespace L_ = swe::lc;
 int lc_in(const swe_lc_t* c, int l) { return c->So + 2 * L_::HALO - 2 * l; }   // input side of layer l
 constexpr int NET_T = 11;     // output block side of the fused inference kernel (a 33-wide crop is 3 x 3 blocks)
 constexpr int NET_NTH = 512;  // its threads per workgroup
+constexpr int LC_RING = 256;  // optimisation steps queued between two host waits
 
 void free_lc(swe_lc_t* c) {
     void* ptrs[] = {c->params, c->grads, c->m1, c->m2, c->wf, c->wb, c->out, c->y, c->mask, c->part, c->loss_part,
-                    c->dscale, c->dX, c->dY, c->dM, c->dT, c->dmc, c->idx};
+                    c->loss, c->dscale, c->dX, c->dY, c->dM, c->dT, c->dmc, c->idx};
     for (void* q : ptrs) if (q) (void)hipFree(q);
     for (int l = 0; l < L_::NL; ++l) {
         if (c->act[l]) (void)hipFree(c->act[l]);
@@ -2195,29 +2198,26 @@ hipError_t lc_infer(swe_lc_t* c, int n, const int* cnt_dev, hipStream_t st) {
 }
 
 // Backward of the last forward (n crops) from g[3] (dL/dz of the last layer),
-// into the packed FP32 gradient.
+// into the block partials of the weight gradients (k_opt sums them).
 hipError_t lc_backward(swe_lc_t* c, int n) {
     hipError_t e;
     auto wgrad = [&](int l) -> hipError_t {
         const int so = lc_in(c, l) - 2;
         const long long total = (long long)n * so * so;
-        int chunk = (int)((total + c->part_blocks - 1) / c->part_blocks);
+        int chunk = (int)((total + L_::PART_BLOCKS - 1) / L_::PART_BLOCKS);
         chunk = (chunk + 15) / 16 * 16;
         const int nblk = (int)((total + chunk - 1) / chunk);
-        float* gl = c->grads + L_::p_off(l);
-        if (l == 0) {
+        c->nblk[l] = nblk;
+        float* part = c->part + L_::part_off(l);
+        if (l == 0)
             hipLaunchKernelGGL((L_::k_conv_bwd_w<16, 32>), dim3(nblk), dim3(256), 0, c->stream, c->g[0], c->act[0],
-                               c->part, lc_in(c, 0), n, chunk);
-            hipLaunchKernelGGL((L_::k_reduce_w<16, 32>), dim3(32), dim3(256), 0, c->stream, c->part, nblk, gl, 6, 32);
-        } else if (l < 3) {
+                               part, lc_in(c, 0), n, chunk);
+        else if (l < 3)
             hipLaunchKernelGGL((L_::k_conv_bwd_w<32, 32>), dim3(nblk), dim3(256), 0, c->stream, c->g[l], c->act[l],
-                               c->part, lc_in(c, l), n, chunk);
-            hipLaunchKernelGGL((L_::k_reduce_w<32, 32>), dim3(32), dim3(256), 0, c->stream, c->part, nblk, gl, 32, 32);
-        } else {
+                               part, lc_in(c, l), n, chunk);
+        else
             hipLaunchKernelGGL((L_::k_conv_bwd_w<32, 16>), dim3(nblk), dim3(256), 0, c->stream, c->g[3], c->act[3],
-                               c->part, lc_in(c, 3), n, chunk);
-            hipLaunchKernelGGL((L_::k_reduce_w<32, 16>), dim3(32), dim3(256), 0, c->stream, c->part, nblk, gl, 32, 6);
-        }
+                               part, lc_in(c, 3), n, chunk);
         return hipGetLastError();
     };
     auto bdata = [&](int l) -> hipError_t {   // g[l-1] from g[l]
@@ -2236,6 +2236,35 @@ hipError_t lc_backward(swe_lc_t* c, int n) {
         if (l > 0 && (e = bdata(l)) != hipSuccess) return e;
     }
     return hipSuccess;
+}
+
+// One optimisation step on the crops already in act[0], y and mask, queued on
+// the stream; its loss goes to loss_dev.
+int lc_opt_step(swe_lc_t* c, int n, double cnt, double lr, double* loss_dev) {
+    HIPCHK(lc_forward(c, n, nullptr, c->stream));
+    c->last_n = n;
+    const size_t np = (size_t)n * c->So * c->So;
+    const float inv = (float)(1.0 / (cnt > 1.0 ? cnt : 1.0));
+    hipLaunchKernelGGL(L_::k_loss, dim3(c->loss_blocks), dim3(256), 0, c->stream, c->out, c->y, c->mask, c->g[3],
+                       (int)np, inv, c->loss_part);
+    HIPCHK(hipGetLastError());
+    HIPCHK(lc_backward(c, n));
+    L_::OptArgs a{};
+    a.part = c->part;
+    for (int l = 0; l < L_::NL; ++l) a.nblk[l] = c->nblk[l];
+    a.params = c->params; a.grads = c->grads; a.m = c->m1; a.v = c->m2; a.wf = c->wf; a.wb = c->wb;
+    a.loss_part = c->loss_part; a.loss_blocks = c->loss_blocks; a.loss = loss_dev;
+    if (lr > 0.0) {
+        c->adam_t++;
+        const double b1 = 0.9, b2 = 0.999;
+        a.adam = 1;
+        a.lr = (float)lr; a.b1 = (float)b1; a.b2 = (float)b2; a.eps = 1e-8f;
+        a.c1 = (float)(1.0 - std::pow(b1, (double)c->adam_t));
+        a.c2 = (float)(1.0 - std::pow(b2, (double)c->adam_t));
+    }
+    hipLaunchKernelGGL(L_::k_opt, dim3(L_::OPT_GRID), dim3(L_::OPT_NTH), 0, c->stream, a);
+    HIPCHK(hipGetLastError());
+    return 0;
 }
 
 // Host FP64 crops (n, Sin, Sin, 6) -> bf16 act[0] with 16 channels.
@@ -2319,10 +2348,10 @@ swe_lc_t* swe_lc_create(int tile, int max_crops, const double* in_scale, const d
     LK(hipMalloc((void**)&c->out, sizeof(float) * (size_t)max_crops * c->So * c->So * 16));
     LK(hipMalloc((void**)&c->y, sizeof(float) * (size_t)max_crops * c->So * c->So * 6));
     LK(hipMalloc((void**)&c->mask, sizeof(float) * (size_t)max_crops * c->So * c->So * 6));
-    c->part_blocks = 512;
-    LK(hipMalloc((void**)&c->part, sizeof(float) * (size_t)c->part_blocks * (9 * 32 * 32 + 32)));
+    LK(hipMalloc((void**)&c->part, sizeof(float) * L_::part_off(L_::NL)));
     c->loss_blocks = 256;
     LK(hipMalloc((void**)&c->loss_part, sizeof(double) * c->loss_blocks));
+    LK(hipMalloc((void**)&c->loss, sizeof(double) * LC_RING));
     LK(hipMemsetAsync(c->params, 0, sizeof(float) * L_::NPARAM, c->stream));
     LK(hipMemsetAsync(c->m1, 0, sizeof(float) * L_::NPARAM, c->stream));
     LK(hipMemsetAsync(c->m2, 0, sizeof(float) * L_::NPARAM, c->stream));
@@ -2443,31 +2472,8 @@ int swe_lc_train_step(swe_lc_t* c, int n, const double* x, const double* y, cons
     for (size_t k = 0; k < np * 6; ++k) { hy[k] = (float)y[k]; hm[k] = (float)mask[k]; cnt += mask[k]; }
     HIPCHK(hipMemcpyAsync(c->y, hy.data(), sizeof(float) * hy.size(), hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(c->mask, hm.data(), sizeof(float) * hm.size(), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(lc_forward(c, n, nullptr, c->stream));
-    c->last_n = n;
-    const float inv = (float)(1.0 / (cnt > 1.0 ? cnt : 1.0));
-    hipLaunchKernelGGL(L_::k_loss, dim3(c->loss_blocks), dim3(256), 0, c->stream, c->out, c->y, c->mask, c->g[3],
-                       (int)np, inv, c->loss_part);
-    HIPCHK(hipGetLastError());
-    HIPCHK(lc_backward(c, n));
-    if (lr > 0.0) {
-        c->adam_t++;
-        const double b1 = 0.9, b2 = 0.999;
-        const float c1 = (float)(1.0 - std::pow(b1, (double)c->adam_t));
-        const float c2 = (float)(1.0 - std::pow(b2, (double)c->adam_t));
-        hipLaunchKernelGGL(L_::k_adam, dim3(64), dim3(256), 0, c->stream, c->params, c->grads, c->m1, c->m2,
-                           L_::NPARAM, (float)lr, (float)b1, (float)b2, 1e-8f, c1, c2);
-        HIPCHK(hipGetLastError());
-        HIPCHK(lc_pack(c));
-    }
-    if (loss) {
-        std::vector<double> lp(c->loss_blocks);
-        HIPCHK(hipMemcpyAsync(lp.data(), c->loss_part, sizeof(double) * lp.size(), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
-        double s = 0.0;
-        for (double v : lp) s += v;
-        *loss = s;
-    }
+    if ((rc = lc_opt_step(c, n, cnt, lr, c->loss))) return rc;
+    if (loss) HIPCHK(hipMemcpyAsync(loss, c->loss, sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     return 0;
 }
@@ -2599,37 +2605,6 @@ int swe_lc_gather(swe_lc_t* c, swe_t* s, double* x, int* tiles) {
 
 namespace {
 
-// One optimisation step on the crops already in act[0], y and mask.
-int lc_opt_step(swe_lc_t* c, int n, double cnt, double lr, double* loss) {
-    HIPCHK(lc_forward(c, n, nullptr, c->stream));
-    c->last_n = n;
-    const size_t np = (size_t)n * c->So * c->So;
-    const float inv = (float)(1.0 / (cnt > 1.0 ? cnt : 1.0));
-    hipLaunchKernelGGL(L_::k_loss, dim3(c->loss_blocks), dim3(256), 0, c->stream, c->out, c->y, c->mask, c->g[3],
-                       (int)np, inv, c->loss_part);
-    HIPCHK(hipGetLastError());
-    HIPCHK(lc_backward(c, n));
-    if (lr > 0.0) {
-        c->adam_t++;
-        const double b1 = 0.9, b2 = 0.999;
-        const float c1 = (float)(1.0 - std::pow(b1, (double)c->adam_t));
-        const float c2 = (float)(1.0 - std::pow(b2, (double)c->adam_t));
-        hipLaunchKernelGGL(L_::k_adam, dim3(64), dim3(256), 0, c->stream, c->params, c->grads, c->m1, c->m2,
-                           L_::NPARAM, (float)lr, (float)b1, (float)b2, 1e-8f, c1, c2);
-        HIPCHK(hipGetLastError());
-        HIPCHK(lc_pack(c));
-    }
-    if (loss) {
-        std::vector<double> lp(c->loss_blocks);
-        HIPCHK(hipMemcpyAsync(lp.data(), c->loss_part, sizeof(double) * lp.size(), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
-        double sum = 0.0;
-        for (double v : lp) sum += v;
-        *loss = sum;
-    }
-    return 0;
-}
-
 template <typename real>
 int lc_collect_t(swe_lc_t* c, swe_t* f, swe_t* g, int r, double tau_c, int n) {
     const int S = c->S, So = c->So;
@@ -2659,7 +2634,8 @@ int swe_lc_data(swe_lc_t* c, int capacity) {
     HIPCHK(hipMalloc((void**)&c->dM, sizeof(float) * (size_t)capacity * So * So * 6));
     HIPCHK(hipMalloc((void**)&c->dT, sizeof(int) * (size_t)capacity));
     HIPCHK(hipMalloc((void**)&c->dmc, sizeof(int) * (size_t)capacity));
-    HIPCHK(hipMalloc((void**)&c->idx, sizeof(int) * (size_t)c->max_crops));
+    c->idx_cap = c->max_crops > (1 << 16) ? c->max_crops : (1 << 16);
+    HIPCHK(hipMalloc((void**)&c->idx, sizeof(int) * (size_t)c->idx_cap));
     HIPCHK(hipMemsetAsync(c->dX, 0, 2 * (size_t)capacity * Sin * Sin * 16, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     return 0;
@@ -2781,30 +2757,47 @@ int swe_lc_fit(swe_lc_t* c, int iters, int batch, double lr, unsigned long long 
     }
     const int So = c->So;
     const int nb = batch < c->count ? batch : c->count;
-    std::vector<int> perm(c->count), pick(nb);
+    std::vector<int> perm(c->count), pick;
     for (int k = 0; k < c->count; ++k) perm[k] = k;
     unsigned long long st = seed * 6364136223846793005ULL + 1442695040888963407ULL;
     auto next = [&]() {   // 64-bit LCG (Knuth's MMIX constants), upper bits
         st = st * 6364136223846793005ULL + 1442695040888963407ULL;
         return (unsigned)(st >> 33);
     };
-    for (int it = 0; it < iters; ++it) {
-        // partial Fisher-Yates: nb distinct crops
-        double cnt = 0.0;
-        for (int b = 0; b < nb; ++b) {
-            const int j = b + (int)(next() % (unsigned)(c->count - b));
-            std::swap(perm[b], perm[j]);
-            pick[b] = perm[b];
-            cnt += c->mcount[perm[b]];
+    // up to `ring` steps are queued between two waits: their minibatches go
+    // up in one copy, their losses come back in one
+    const int fit = c->idx_cap / nb, ring = fit < LC_RING ? fit : LC_RING;
+    std::vector<double> cnt(ring);
+    pick.resize((size_t)nb * ring);
+    for (int base = 0; base < iters; base += ring) {
+        const int m = iters - base < ring ? iters - base : ring;
+        for (int it = 0; it < m; ++it) {
+            // partial Fisher-Yates: nb distinct crops
+            cnt[it] = 0.0;
+            for (int b = 0; b < nb; ++b) {
+                const int j = b + (int)(next() % (unsigned)(c->count - b));
+                std::swap(perm[b], perm[j]);
+                pick[(size_t)it * nb + b] = perm[b];
+                cnt[it] += c->mcount[perm[b]];
+            }
         }
-        HIPCHK(hipMemcpyAsync(c->idx, pick.data(), sizeof(int) * nb, hipMemcpyHostToDevice, c->stream));
-        hipLaunchKernelGGL(L_::k_batch_copy, dim3(2048), dim3(256), 0, c->stream, c->idx, nb, So, c->dX, c->dY, c->dM,
-                           c->act[0], c->y, c->mask);
-        HIPCHK(hipGetLastError());
-        int rc = lc_opt_step(c, nb, cnt, lr, losses ? &losses[it] : nullptr);
+        HIPCHK(hipMemcpyAsync(c->idx, pick.data(), sizeof(int) * (size_t)nb * m, hipMemcpyHostToDevice, c->stream));
+        int rc = 0;
+        for (int it = 0; it < m && !rc; ++it) {
+            hipLaunchKernelGGL(L_::k_batch_copy, dim3(2048), dim3(256), 0, c->stream, c->idx + (size_t)it * nb, nb, So,
+                               c->dX, c->dY, c->dM, c->act[0], c->y, c->mask);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) { set_hip_err("swe_lc_fit", e); rc = SWE_EHIP; }
+            else rc = lc_opt_step(c, nb, cnt[it], lr, c->loss + it);
+        }
+        if (!rc && losses &&
+            hipMemcpyAsync(losses + base, c->loss, sizeof(double) * m, hipMemcpyDeviceToHost, c->stream) != hipSuccess) {
+            set_err("swe_lc_fit: reading the losses failed"); rc = SWE_EHIP;
+        }
+        const hipError_t e = hipStreamSynchronize(c->stream);   // the copies' host buffers are ours again
         if (rc) return rc;
+        HIPCHK(e);
     }
-    HIPCHK(hipStreamSynchronize(c->stream));
     return 0;
 }
 

@@ -532,25 +532,6 @@ __global__ __launch_bounds__(256) void k_conv_bwd_w(const unsigned short* __rest
     }
 }
 
-// Sum the block partials (fixed order) into the packed FP32 gradient of a layer.
-template <int CI, int CO>
-__global__ void k_reduce_w(const float* __restrict__ part, int nblk, float* __restrict__ grad, int ci_real, int co_real) {
-    const int per = 9 * CO * CI + CO;
-    const int wc = co_real * ci_real * 9;
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < wc + co_real; k += gridDim.x * blockDim.x) {
-        int src;
-        if (k < wc) {
-            const int co = k / (ci_real * 9), ci = (k / 9) % ci_real, tap = k % 9;
-            src = (tap * CO + co) * CI + ci;
-        } else {
-            src = 9 * CO * CI + (k - wc);
-        }
-        float s = 0.f;
-        for (int b = 0; b < nblk; ++b) s += part[(size_t)b * per + src];
-        grad[k] = s;
-    }
-}
-
 // ------------------------------------------------------------------ parameters
 // bf16 copies of the packed FP32 weights in both layouts (zero padding).
 __global__ void k_pack_weights(const float* __restrict__ params, unsigned short* __restrict__ wf,
@@ -568,16 +549,132 @@ __global__ void k_pack_weights(const float* __restrict__ params, unsigned short*
     }
 }
 
-// Adam (bias-corrected) on the packed FP32 parameters.
-__global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, int n, float lr, float b1, float b2, float eps, float c1, float c2) {
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
-        const float gk = g[k];
-        const float mk = b1 * m[k] + (1.f - b1) * gk;
-        const float vk = b2 * v[k] + (1.f - b2) * gk * gk;
-        m[k] = mk;
-        v[k] = vk;
-        p[k] -= lr * (mk / c1) / (sqrtf(vk / c2) + eps);
+// ------------------------------------------------------------------ gradient sums and Adam
+// Block partials of the weight gradients: layer l holds PART_BLOCKS of
+// part_elems(l) floats from part_off(l) on.
+constexpr int PART_BLOCKS = 512;
+__host__ __device__ constexpr int part_elems(int l) { return 9 * COUT[l] * CIN[l] + COUT[l]; }
+__host__ __device__ constexpr size_t part_off(int l) {
+    return l == 0 ? 0 : part_off(l - 1) + (size_t)PART_BLOCKS * part_elems(l - 1);
+}
+
+constexpr int OPT_E = 64;        // gradient elements per workgroup (one per lane)
+constexpr int OPT_ROWS = 128;    // block partials staged at a time
+constexpr int OPT_NTH = 512;
+__host__ __device__ constexpr int opt_blocks(int l) { return (part_elems(l) + OPT_E - 1) / OPT_E; }
+constexpr int OPT_GRID = opt_blocks(0) + opt_blocks(1) + opt_blocks(2) + opt_blocks(3) + 1;
+
+struct OptArgs {
+    const float* part;          // block partials
+    int nblk[NL];               // partials of each layer
+    float *params, *grads, *m, *v;
+    unsigned short *wf, *wb;    // bf16 weight copies [tap][out][in] and [tap][in][out]
+    const double* loss_part;    // loss partials of the batch, their count, and the loss
+    int loss_blocks;
+    double* loss;
+    int adam;                   // 0: gradient (and loss) only
+    float lr, b1, b2, eps, c1, c2;
+};
+
+// The end of an optimisation step in one launch: every gradient element is
+// the sum of its block partials in block order (the order is part of the
+// result: FP32 sums), then its Adam update (bias-corrected) and its bf16
+// weight copies, all of which are elementwise in the parameter; the last
+// workgroup sums the loss partials in order.  A workgroup owns 64 elements:
+// its eight waves fetch the partials of 128 blocks at a time (16 coalesced
+// 256-byte rows per wave in flight) into LDS while wave 0 adds the previous
+// 128, so the serial chain is LDS reads and adds, not memory round trips.
+// 64 crops of a 32-cell tile (498 to 512 partials a layer): one thread per
+// element with its loads in the chain took 151-309 us per layer (four
+// launches, 928 us) plus Adam, packing and a host sum of the loss; this takes
+// 14.5 us, reading the 57 MB of partials at 3.9 TB/s.
+__global__ __launch_bounds__(OPT_NTH) void k_opt(OptArgs a) {
+    constexpr int NW = OPT_NTH / 64, J = OPT_ROWS / NW;
+    __shared__ float buf[2][OPT_ROWS][OPT_E];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    int l = 0, blk = blockIdx.x;
+#pragma unroll
+    for (int q = 0; q < NL; ++q)
+        if (l == q && blk >= opt_blocks(q)) { blk -= opt_blocks(q); l = q + 1; }
+    if (l == NL) {   // the loss
+        __shared__ double lp[OPT_NTH];
+        double s = 0.0;
+        for (int k0 = 0; k0 < a.loss_blocks; k0 += OPT_NTH) {
+            const int n = min(OPT_NTH, a.loss_blocks - k0);
+            __syncthreads();
+            if (tid < n) lp[tid] = a.loss_part[k0 + tid];
+            __syncthreads();
+            if (tid == 0)
+                for (int k = 0; k < n; ++k) s += lp[k];
+        }
+        if (tid == 0) *a.loss = s;
+        return;
+    }
+    int co_p = 0, ci_p = 0, co_r = 0, ci_r = 0, po = 0, wo = 0, nb = 0;
+    const float* part = a.part;
+#pragma unroll
+    for (int q = 0; q < NL; ++q)
+        if (l == q) {
+            co_p = COUT[q]; ci_p = CIN[q]; co_r = COUT_REAL[q]; ci_r = CIN_REAL[q];
+            po = p_off(q); wo = wb_off(q); nb = a.nblk[q]; part += part_off(q);
+        }
+    const int wcount = 9 * co_p * ci_p, per = wcount + co_p;
+    const int e = blk * OPT_E + lane;
+    const bool has = e < per;
+    const float* col = part + (has ? e : 0);
+    float r[J];
+    auto fetch = [&](int row0) {
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int b = row0 + wv + NW * j;
+            r[j] = b < nb ? col[(size_t)b * per] : 0.f;
+        }
+    };
+    float s = 0.f;
+    fetch(0);
+    for (int row0 = 0, p = 0; row0 < nb; row0 += OPT_ROWS, p ^= 1) {
+#pragma unroll
+        for (int j = 0; j < J; ++j) buf[p][wv + NW * j][lane] = r[j];
+        __syncthreads();   // also: wave 0 is done with this buffer's previous rows
+        if (row0 + OPT_ROWS < nb) fetch(row0 + OPT_ROWS);
+        if (wv == 0) {
+            const int n = min(OPT_ROWS, nb - row0);
+            int k = 0;
+            for (; k + 16 <= n; k += 16) {
+                float t[16];
+#pragma unroll
+                for (int j = 0; j < 16; ++j) t[j] = buf[p][k + j][lane];
+#pragma unroll
+                for (int j = 0; j < 16; ++j) s += t[j];
+            }
+            for (; k < n; ++k) s += buf[p][k][lane];
+        }
+    }
+    if (wv != 0 || !has) return;
+    int k, tap = 0, co = 0, ci = 0;
+    const bool weight = e < wcount;
+    if (weight) {
+        tap = e / (co_p * ci_p); co = (e / ci_p) % co_p; ci = e % ci_p;
+        if (co >= co_r || ci >= ci_r) return;   // padding
+        k = po + (co * ci_r + ci) * 9 + tap;
+    } else {
+        if (e - wcount >= co_r) return;
+        k = po + co_r * ci_r * 9 + (e - wcount);
+    }
+    a.grads[k] = s;
+    if (!a.adam) return;
+    const float gk = s;
+    const float mk = a.b1 * a.m[k] + (1.f - a.b1) * gk;
+    const float vk = a.b2 * a.v[k] + (1.f - a.b2) * gk * gk;
+    a.m[k] = mk;
+    a.v[k] = vk;
+    float pk = a.params[k];
+    pk -= a.lr * (mk / a.c1) / (sqrtf(vk / a.c2) + a.eps);
+    a.params[k] = pk;
+    if (weight) {
+        const unsigned short h = to_bf16(pk);
+        a.wf[wo + (tap * co_p + co) * ci_p + ci] = h;
+        a.wb[wo + (tap * ci_p + ci) * co_p + co] = h;
     }
 }
 

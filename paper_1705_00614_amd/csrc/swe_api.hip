@@ -2201,25 +2201,6 @@ hipError_t lc_infer(swe_lc_t* c, int n, const int* cnt_dev, hipStream_t st) {
 // into the block partials of the weight gradients (k_opt sums them).
 hipError_t lc_backward(swe_lc_t* c, int n) {
     hipError_t e;
-    auto wgrad = [&](int l) -> hipError_t {
-        const int so = lc_in(c, l) - 2;
-        const long long total = (long long)n * so * so;
-        int chunk = (int)((total + L_::PART_BLOCKS - 1) / L_::PART_BLOCKS);
-        chunk = (chunk + 15) / 16 * 16;
-        const int nblk = (int)((total + chunk - 1) / chunk);
-        c->nblk[l] = nblk;
-        float* part = c->part + L_::part_off(l);
-        if (l == 0)
-            hipLaunchKernelGGL((L_::k_conv_bwd_w<16, 32>), dim3(nblk), dim3(256), 0, c->stream, c->g[0], c->act[0],
-                               part, lc_in(c, 0), n, chunk);
-        else if (l < 3)
-            hipLaunchKernelGGL((L_::k_conv_bwd_w<32, 32>), dim3(nblk), dim3(256), 0, c->stream, c->g[l], c->act[l],
-                               part, lc_in(c, l), n, chunk);
-        else
-            hipLaunchKernelGGL((L_::k_conv_bwd_w<32, 16>), dim3(nblk), dim3(256), 0, c->stream, c->g[3], c->act[3],
-                               part, lc_in(c, 3), n, chunk);
-        return hipGetLastError();
-    };
     auto bdata = [&](int l) -> hipError_t {   // g[l-1] from g[l]
         const int si = lc_in(c, l);
         const long long items = (long long)n * ((si * si + 15) / 16);
@@ -2231,11 +2212,26 @@ hipError_t lc_backward(swe_lc_t* c, int n) {
                                c->g[l], c->act[l], c->g[l - 1], c->wb + L_::wb_off(l), si, n);
         return hipGetLastError();
     };
-    for (int l = 3; l >= 0; --l) {
-        if ((e = wgrad(l)) != hipSuccess) return e;
-        if (l > 0 && (e = bdata(l)) != hipSuccess) return e;
+    for (int l = 3; l > 0; --l)
+        if ((e = bdata(l)) != hipSuccess) return e;
+    L_::WgradArgs w{};
+    int grid = 0;
+    for (int l = 0; l < L_::NL; ++l) {
+        const int so = lc_in(c, l) - 2;
+        const long long total = (long long)n * so * so;
+        int chunk = (int)((total + L_::PART_BLOCKS - 1) / L_::PART_BLOCKS);
+        chunk = (chunk + 15) / 16 * 16;
+        w.g[l] = c->g[l];
+        w.a[l] = c->act[l];
+        w.chunk[l] = chunk;
+        w.nblk[l] = c->nblk[l] = (int)((total + chunk - 1) / chunk);
+        grid += w.nblk[l];
     }
-    return hipSuccess;
+    w.part = c->part;
+    w.Sin0 = lc_in(c, 0);
+    w.n = n;
+    hipLaunchKernelGGL(L_::k_conv_bwd_w, dim3(grid), dim3(L_::WG_NTH), 0, c->stream, w);
+    return hipGetLastError();
 }
 
 // One optimisation step on the crops already in act[0], y and mask, queued on

@@ -46,6 +46,14 @@ constexpr int NPARAM = p_off(NL);
 __host__ __device__ constexpr int wb_count(int l) { return 9 * COUT[l] * CIN[l]; }
 __host__ __device__ constexpr int wb_off(int l) { return l == 0 ? 0 : wb_off(l - 1) + wb_count(l - 1); }
 constexpr int NWB = wb_off(NL);
+// block partials of the weight gradients: layer l holds PART_BLOCKS of
+// part_elems(l) floats ([tap][COUT][CIN], then [COUT]) from part_off(l) on
+constexpr int PART_BLOCKS = 512;
+__host__ __device__ constexpr int part_elems_of(int ci, int co) { return 9 * co * ci + co; }
+__host__ __device__ constexpr int part_elems(int l) { return part_elems_of(CIN[l], COUT[l]); }
+__host__ __device__ constexpr size_t part_off(int l) {
+    return l == 0 ? 0 : part_off(l - 1) + (size_t)PART_BLOCKS * part_elems(l - 1);
+}
 
 __device__ __forceinline__ unsigned short to_bf16(float f) {
     unsigned u = __float_as_uint(f);
@@ -469,67 +477,138 @@ __global__ __launch_bounds__(256) void k_conv_bwd_data(const unsigned short* __r
 // ------------------------------------------------------------------ backward weights
 // Partial weight and bias gradients of one pixel chunk per block:
 // dW[tap][co][ci] = sum_p g[p][co] a_in[p + tap][ci], db[co] = sum_p g[p][co].
-// The 9 x (CO/16) x (CI/16) output tiles are dealt round-robin to the 4
-// waves; part[block] holds [tap][CO][CI] then [CO] in FP32.
+// part[block] holds [tap][CO][CI] then [CO] in FP32; the chunk's pixels enter
+// in order, 16 per MFMA.
+//
+// The reduction runs over pixels, but both operands lie channels-last, so an
+// MFMA lane (4 pixels of one channel) is a column of 4 rows.  The chunk's g
+// rows and the a_in rows its taps reach are staged in LDS as they lie (both
+// are contiguous in memory), WG_SUB pixels at a time, and read back through
+// the transposing LDS load: a group of 16 lanes reads 4 pixel rows of 16
+// channels at any 4 row addresses, so a tap is a constant offset and chunks
+// cross rows and crops freely.  Reading each operand element by 2-byte global
+// loads instead took 96 us for a 32 -> 32 layer of 64 crops of 39^2 and 291 us
+// for the four layers (one launch each); this takes 24.7 us for all of them,
+// bound by its 57 MB of partials.
+constexpr int WG_SUB = 96;     // pixels staged at a time
+constexpr int WG_NTH = 320;    // four MFMA waves and one for the bias sums
+// Positions of the input plane between the first pixel of `sub` consecutive
+// outputs (side so) and the last one's last tap: one per pixel, two more per
+// row end and 2 (so + 2) more per crop end passed.
+__host__ __device__ constexpr int wg_span(int so, int sub) {
+    const int d = sub - 1, si = so + 2;
+    return d + 2 * (d / so + 1) + 2 * si * (d / (so * so) + 1) + 2 * si + 3;
+}
+constexpr int WG_SPAN = 400;
+constexpr bool wg_span_fits() {
+    for (int so = 2; so <= 64 + 1 + 2 * (NL - 1); ++so)   // output sides of tiles of 1 to 64 cells
+        if (wg_span(so, WG_SUB) > WG_SPAN) return false;
+    return true;
+}
+static_assert(wg_span_fits(), "a sub-chunk's input rows must fit their LDS buffer");
+
+struct alignas(16) WgLds {
+    unsigned short g[WG_SUB * 32];
+    unsigned short a[WG_SPAN * 32];
+    int off[WG_SUB];           // element offset of each pixel's first tap in a[]
+};
+
+__device__ __forceinline__ bf16x4 lds_column(const unsigned short* p) {
+    typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_bf16x4*)p);
+}
+
 template <int CI, int CO>
-__global__ __launch_bounds__(256) void k_conv_bwd_w(const unsigned short* __restrict__ g,
-                                                     const unsigned short* __restrict__ a_in,
-                                                     float* __restrict__ part, int Sin, int n, int chunk) {
-    constexpr int TCO = CO / 16, TCI = CI / 16, NTILE = 9 * TCO * TCI, PER = (NTILE + 3) / 4;
+__device__ __forceinline__ void wgrad_chunk(WgLds& L, const unsigned short* __restrict__ g,
+                                            const unsigned short* __restrict__ a_in, float* __restrict__ part, int Sin,
+                                            int n, int chunk, int blk) {
+    constexpr int TCO = CO / 16, TCI = CI / 16, NC = TCO * TCI, PARTS = 4 / NC, TP = (9 + PARTS - 1) / PARTS;
     const int Sout = Sin - 2, P = Sout * Sout, total = n * P;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int m = lane & 15, kq = lane >> 4;
-    const int q0 = blockIdx.x * chunk, q1 = min(total, q0 + chunk);
-    f32x4 acc[PER];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int q0 = blk * chunk, q1 = min(total, q0 + chunk);
+    // wave -> output channels (to, ti) and its share of the taps
+    const int to = (wv % NC) / TCI, ti = wv % TCI, tap0 = (wv / NC) % PARTS;
+    auto pos = [&](int q) {
+        const int c = q / P, p = q % P;
+        return (c * Sin + p / Sout) * Sin + p % Sout;
+    };
+    f32x4 acc[TP];
 #pragma unroll
-    for (int j = 0; j < PER; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = q0; k0 < q1; k0 += 16) {
-        // K index: pixels k0 + 4*kq + i of the flattened (crop, pixel) range
-        int cc[4], py[4], px[4];
-        bool ok[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int q = k0 + 4 * kq + i;
-            ok[i] = q < q1;
-            const int qq = ok[i] ? q : q0;
-            cc[i] = qq / P;
-            const int p = qq % P;
-            py[i] = p / Sout;
-            px[i] = p % Sout;
+    for (int j = 0; j < TP; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float bsum = 0.f;
+    for (int s0 = q0; s0 < q1; s0 += WG_SUB) {
+        const int cnt = min(WG_SUB, q1 - s0), rows = (cnt + 15) / 16 * 16;
+        const int base = pos(s0), len = pos(s0 + cnt - 1) + 2 * Sin + 3 - base;
+        __syncthreads();   // the previous sub-chunk is read
+        {
+            const uint4* src = reinterpret_cast<const uint4*>(g + (size_t)s0 * CO);
+            uint4* dst = reinterpret_cast<uint4*>(L.g);
+            for (int k = tid; k < rows * CO / 8; k += WG_NTH) dst[k] = k < cnt * CO / 8 ? src[k] : uint4{0u, 0u, 0u, 0u};
         }
+        {
+            const uint4* src = reinterpret_cast<const uint4*>(a_in + (size_t)base * CI);
+            uint4* dst = reinterpret_cast<uint4*>(L.a);
+            for (int k = tid; k < len * CI / 8; k += WG_NTH) dst[k] = src[k];
+        }
+        // pixels past the chunk have g = 0 and read the first pixel's taps
+        if (tid < rows) L.off[tid] = tid < cnt ? (pos(s0 + tid) - base) * CI : 0;
+        __syncthreads();
+        if (wv < 4) {
+            const int r = (lane >> 4) * 4 + ((lane & 15) >> 2), c4 = (lane & 3) * 4;
+            for (int k0 = 0; k0 < rows; k0 += 16) {
+                const bf16x4 av = lds_column(L.g + (k0 + r) * CO + to * 16 + c4);
+                const unsigned short* ap = L.a + L.off[k0 + r] + ti * 16 + c4;
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int tile = wv + 4 * j;
-            if (tile >= NTILE) break;
-            const int tap = tile / (TCO * TCI), to = (tile / TCI) % TCO, ti = tile % TCI;
-            const int dy = tap / 3, dx = tap % 3;
-            bf16x4 a, b;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const size_t go = (((size_t)cc[i] * Sout + py[i]) * Sout + px[i]) * CO + to * 16 + m;
-                const size_t ao = (((size_t)cc[i] * Sin + py[i] + dy) * Sin + px[i] + dx) * CI + ti * 16 + m;
-                a[i] = ok[i] ? (short)g[go] : (short)0;
-                b[i] = ok[i] ? (short)a_in[ao] : (short)0;
+                for (int j = 0; j < TP; ++j) {
+                    const int tap = tap0 + PARTS * j;
+                    if (TP * PARTS > 9 && tap >= 9) break;
+                    const bf16x4 bv = lds_column(ap + ((tap / 3) * Sin + tap % 3) * CI);
+                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc[j], 0, 0, 0);
+                }
             }
-            acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[j], 0, 0, 0);
+        } else if (lane < CO) {   // bias: each lane sums its channel over the chunk
+#pragma unroll 8
+            for (int q = 0; q < cnt; ++q) bsum += from_bf16(L.g[q * CO + lane]);
         }
     }
-    float* out = part + (size_t)blockIdx.x * (9 * CO * CI + CO);
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int tile = wv + 4 * j;
-        if (tile >= NTILE) break;
-        const int tap = tile / (TCO * TCI), to = (tile / TCI) % TCO, ti = tile % TCI;
+    float* out = part + (size_t)blk * part_elems_of(CI, CO);
+    const int m = lane & 15, kq = lane >> 4;
+    if (wv < 4) {
         // lane holds rows (co) to*16 + 4*kq + i, column (ci) ti*16 + m
 #pragma unroll
-        for (int i = 0; i < 4; ++i) out[(tap * CO + to * 16 + 4 * kq + i) * CI + ti * 16 + m] = acc[j][i];
+        for (int j = 0; j < TP; ++j) {
+            const int tap = tap0 + PARTS * j;
+            if (TP * PARTS > 9 && tap >= 9) break;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[(tap * CO + to * 16 + 4 * kq + i) * CI + ti * 16 + m] = acc[j][i];
+        }
+    } else if (lane < CO) {
+        out[9 * CO * CI + lane] = bsum;
     }
-    // bias: thread t < CO sums its channel over the chunk
-    if (threadIdx.x < CO) {
-        float s = 0.f;
-        for (int q = q0; q < q1; ++q) s += from_bf16(g[(size_t)q * CO + threadIdx.x]);
-        out[9 * CO * CI + threadIdx.x] = s;
-    }
+}
+
+// All layers in one launch (after the backward-data passes): nblk[l] chunks
+// of layer l.
+struct WgradArgs {
+    const unsigned short* g[NL];
+    const unsigned short* a[NL];
+    float* part;
+    int nblk[NL], chunk[NL];
+    int Sin0, n;               // input side of layer 0, crops
+};
+__global__ __launch_bounds__(WG_NTH) void k_conv_bwd_w(WgradArgs w) {
+    __shared__ WgLds L;
+    int b = blockIdx.x;
+    if (b < w.nblk[1])
+        return wgrad_chunk<32, 32>(L, w.g[1], w.a[1], w.part + part_off(1), w.Sin0 - 2, w.n, w.chunk[1], b);
+    b -= w.nblk[1];
+    if (b < w.nblk[2])
+        return wgrad_chunk<32, 32>(L, w.g[2], w.a[2], w.part + part_off(2), w.Sin0 - 4, w.n, w.chunk[2], b);
+    b -= w.nblk[2];
+    if (b < w.nblk[0])
+        return wgrad_chunk<16, 32>(L, w.g[0], w.a[0], w.part + part_off(0), w.Sin0, w.n, w.chunk[0], b);
+    b -= w.nblk[0];
+    wgrad_chunk<32, 16>(L, w.g[3], w.a[3], w.part + part_off(3), w.Sin0 - 6, w.n, w.chunk[3], b);
 }
 
 // ------------------------------------------------------------------ parameters
@@ -550,14 +629,6 @@ __global__ void k_pack_weights(const float* __restrict__ params, unsigned short*
 }
 
 // ------------------------------------------------------------------ gradient sums and Adam
-// Block partials of the weight gradients: layer l holds PART_BLOCKS of
-// part_elems(l) floats from part_off(l) on.
-constexpr int PART_BLOCKS = 512;
-__host__ __device__ constexpr int part_elems(int l) { return 9 * COUT[l] * CIN[l] + COUT[l]; }
-__host__ __device__ constexpr size_t part_off(int l) {
-    return l == 0 ? 0 : part_off(l - 1) + (size_t)PART_BLOCKS * part_elems(l - 1);
-}
-
 constexpr int OPT_E = 64;        // gradient elements per workgroup (one per lane)
 constexpr int OPT_ROWS = 128;    // block partials staged at a time
 constexpr int OPT_NTH = 512;

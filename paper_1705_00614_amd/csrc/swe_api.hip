@@ -2114,6 +2114,7 @@ struct swe_lc_s {
     double* loss = nullptr;            // losses of up to LC_RING optimisation steps
     int last_n = 0;                    // crops of the last forward
     int fwd_blocks[swe::lc::NL] = {};  // resident workgroups of each forward kernel
+    int bwd_blocks[swe::lc::NL] = {};  // and of each backward-data kernel
     int net_blocks = 0;                // resident workgroups of the fused inference kernel
     // training data set on the device: crops, labels, masks, tile indices
     int cap = 0, count = 0;
@@ -2203,13 +2204,14 @@ hipError_t lc_backward(swe_lc_t* c, int n) {
     hipError_t e;
     auto bdata = [&](int l) -> hipError_t {   // g[l-1] from g[l]
         const int si = lc_in(c, l);
-        const long long items = (long long)n * ((si * si + 15) / 16);
+        const long long items = (long long)n * ((si * si + 15) / 16), most = 4LL * c->bwd_blocks[l];
+        const int grid = grid_for(items < most ? items : most, 4);
         if (l == 3)
-            hipLaunchKernelGGL((L_::k_conv_bwd_data<32, 16>), dim3(grid_for(items, 4)), dim3(256), 0, c->stream,
-                               c->g[3], c->act[3], c->g[2], c->wb + L_::wb_off(3), si, n);
+            hipLaunchKernelGGL((L_::k_conv_bwd_data<32, 16>), dim3(grid), dim3(256), 0, c->stream, c->g[3], c->act[3],
+                               c->g[2], c->wb + L_::wb_off(3), si, n);
         else
-            hipLaunchKernelGGL((L_::k_conv_bwd_data<32, 32>), dim3(grid_for(items, 4)), dim3(256), 0, c->stream,
-                               c->g[l], c->act[l], c->g[l - 1], c->wb + L_::wb_off(l), si, n);
+            hipLaunchKernelGGL((L_::k_conv_bwd_data<32, 32>), dim3(grid), dim3(256), 0, c->stream, c->g[l], c->act[l],
+                               c->g[l - 1], c->wb + L_::wb_off(l), si, n);
         return hipGetLastError();
     };
     for (int l = 3; l > 0; --l)
@@ -2319,6 +2321,10 @@ swe_lc_t* swe_lc_create(int tile, int max_crops, const double* in_scale, const d
         occ[2] = occ[1];
         LK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[3], L_::k_conv_fwd<32, 16, true>, 256, 0));
         for (int l = 0; l < L_::NL; ++l) c->fwd_blocks[l] = cus * (occ[l] > 0 ? occ[l] : 1);
+        LK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[1], L_::k_conv_bwd_data<32, 32>, 256, 0));
+        occ[2] = occ[1];
+        LK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ[3], L_::k_conv_bwd_data<32, 16>, 256, 0));
+        for (int l = 1; l < L_::NL; ++l) c->bwd_blocks[l] = cus * (occ[l] > 0 ? occ[l] : 1);
         int on = 0;
         LK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&on, L_::k_net_fwd<NET_T, NET_NTH>, NET_NTH, 0));
         c->net_blocks = cus * (on > 0 ? on : 1);

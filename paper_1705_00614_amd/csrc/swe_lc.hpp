@@ -426,51 +426,87 @@ __global__ __launch_bounds__(NTH) void k_net_fwd(const unsigned short* __restric
 // g_in = bf16(dL/da_in * (1 - a_in^2)) from g = dL/dz of this layer:
 // dL/da_in[q] = sum_{tap, co} g[q - tap][co] w[co][ci][tap] (zero outside the
 // output plane).  a_in and g_in: [n][Sin][Sin][CI]; g: [n][Sout][Sout][CO].
+//
+// As in the forward, a wave keeps the layer's weights (of every tap and
+// 16-channel chunk) in registers for all its 16-pixel items and loads the
+// next item's gradients and activations while the current one's MFMAs run.
+template <int CI, int CO>
+struct BwdItem {
+    uint2 g[9][CO / 16];
+    unsigned short a[CI / 16][4];
+    int in;      // taps inside the output plane, one bit each
+};
+template <int CI, int CO>
+__device__ __forceinline__ void load_bwd(BwdItem<CI, CO>& f, const unsigned short* __restrict__ g,
+                                         const unsigned short* __restrict__ a_in, int item, int blocks, int Sin, int P,
+                                         int m, int kq) {
+    const int Sout = Sin - 2, c = item / blocks, p0 = (item % blocks) * 16, p = min(p0 + m, P - 1);
+    const int qy = p / Sin, qx = p % Sin;
+    const unsigned short* gc = g + (size_t)c * Sout * Sout * CO + 4 * kq;
+    f.in = 0;
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+        const int oy = qy - tap / 3, ox = qx - tap % 3;
+        const bool in = oy >= 0 && oy < Sout && ox >= 0 && ox < Sout;
+        f.in |= in << tap;
+        const unsigned short* gp = gc + ((in ? oy : 0) * Sout + (in ? ox : 0)) * CO;
+#pragma unroll
+        for (int h = 0; h < CO / 16; ++h) f.g[tap][h] = *reinterpret_cast<const uint2*>(gp + 16 * h);
+    }
+#pragma unroll
+    for (int t = 0; t < CI / 16; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            f.a[t][i] = a_in[((size_t)c * P + min(p0 + 4 * kq + i, P - 1)) * CI + t * 16 + m];
+}
+
 template <int CI, int CO>
 __global__ __launch_bounds__(256) void k_conv_bwd_data(const unsigned short* __restrict__ g,
                                                         const unsigned short* __restrict__ a_in,
                                                         unsigned short* __restrict__ g_in,
                                                         const unsigned short* __restrict__ wb, int Sin, int n) {
-    constexpr int NT = CI / 16;
-    const int Sout = Sin - 2, P = Sin * Sin, blocks = (P + 15) / 16;
+    constexpr int NT = CI / 16, NH = CO / 16;
+    const int P = Sin * Sin, blocks = (P + 15) / 16, total = n * blocks, stride = gridDim.x * 4;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int m = lane & 15, kq = lane >> 4;
-    for (int item = blockIdx.x * 4 + wv; item < n * blocks; item += gridDim.x * 4) {
-        const int c = item / blocks, p0 = (item % blocks) * 16;
-        const int p = min(p0 + m, P - 1);
-        const int qy = p / Sin, qx = p % Sin;
-        const unsigned short* gc = g + (size_t)c * Sout * Sout * CO;
+    int item = blockIdx.x * 4 + wv;
+    if (item >= total) return;
+    uint2 B[9][NH][NT];
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                B[tap][h][t] = *reinterpret_cast<const uint2*>(wb + (tap * CI + t * 16 + m) * CO + 16 * h + 4 * kq);
+    BwdItem<CI, CO> cur, nxt;
+    load_bwd<CI, CO>(cur, g, a_in, item, blocks, Sin, P, m, kq);
+    for (; item < total; item += stride) {
+        if (item + stride < total) load_bwd<CI, CO>(nxt, g, a_in, item + stride, blocks, Sin, P, m, kq);
         f32x4 acc[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int tap = 0; tap < 9; ++tap) {
-            const int oy = qy - tap / 3, ox = qx - tap % 3;
-            const bool in = oy >= 0 && oy < Sout && ox >= 0 && ox < Sout;
-            const unsigned short* gp = gc + ((in ? oy : 0) * Sout + (in ? ox : 0)) * CO + 4 * kq;
+        for (int tap = 0; tap < 9; ++tap)
 #pragma unroll
-            for (int c0 = 0; c0 < CO; c0 += 16) {
-                bf16x4 a = load4(gp + c0);
-                if (!in) a = bf16x4{0, 0, 0, 0};
+            for (int h = 0; h < NH; ++h) {
+                bf16x4 a = as4(cur.g[tap][h]);
+                if (!((cur.in >> tap) & 1)) a = bf16x4{0, 0, 0, 0};
 #pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const bf16x4 b = load4(wb + (tap * CI + t * 16 + m) * CO + c0 + 4 * kq);
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[t], 0, 0, 0);
-                }
+                for (int t = 0; t < NT; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, as4(B[tap][h][t]), acc[t], 0, 0, 0);
             }
-        }
+        const int c = item / blocks, p0 = (item % blocks) * 16;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int ch = t * 16 + m;
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int pp = p0 + 4 * kq + i;
                 if (pp >= P) continue;
-                const size_t o = ((size_t)c * P + pp) * CI + ch;
-                const float a = from_bf16(a_in[o]);
-                g_in[o] = to_bf16(acc[t][i] * (1.f - a * a));
+                const float a = from_bf16(cur.a[t][i]);
+                g_in[((size_t)c * P + pp) * CI + t * 16 + m] = to_bf16(acc[t][i] * (1.f - a * a));
             }
-        }
+        cur = nxt;
     }
 }
 

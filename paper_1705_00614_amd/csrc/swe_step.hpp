@@ -183,6 +183,8 @@ __device__ __forceinline__ float rabs(float a) { return __builtin_fabsf(a); }
 __device__ __forceinline__ double rmax(double a, double b) { return __builtin_fmax(a, b); }
 __device__ __forceinline__ double rmin(double a, double b) { return __builtin_fmin(a, b); }
 __device__ __forceinline__ double rabs(double a) { return __builtin_fabs(a); }
+__device__ __forceinline__ float rcopysign(float a, float s) { return __builtin_copysignf(a, s); }
+__device__ __forceinline__ double rcopysign(double a, double s) { return __builtin_copysign(a, s); }
 // false for NaN and +-inf (compare against the largest finite value)
 __device__ __forceinline__ bool finite(float a) { return rabs(a) <= 3.40282347e38f; }
 __device__ __forceinline__ bool finite(double a) { return rabs(a) <= 1.7976931348623157e308; }
@@ -209,9 +211,10 @@ __device__ __forceinline__ float round_stochastic(float a, float d, float s, uns
     const float bb = s - a;
     const float e = (a - (s - bb)) + (d - bb);
     if (!(e != 0.0f)) return s;
-    const unsigned bits = __float_as_uint(s);
-    const bool away = (e > 0.0f) == (s > 0.0f);
-    const float nb = s == 0.0f ? (e > 0.0f ? 1.4e-45f : -1.4e-45f) : __uint_as_float(away ? bits + 1u : bits - 1u);
+    // s is not 0 here (a sum that cancels is exact): one ulp away from zero
+    // when e and s have the same sign, towards it otherwise
+    const int bits = __float_as_int(s), to = ((bits ^ __float_as_int(e)) >> 31) | 1;
+    const float nb = __int_as_float(bits + to);
     const float p = e * __builtin_amdgcn_rcpf(nb - s);   // in [0, 1]; the gap nb - s is exact
     return (float)(h >> 8) * 5.9604645e-8f < p ? nb : s;
 }
@@ -242,9 +245,11 @@ template <typename T> __device__ __forceinline__ T wave_sum(T v) {
 // ---------------------------------------------------------------- limiter, Riemann
 
 // Limited slope from the backward and forward differences (0 minmod,
-// 1 van Leer, 2 monotonised central).
+// 1 van Leer, 2 monotonised central).  The minmod of two numbers is the
+// median of both and zero: one v_med3_f32.
 template <typename real, int LIM>
 __device__ __forceinline__ real limit(real a, real b) {
+    if constexpr (LIM == 0 && sizeof(real) == 4) return __builtin_amdgcn_fmed3f(a, b, 0.0f);
     const bool same = a * b > real(0);
     real m;
     if constexpr (LIM == 1) {
@@ -258,32 +263,45 @@ __device__ __forceinline__ real limit(real a, real b) {
     return same ? m : real(0);
 }
 
-template <typename real> struct Face { real H, eta, un, ut; };
+// max(lo, min(x, hi)) for lo <= hi
+__device__ __forceinline__ float clamp_level(float x, float lo, float hi) { return __builtin_amdgcn_fmed3f(x, lo, hi); }
+__device__ __forceinline__ double clamp_level(double x, double lo, double hi) { return rmax(lo, rmin(x, hi)); }
+
+// One side of a face: level, bed (level minus depth), normal and tangential
+// velocity.
+template <typename real> struct Face { real eta, b, un, ut; };
 
 // Post-Lagrangian values of one cell for reconstruction along one axis.
 template <typename real> struct Cell { real H, b, un, ut; };
 
 // Limited reconstruction of cell c on its low (towards m) and high (towards
 // q) faces.  A dry cell (H_t <= eps) shows H = 0, U = 0, eta = b; a dry
-// neighbour contributes a zero velocity difference; face depth >= 0.
+// neighbour contributes a zero velocity difference; face depth >= 0.  The
+// velocities of dry cells are stored as 0, so that only slopes and the depth
+// are selected; half a slope is exact, so each face value is one fma.
 template <typename real, int LIM>
 __device__ __forceinline__ void recon(real eps, const Cell<real>& m, const Cell<real>& c,
                                       const Cell<real>& q, Face<real>& lo, Face<real>& hi) {
     const real em = m.H + m.b, ec = c.H + c.b, eq = q.H + q.b;   // eta_t = H_t + b
-    const real sH = limit<real, LIM>(c.H - m.H, q.H - c.H);
-    const real sE = limit<real, LIM>(ec - em, eq - ec);
-    const bool wm = m.H > eps, wq = q.H > eps, wc = c.H > eps;
-    const real sN = limit<real, LIM>(wm ? c.un - m.un : real(0), wq ? q.un - c.un : real(0));
-    const real sT = limit<real, LIM>(wm ? c.ut - m.ut : real(0), wq ? q.ut - c.ut : real(0));
-    const real hH = real(0.5) * sH, hE = real(0.5) * sE, hN = real(0.5) * sN, hT = real(0.5) * sT;
-    hi.H = wc ? rmax(real(0), c.H + hH) : real(0);
-    lo.H = wc ? rmax(real(0), c.H - hH) : real(0);
-    hi.eta = wc ? ec + hE : c.b;
-    lo.eta = wc ? ec - hE : c.b;
-    hi.un = wc ? c.un + hN : real(0);
-    lo.un = wc ? c.un - hN : real(0);
-    hi.ut = wc ? c.ut + hT : real(0);
-    lo.ut = wc ? c.ut - hT : real(0);
+    const bool wc = c.H > eps, wa = wc && m.H > eps && q.H > eps;
+    const real Hc = wc ? c.H : real(0), e0 = Hc + c.b;
+    real sH = limit<real, LIM>(c.H - m.H, q.H - c.H);
+    real sE = limit<real, LIM>(ec - em, eq - ec);
+    real sN = limit<real, LIM>(c.un - m.un, q.un - c.un);
+    real sT = limit<real, LIM>(c.ut - m.ut, q.ut - c.ut);
+    sH = wc ? sH : real(0);
+    sE = wc ? sE : real(0);
+    sN = wa ? sN : real(0);
+    sT = wa ? sT : real(0);
+    const real hiH = rmax(real(0), Hc + real(0.5) * sH), loH = rmax(real(0), Hc - real(0.5) * sH);
+    hi.eta = e0 + real(0.5) * sE;
+    lo.eta = e0 - real(0.5) * sE;
+    hi.b = hi.eta - hiH;
+    lo.b = lo.eta - loH;
+    hi.un = c.un + real(0.5) * sN;
+    lo.un = c.un - real(0.5) * sN;
+    hi.ut = c.ut + real(0.5) * sT;
+    lo.ut = c.ut - real(0.5) * sT;
 }
 
 // Hydrostatic reconstruction over b* = max(bL, bR) and the Rusanov flux of
@@ -291,13 +309,29 @@ __device__ __forceinline__ void recon(real eps, const Cell<real>& m, const Cell<
 template <typename real>
 __device__ __forceinline__ void riemann(real g, const Face<real>& L, const Face<real>& R,
                                         real& FH, real& Fn, real& Ft) {
-    const real bs = rmax(L.eta - L.H, R.eta - R.H);
+    const real bs = rmax(L.b, R.b);
     const real hL = rmax(real(0), L.eta - bs), hR = rmax(real(0), R.eta - bs);
     const real a = rmax(rabs(L.un) + Mth<real>::sqrt(g * hL), rabs(R.un) + Mth<real>::sqrt(g * hR));
     const real qL = hL * L.un, qR = hR * R.un;
     FH = real(0.5) * (qL + qR) - real(0.5) * a * (hR - hL);
     Fn = real(0.5) * (qL * L.un + qR * R.un) - real(0.5) * a * (qR - qL);
     Ft = real(0.5) * (qL * L.ut + qR * R.ut) - real(0.5) * a * (hR * R.ut - hL * L.ut);
+}
+
+// The value of the lane before / after this one (DPP wave shifts: no LDS).
+// Every lane of the wave must be active.
+__device__ __forceinline__ int lane_prev(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, true); }
+__device__ __forceinline__ int lane_next(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, true); }
+__device__ __forceinline__ float lane_prev(float v) { return __int_as_float(lane_prev(__float_as_int(v))); }
+__device__ __forceinline__ float lane_next(float v) { return __int_as_float(lane_next(__float_as_int(v))); }
+__device__ __forceinline__ double lane_prev(double v) {
+    return __hiloint2double(lane_prev(__double2hiint(v)), lane_prev(__double2loint(v)));
+}
+__device__ __forceinline__ double lane_next(double v) {
+    return __hiloint2double(lane_next(__double2hiint(v)), lane_next(__double2loint(v)));
+}
+template <typename real> __device__ __forceinline__ Face<real> lane_prev(const Face<real>& f) {
+    return Face<real>{lane_prev(f.eta), lane_prev(f.b), lane_prev(f.un), lane_prev(f.ut)};
 }
 
 // ---------------------------------------------------------------- forces
@@ -339,10 +373,8 @@ __device__ __forceinline__ real cfl_speed(const Args<real>& a, real H, real cf, 
     fx -= fr * ux;
     fy -= fr * uy;
     const real us = rmax(rabs(ux), rabs(uy)) + Mth<real>::sqrt(a.g * H);
-    const real sx = fx > real(0) ? real(1) : (fx < real(0) ? real(-1) : real(0));
-    const real sy = fy > real(0) ? real(1) : (fy < real(0) ? real(-1) : real(0));
-    const real upx = rabs(ux + sx * Mth<real>::sqrt(a.h * rabs(fx)));
-    const real upy = rabs(uy + sy * Mth<real>::sqrt(a.h * rabs(fy)));
+    const real upx = rabs(ux + rcopysign(Mth<real>::sqrt(a.h * rabs(fx)), fx));
+    const real upy = rabs(uy + rcopysign(Mth<real>::sqrt(a.h * rabs(fy)), fy));
     return rmax(us, rmax(upx, upy));
 }
 
@@ -716,14 +748,23 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
     // al = 1/(12 sqrt2 - 14), be = (3 sqrt2 - 4)/(12 sqrt2 - 14), 2 al + 4 be = 1
     const real al = real(0.33663655161388173), be = real(0.08168172419305914);
     // Cells per thread along the run of each stage.  FP32 kernels run four
-    // waves per SIMD (128 VGPRs), which short runs fit without spilling:
-    // 2 in P1/P2, 3 in FX/FY where the face count divides, so that one pass
-    // of a 512-thread workgroup covers a 32-wide tile.  FP64 keeps runs of 4.
+    // waves per SIMD (128 VGPRs), which short runs fit without spilling: 2 in
+    // P1/P2, 3 in FX/FY where the cell count divides, so that one pass of a
+    // 512-thread workgroup covers a 32-wide tile.  FP64 keeps runs of 4 in
+    // P1/P2; its flux runs are short, for more lanes at work.
     constexpr bool F32 = sizeof(real) == 4;
     constexpr int RP = F32 ? 2 : 4;
-    constexpr int RFX = F32 ? ((TX + 4) % 3 == 0 ? 3 : 2) : 4;
-    constexpr int RFY = F32 ? 3 : 4;
-    static_assert((TX + 8) % RP == 0 && (TX + 4) % RFX == 0, "run lengths must tile the stage rows");
+    constexpr int RFX = (TX + 4) % 3 == 0 ? 3 : (F32 && TX > 32 ? 4 : 2);
+    constexpr int RFY = (TY + 4) % 3 == 0 ? 3 : 2;
+    constexpr int NWAVE = NT / 64;
+    static_assert((TX + 8) % RP == 0 && (TX + 4) % RFX == 0 && (TY + 4) % RFY == 0,
+                  "run lengths must tile the stage rows");
+    const int lane = tid & 63, wv = tid >> 6;
+    // whether inlet cells can lie in the tile's window (uniform)
+    const bool src_here = PER ? a.ni > 0
+                              : tx0 - HALO < a.i0 + a.ni && a.i0 < tx0 + TX + HALO && ty0 - HALO < a.j0 + a.nj &&
+                                    a.j0 < ty0 + TY + HALO;
+    auto source = [&](int x, int y) { return src_here && is_src(a, wrapx(tx0 + x), wrapy(ty0 + y)); };
     auto inside = [&](int x, int y) {
         if constexpr (!EDGE || PER) return true;
         const int gx = tx0 + x, gy = ty0 + y;
@@ -772,7 +813,7 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
             // K1 rule at layer n: own cells and outer face neighbours (no corners)
             const bool own = x >= 0 && x < TX && y >= 0 && y < TY;
             const bool ring = ((x == -1 || x == TX) && y >= 0 && y < TY) || ((y == -1 || y == TY) && x >= 0 && x < TX);
-            if ((own || ring) && inside(x, y) && (w || is_src(a, wrapx(tx0 + x), wrapy(ty0 + y)))) act = 1;
+            if ((own || ring) && inside(x, y) && (w || source(x, y))) act = 1;
         }
         if (__syncthreads_or(act) || (FLD && (fm & 33))) bits |= 64;
     }
@@ -834,7 +875,7 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
                 for (int j = 0; j < 3; ++j)
 #pragma unroll
                     for (int d = 0; d < 3; ++d)
-                        e[j][d] = rmax(bc, rmin(Le[j][c - 1 + d], ec + He[j][c - 1 + d]));
+                        e[j][d] = clamp_level(Le[j][c - 1 + d], bc, ec + He[j][c - 1 + d]);   // bc <= ec
                 // e[j][d]: j = 0 south row, 2 north row; d = 0 west column, 2 east
                 const real Gx = (al * (e[1][2] - e[1][0]) + be * ((e[2][2] - e[2][0]) + (e[0][2] - e[0][0]))) * a.ih;
                 const real Gy = (al * (e[2][1] - e[0][1]) + be * ((e[2][2] - e[0][2]) + (e[2][0] - e[0][0]))) * a.ih;
@@ -918,7 +959,7 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
                     const int x = x0 + i;
                     if (!inside(x, y)) continue;
                     const int s = G::at(x, y);
-                    const real Hs = is_src(a, wrapx(tx0 + x), wrapy(ty0 + y)) ? Hr[i + 1] + sdep : Hr[i + 1];
+                    const real Hs = source(x, y) ? Hr[i + 1] + sdep : Hr[i + 1];
                     if constexpr (FLD)
                         L.UX[s] = field_depth_t<real, TX, TY>(a, tx0 + x, ty0 + y, tau, Hs, false, x, y, fsum);
                     else
@@ -949,7 +990,7 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
                 const real d = real(1) + tau * lam;
                 const real qx = wc ? Hc * Mth<real>::div(ux + tau * ax, d) : real(0);
                 const real qy = wc ? Hc * Mth<real>::div(uy + tau * ay, d) : real(0);
-                const real Hs = is_src(a, wrapx(tx0 + x), wrapy(ty0 + y)) ? Hc + sdep : Hc;
+                const real Hs = source(x, y) ? Hc + sdep : Hc;
                 real Ht = Hs;
                 if constexpr (FLD)
                     if (inside(x, y)) Ht = field_depth_t<real, TX, TY>(a, tx0 + x, ty0 + y, tau, Hs, wc, x, y, fsum);
@@ -982,44 +1023,55 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
         }
     }
 
-    // ---- FX: x faces of rows -1..TY, face x between cells x-1 and x
+    // ---- FX: x faces of rows -1..TY, face x between cells x-1 and x.  A lane
+    // owns a run of cells and their low faces; consecutive lanes hold
+    // consecutive runs of a row, so the high side of the face before a run
+    // comes from the lane before: every cell is reconstructed once.  Runs
+    // cover cells -2..TX+1 (the low face of -2 is not used); a wave takes
+    // whole rows.  Runs that reconstructed their neighbours' cells too (and
+    // compare-and-select minmods) took 288 instructions per 3 faces here and
+    // 329 in FY, against 191 and 202: 107.3 -> 101.3 us for a 2048^2 lake.
+    // FP64 (runs of 4 -> 2, twice the lanes): 24.6 -> 21.8 us on 256 tiles.
     {
-        constexpr int NRW = (TX + 4) / RFX, NRH = TY + 2, NR = NRW * NRH;
-        for (int k = tid; k < NR; k += NT) {
-            const int y = k % NRH - 1, x0 = (k / NRH) * RFX - 1;
-            Cell<real> cl[RFX + 3];
+        constexpr int NRUN = (TX + 4) / RFX, RPW = 64 / NRUN, NU = (TY + 2 + RPW - 1) / RPW;
+        const int run = lane % NRUN, lrow = lane / NRUN;
+        for (int u = wv; u < NU; u += NWAVE) {
+            const int row = u * RPW + lrow, x0 = run * RFX - 2;
+            const bool live = lrow < RPW && row < TY + 2;   // other lanes: a copy of the last row, not stored
+            const int y = (live ? row : TY + 1) - 1;
+            Cell<real> cl[RFX + 2];
 #pragma unroll
-            for (int i = 0; i < RFX + 3; ++i) {
-                const int s = G::at(x0 - 2 + i, y);
+            for (int i = 0; i < RFX + 2; ++i) {
+                const int s = G::at(x0 - 1 + i, y);
                 cl[i].H = L.UX[s]; cl[i].b = L.B[s]; cl[i].un = L.UY[s]; cl[i].ut = L.LM[s];
             }
             bool anyw = false;
 #pragma unroll
-            for (int i = 1; i < RFX + 2; ++i) anyw |= cl[i].H > eps;
+            for (int i = 0; i < RFX + 1; ++i) anyw |= cl[i].H > eps;
+            const int s0 = G::at(x0, y);
             if (!__any(anyw)) {   // dry on both sides of every face: zero fluxes
+                if (live) {
 #pragma unroll
-                for (int f = 0; f < RFX; ++f) {
-                    const int s = G::at(x0 + f, y);
-                    L.HX[s] = real(0); L.HY[s] = real(0); L.H[s] = real(0);
+                    for (int f = 0; f < RFX; ++f) { L.HX[s0 + f] = real(0); L.HY[s0 + f] = real(0); L.H[s0 + f] = real(0); }
                 }
                 continue;
             }
-            Face<real> lo[RFX + 1], hi[RFX + 1];
+            // recon index i is cell x0 + i; face x0 + f sits below cell f
+            Face<real> lo[RFX], hi[RFX];
 #pragma unroll
-            for (int i = 0; i < RFX + 1; ++i) recon<real, LIM>(eps, cl[i], cl[i + 1], cl[i + 2], lo[i], hi[i]);
-            // recon index i is cell x0 - 1 + i; face x0 + f sits between cells f and f+1
+            for (int i = 0; i < RFX; ++i) recon<real, LIM>(eps, cl[i], cl[i + 1], cl[i + 2], lo[i], hi[i]);
+            const Face<real> before = lane_prev(hi[RFX - 1]);
 #pragma unroll
             for (int f = 0; f < RFX; ++f) {
                 real FH, Fn, Ft;
-                riemann<real>(a.g, hi[f], lo[f + 1], FH, Fn, Ft);
+                riemann<real>(a.g, f == 0 ? before : hi[f > 0 ? f - 1 : 0], lo[f], FH, Fn, Ft);
                 if constexpr (CORR) {
                     // face between cells gx-1 and gx: the east face of gx-1
                     const int gx = tx0 + x0 + f, gy = ty0 + y;
                     if (gx >= 1 && gx < nx && gy >= 0 && gy < ny)
-                        add_correction(a, a.corrE, gy * nx + gx - 1, cl[f + 1].H, cl[f + 2].H, FH, Fn, Ft, true);
+                        add_correction(a, a.corrE, gy * nx + gx - 1, cl[f].H, cl[f + 1].H, FH, Fn, Ft, true);
                 }
-                const int s = G::at(x0 + f, y);
-                L.HX[s] = FH; L.HY[s] = Fn; L.H[s] = Ft;
+                if (live) { L.HX[s0 + f] = FH; L.HY[s0 + f] = Fn; L.H[s0 + f] = Ft; }
             }
         }
         __syncthreads();
@@ -1037,9 +1089,13 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
         if (nb >= 0) nbst = lx.stamp[lx.tile_base + nb];
     }
 
-    // ---- FY + final update: columns -1..TX, runs of 4 cells along y
+    // ---- FY + final update: columns -1..TX, runs along y with the low faces
+    // of their cells, consecutive lanes holding consecutive runs of a column:
+    // the side below a run comes from the lane before, the flux above it from
+    // the lane after.  Runs cover cells -2..TY+1, of which -1..TY are updated.
     {
-        constexpr int NC = TX + 2, NRY = (TY + 2 + RFY - 1) / RFY, NR = NC * NRY;
+        constexpr int NRUN = (TY + 4) / RFY, CPW = 64 / NRUN, NU = (TX + 2 + CPW - 1) / CPW;
+        const int run = lane % NRUN, lcol = lane / NRUN;
         // tap faces in this tile: a face belongs to the tile of the cell east
         // (x face) or north (y face) of it
         bool tap_here = false;
@@ -1054,47 +1110,53 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
                 tap_here |= xs || ys;
             }
         }
-        for (int k = tid; k < NR; k += NT) {
-            const int x = k % NC - 1, y0 = (k / NC) * RFY - 1;
-            Cell<real> cl[RFY + 4];
+        for (int u = wv; u < NU; u += NWAVE) {
+            const int col = u * CPW + lcol, y0 = run * RFY - 2;
+            const bool live = lcol < CPW && col < TX + 2;   // other lanes: a copy of the last column, not stored
+            const int x = (live ? col : TX + 1) - 1;
+            Cell<real> cl[RFY + 2];
 #pragma unroll
-            for (int i = 0; i < RFY + 4; ++i) {
-                const int s = G::at(x, y0 - 2 + i);
+            for (int i = 0; i < RFY + 2; ++i) {
+                const int s = G::at(x, y0 - 1 + i);
                 cl[i].H = L.UX[s]; cl[i].b = L.B[s]; cl[i].un = L.LM[s]; cl[i].ut = L.UY[s];
             }
             real FH[RFY + 1], Fn[RFY + 1], Ft[RFY + 1];
             bool anyw = false;
 #pragma unroll
-            for (int i = 1; i < RFY + 3; ++i) anyw |= cl[i].H > eps;
+            for (int i = 0; i < RFY + 1; ++i) anyw |= cl[i].H > eps;
             if (__any(anyw)) {
-                Face<real> lo[RFY + 2], hi[RFY + 2];
+                Face<real> lo[RFY], hi[RFY];
 #pragma unroll
-                for (int i = 0; i < RFY + 2; ++i) recon<real, LIM>(eps, cl[i], cl[i + 1], cl[i + 2], lo[i], hi[i]);
-                // recon index i is cell y0 - 1 + i; face y0 + f between cells f and f+1
+                for (int i = 0; i < RFY; ++i) recon<real, LIM>(eps, cl[i], cl[i + 1], cl[i + 2], lo[i], hi[i]);
+                const Face<real> before = lane_prev(hi[RFY - 1]);
+                // recon index i is cell y0 + i; face y0 + f sits below cell f
 #pragma unroll
-                for (int f = 0; f < RFY + 1; ++f) {
-                    riemann<real>(a.g, hi[f], lo[f + 1], FH[f], Fn[f], Ft[f]);
+                for (int f = 0; f < RFY; ++f) {
+                    riemann<real>(a.g, f == 0 ? before : hi[f > 0 ? f - 1 : 0], lo[f], FH[f], Fn[f], Ft[f]);
                     if constexpr (CORR) {
                         // face between cells gy-1 and gy: the north face of gy-1
                         const int gx = tx0 + x, gy = ty0 + y0 + f;
                         if (gy >= 1 && gy < ny && gx >= 0 && gx < nx)
-                            add_correction(a, a.corrN, (gy - 1) * nx + gx, cl[f + 1].H, cl[f + 2].H, FH[f], Fn[f],
-                                           Ft[f], false);
+                            add_correction(a, a.corrN, (gy - 1) * nx + gx, cl[f].H, cl[f + 1].H, FH[f], Fn[f], Ft[f],
+                                           false);
                     }
                 }
-            } else {   // dry on both sides of every face of the run: zero fluxes
+                FH[RFY] = lane_next(FH[0]);
+                Fn[RFY] = lane_next(Fn[0]);
+                Ft[RFY] = lane_next(Ft[0]);
+            } else {   // dry on both sides of every face of the wave: zero fluxes
 #pragma unroll
                 for (int f = 0; f < RFY + 1; ++f) { FH[f] = real(0); Fn[f] = real(0); Ft[f] = real(0); }
             }
 #pragma unroll
             for (int i = 0; i < RFY; ++i) {
                 const int y = y0 + i;
-                if (y > TY || !inside(x, y)) continue;
+                if (!live || y < -1 || y > TY || !inside(x, y)) continue;
                 const int s = G::at(x, y);
                 const real dxH = L.HX[s] - L.HX[s + 1];
                 const real dxQx = L.HY[s] - L.HY[s + 1];
                 const real dxQy = L.H[s] - L.H[s + 1];
-                const real Ht = cl[i + 2].H, dH = r * (dxH + (FH[i] - FH[i + 1]));
+                const real Ht = cl[i + 1].H, dH = r * (dxH + (FH[i] - FH[i + 1]));
                 real Hn = Ht + dH;
                 if constexpr (F32)
                     Hn = round_stochastic(Ht, dH, Hn, cell_hash((unsigned)((ty0 + y) * nx + tx0 + x), lx.clk));
@@ -1152,7 +1214,7 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
             const int s = G::at(x, y);
             const real H = L.NH[s];
             const bool w = H > eps;
-            const bool ws = w || is_src(a, wrapx(tx0 + x), wrapy(ty0 + y));
+            const bool ws = w || source(x, y);
             if (k >= NT_CELLS) { rg |= ws; continue; }
             if (ws) {
                 own = 1;

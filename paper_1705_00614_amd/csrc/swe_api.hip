@@ -165,8 +165,6 @@ struct swe_s {
     int* hot = nullptr;         // completion and list counters (one per 256-byte line)
     int* lists = nullptr;       // [2 slots][NSEG segments][ntiles]
     int* stamp = nullptr;
-    void* wg_speed = nullptr;   // per-workgroup maximum speed
-    long long* wg_cells = nullptr;
     double* mass = nullptr;
     double* ledger = nullptr;
     double* scalar = nullptr;   // device scratch for reductions
@@ -227,8 +225,6 @@ void fill_args(swe_t* s, int parity, Args<real>* a) {
     a->lists = s->lists;
     a->slot = parity;
     a->stamp = s->stamp;
-    a->wg_speed = (real*)s->wg_speed;
-    a->wg_cells = s->wg_cells;
     a->mass = s->mass;
     a->ledger = s->ledger;
     a->nx = s->nx; a->ny = s->ny; a->ntx = s->ntx; a->nty = s->nty; a->ntiles = s->ntiles;
@@ -366,7 +362,7 @@ int set_state_impl(swe_t* s, const double* H, const double* Qx, const double* Qy
 void free_all(swe_t* s) {
     if (s->graph) (void)hipGraphExecDestroy(s->graph);
     void* ptrs[] = {s->Hb[0], s->Hb[1], s->Qxb[0], s->Qxb[1], s->Qyb[0], s->Qyb[1], s->bed, s->cf,
-                    s->ctrl, s->hot, s->lists, s->stamp, s->wg_speed, s->wg_cells, s->mass, s->ledger,
+                    s->ctrl, s->hot, s->lists, s->stamp, s->mass, s->ledger,
                     s->scalar, s->corrE, s->corrN, s->claims, s->tapx, s->tapy, s->sigma, s->fmask, s->fvol};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
@@ -631,8 +627,6 @@ static swe_t* create_grid(int nx, int ny, double dx, const double* b, const doub
     if (s->grid < 8) s->grid = 8;
     if (!p->skip_dry && s->grid > s->ntiles) s->grid = s->ntiles;
     s->grid_max = s->grid;
-    CK(hipMalloc(&s->wg_speed, sizeof(double) * s->grid));
-    CK(hipMalloc((void**)&s->wg_cells, sizeof(long long) * s->grid));
 
     build_args(s);
     if (set_state_impl(s, p->H0, p->Qx0, p->Qy0, p->solid) != 0) {
@@ -1136,7 +1130,6 @@ struct swe_batch_s {
     int* hot = nullptr;
     int* lists = nullptr;
     int* stamp = nullptr;
-    long long* wg_cells = nullptr;
     double* scalar = nullptr;
     void* dargs[2] = {nullptr, nullptr};
     std::vector<unsigned char> hargs[2];   // Args<real>[n] per parity (host copies)
@@ -1162,7 +1155,6 @@ void fill_batch_args(swe_batch_t* b, int par) {
         a->ctrl = b->ctrls + k; a->lctrl = b->lctrl;
         a->sid = k; a->tile_base = c.tile_base;
         a->hot = b->hot; a->lists = b->lists; a->slot = par; a->stamp = b->stamp;
-        a->wg_speed = nullptr; a->wg_cells = b->wg_cells;
         a->mass = c.mass; a->ledger = c.ledger;
         a->nx = c.nx; a->ny = c.ny; a->ntx = c.ntx; a->nty = c.nty; a->ntiles = c.ntiles;
         a->skip = 1; a->limiter = p.limiter; a->list_cap = b->total_tiles;
@@ -1178,7 +1170,7 @@ void fill_batch_args(swe_batch_t* b, int par) {
     swe::BatchArgs<real>* ba = (swe::BatchArgs<real>*)b->bargs[par].data();
     ba->scen = (const Args<real>*)b->dargs[par];
     ba->n = b->n; ba->lctrl = b->lctrl; ba->hot = b->hot; ba->lists = b->lists;
-    ba->list_cap = b->total_tiles; ba->slot = par; ba->wg_cells = b->wg_cells;
+    ba->list_cap = b->total_tiles; ba->slot = par;
 }
 
 void free_batch(swe_batch_t* b) {
@@ -1187,7 +1179,7 @@ void free_batch(swe_batch_t* b) {
         void* ptrs[] = {c.Hb[0], c.Hb[1], c.Qxb[0], c.Qxb[1], c.Qyb[0], c.Qyb[1], c.bed, c.cf, c.mass, c.ledger};
         for (void* q : ptrs) if (q) (void)hipFree(q);
     }
-    void* ptrs[] = {b->lctrl, b->ctrls, b->hot, b->lists, b->stamp, b->wg_cells, b->scalar, b->dargs[0], b->dargs[1]};
+    void* ptrs[] = {b->lctrl, b->ctrls, b->hot, b->lists, b->stamp, b->scalar, b->dargs[0], b->dargs[1]};
     for (void* q : ptrs) if (q) (void)hipFree(q);
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
 }
@@ -1349,7 +1341,6 @@ swe_batch_t* swe_batch_create(int n, const int* nx, const int* ny, const double*
     if (L->occupancy(&occ) != 0 || occ < 1) occ = 1;
     B->grid = cus * occ;
     if (B->grid < 8) B->grid = 8;
-    BK(hipMalloc((void**)&B->wg_cells, sizeof(long long) * B->grid));
     const size_t asz = B->precision == 32 ? sizeof(Args<float>) : sizeof(Args<double>);
     for (int t = 0; t < 2; ++t) {
         BK(hipMalloc(&B->dargs[t], asz * n));

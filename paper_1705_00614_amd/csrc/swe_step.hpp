@@ -46,8 +46,7 @@ constexpr double GATE_BED = 1.0e6;
 // serialise (~11 ns each on this part), so nothing per workgroup goes to one
 // address: the workgroups of a step form NSEG groups, each with its own
 // completion counter and its own segment of the next tile list, every counter
-// on its own 256-byte line; per-workgroup maxima are plain stores reduced by
-// the last workgroup.
+// on its own 256-byte line.
 constexpr int NSEG = 8;
 constexpr int LINE = 64;   // ints per 256-byte line
 __host__ __device__ constexpr int hot_done(int g) { return g * LINE; }          // g < NSEG; NSEG: all groups
@@ -99,8 +98,6 @@ struct Args {
     int* lists;                                         // [2 slots][NSEG segments][ntiles]
     int slot;                                           // list slot read by this step
     int* stamp;                                         // de-duplication stamps
-    real* wg_speed;                                     // per-workgroup maximum speed
-    long long* wg_cells;                                // per-workgroup processed cells
     double* mass;                                       // per-tile sum of H
     double* ledger;                                     // per-tile clamp volume
     int nx, ny, ntx, nty, ntiles, skip, limiter;
@@ -231,15 +228,57 @@ __device__ __forceinline__ int mirror(int i, int n, int& flips) {
 
 // ---------------------------------------------------------------- reductions
 
+// Wave reductions by halves: lanes 32 and 16 apart are paired by the row swaps
+// of gfx950, 8 to 1 apart by row rotations (DPP), so a step costs a few cycles
+// where a cross-lane read through LDS costs over a hundred.  Every lane gets
+// the result; the pairing (and so an FP64 sum's rounding) is that of an xor
+// butterfly from 32 down to 1.
+template <int CTRL> __device__ __forceinline__ int dpp_row(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL> __device__ __forceinline__ float dpp_row(float v) { return __int_as_float(dpp_row<CTRL>(__float_as_int(v))); }
+template <int CTRL> __device__ __forceinline__ double dpp_row(double v) {
+    return __hiloint2double(dpp_row<CTRL>(__double2hiint(v)), dpp_row<CTRL>(__double2loint(v)));
+}
+// a, b: the values of lanes 32 (FAR) or 16 apart, the same pair in both
+template <bool FAR> __device__ __forceinline__ void row_swap(int v, int& a, int& b) {
+    const auto r = FAR ? __builtin_amdgcn_permlane32_swap(v, v, false, false)
+                       : __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    a = (int)r[0];
+    b = (int)r[1];
+}
+template <bool FAR> __device__ __forceinline__ void row_swap(float v, float& a, float& b) {
+    int x, y;
+    row_swap<FAR>(__float_as_int(v), x, y);
+    a = __int_as_float(x);
+    b = __int_as_float(y);
+}
+template <bool FAR> __device__ __forceinline__ void row_swap(double v, double& a, double& b) {
+    int xl, yl, xh, yh;
+    row_swap<FAR>(__double2loint(v), xl, yl);
+    row_swap<FAR>(__double2hiint(v), xh, yh);
+    a = __hiloint2double(xh, xl);
+    b = __hiloint2double(yh, yl);
+}
+template <typename T, class Op> __device__ __forceinline__ T wave_reduce(T v, Op op) {
+    T a, b;
+    row_swap<true>(v, a, b);
+    v = op(a, b);
+    row_swap<false>(v, a, b);
+    v = op(a, b);
+    v = op(v, dpp_row<0x128>(v));
+    v = op(v, dpp_row<0x124>(v));
+    v = op(v, dpp_row<0x122>(v));
+    return op(v, dpp_row<0x121>(v));
+}
 template <typename T> __device__ __forceinline__ T wave_max(T v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { T u = __shfl_xor(v, o, 64); v = v > u ? v : u; }
-    return v;
+    return wave_reduce(v, [](T x, T y) { return x > y ? x : y; });
 }
 template <typename T> __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    return wave_reduce(v, [](T x, T y) { return x + y; });
+}
+__device__ __forceinline__ int wave_or(int v) {
+    return wave_reduce(v, [](int x, int y) { return x | y; });
 }
 
 // ---------------------------------------------------------------- limiter, Riemann
@@ -378,11 +417,12 @@ __device__ __forceinline__ real cfl_speed(const Args<real>& a, real H, real cf, 
     return rmax(us, rmax(upx, upy));
 }
 
-__device__ __forceinline__ void atomic_max_prep(Ctrl* c, float v) {
-    atomicMax((unsigned int*)&c->prep_speed, __float_as_uint(v));
+// Raise the layer's maximum speed (v >= 0); returns its bits from before.
+__device__ __forceinline__ unsigned long long atomic_max_prep(Ctrl* c, float v) {
+    return atomicMax((unsigned int*)&c->prep_speed, __float_as_uint(v));
 }
-__device__ __forceinline__ void atomic_max_prep(Ctrl* c, double v) {
-    atomicMax(&c->prep_speed, (unsigned long long)__double_as_longlong(v));
+__device__ __forceinline__ unsigned long long atomic_max_prep(Ctrl* c, double v) {
+    return atomicMax(&c->prep_speed, (unsigned long long)__double_as_longlong(v));
 }
 __device__ __forceinline__ double prep_speed(const Ctrl* c, float) {
     return (double)__uint_as_float(*(const unsigned int*)&c->prep_speed);
@@ -456,13 +496,20 @@ __device__ __forceinline__ void close_segments_from(Ctrl* c, const int (&n)[NSEG
     }
 }
 
-// Entry p of the list in `slot` (segments concatenated in order); cap is the
-// capacity of one segment.
-__device__ __forceinline__ int list_entry(const Ctrl* c, const int* lists, int cap, int slot, int p) {
-    int g = 0;
+// Entry p of the list in `slot` (segments concatenated in order, starting at
+// off[]); cap is the capacity of one segment.
+__device__ __forceinline__ int list_entry(const int (&off)[NSEG + 1], const int* lists, int cap, int slot, int p) {
+    int g = 0, o = 0;
 #pragma unroll
-    for (int q = 1; q < NSEG; ++q) g += p >= c->seg_off[slot][q];
-    return lists[(slot * NSEG + g) * cap + p - c->seg_off[slot][g]];
+    for (int q = 1; q < NSEG; ++q)
+        if (p >= off[q]) { g = q; o = off[q]; }
+    return lists[(slot * NSEG + g) * cap + p - o];
+}
+__device__ __forceinline__ int list_entry(const Ctrl* c, const int* lists, int cap, int slot, int p) {
+    int off[NSEG + 1];
+#pragma unroll
+    for (int g = 0; g <= NSEG; ++g) off[g] = c->seg_off[slot][g];
+    return list_entry(off, lists, cap, slot, p);
 }
 
 // The list entry of workgroup b when the list in `slot` is no longer than
@@ -731,7 +778,7 @@ __device__ __forceinline__ real field_depth_t(const Args<real>& a, int gx, int g
 template <typename real, int TX, int TY, int NT, int LIM, bool EDGE, int MODE>
 __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, int ty0,
                           real tau, real sdep, real& vmax, bool& bad, double& msum, double& lsum,
-                          double& fsum, int fm, int& bits, const ListCtx& lx, int& nbst) {
+                          double& fsum, int fm, int& bits, const ListCtx& lx, int& nbst, int* s_act) {
     using G = Geo<TX, TY>;
     constexpr int W = G::W;
     constexpr bool TAP = MODE == MODE_TAP, CORR = MODE == MODE_CORR, FLD = MODE == MODE_FIELD;
@@ -815,11 +862,23 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
             const bool ring = ((x == -1 || x == TX) && y >= 0 && y < TY) || ((y == -1 || y == TY) && x >= 0 && x < TX);
             if ((own || ring) && inside(x, y) && (w || source(x, y))) act = 1;
         }
-        if (__syncthreads_or(act) || (FLD && (fm & 33))) bits |= 64;
+        if (__any(act) && lane == 0) s_act[wv] = 1;
+        else if (lane == 0) s_act[wv] = 0;
+        __syncthreads();
+        // only the last wave keeps the list (below) and needs the vote
+        if (wv == NWAVE - 1) {
+            int v = FLD && (fm & 33) ? 1 : 0;
+#pragma unroll
+            for (int q = 0; q < NWAVE; ++q) v |= s_act[q];
+            if (v) bits |= 64;
+        }
     }
     // self-append of a tile K1-active at layer n: stamp now, slot after P1,
-    // entry after P2 (thread 0)
-    const bool early = lx.on && tid == 0 && (bits & 64);
+    // entry after P2.  The last wave does all list work: it has the fewest
+    // runs in P1 and P2 and none in FX and FY, so that the atomics' round
+    // trips (about 2 us each) pass while the others compute; on wave 0 they
+    // held up P2 and FX of every wet tile.
+    const bool early = lx.on && tid == NT - 64 && (bits & 64);
     int e_old = lx.gen, e_base = 0;
     if (early) e_old = atomicMax(&lx.stamp[lx.tile_base + lx.tile], lx.gen);
 
@@ -1077,14 +1136,14 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
         __syncthreads();
     }
 
-    // stamps of the four neighbours (lanes 1..4 of wave 0: W, E, S, N); a
+    // stamps of the four neighbours (lanes 1..4 of the last wave: W, E, S, N); a
     // stale value only costs an atomic at the end
     nbst = lx.gen;
-    if (lx.on && tid >= 1 && tid <= 4) {
+    if (lx.on && wv == NWAVE - 1 && lane >= 1 && lane <= 4) {
         const int ti = lx.tile % lx.ntx, tj = lx.tile / lx.ntx;
-        const int nb = tid == 1 ? (ti > 0 ? lx.tile - 1 : PER ? lx.tile + lx.ntx - 1 : -1)
-                     : tid == 2 ? (ti < lx.ntx - 1 ? lx.tile + 1 : PER ? lx.tile - lx.ntx + 1 : -1)
-                     : tid == 3 ? (tj > 0 ? lx.tile - lx.ntx : PER ? lx.tile + (lx.nty - 1) * lx.ntx : -1)
+        const int nb = lane == 1 ? (ti > 0 ? lx.tile - 1 : PER ? lx.tile + lx.ntx - 1 : -1)
+                     : lane == 2 ? (ti < lx.ntx - 1 ? lx.tile + 1 : PER ? lx.tile - lx.ntx + 1 : -1)
+                     : lane == 3 ? (tj > 0 ? lx.tile - lx.ntx : PER ? lx.tile + (lx.nty - 1) * lx.ntx : -1)
                                 : (tj < lx.nty - 1 ? lx.tile + lx.ntx : PER ? lx.tile - (lx.nty - 1) * lx.ntx : -1);
         if (nb >= 0) nbst = lx.stamp[lx.tile_base + nb];
     }
@@ -1259,7 +1318,8 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> 
     constexpr int NWAVE = NT / 64;
     __shared__ Lds<real, TX, TY> L;
     __shared__ double red_d[MODE == MODE_FIELD ? 3 : 2][NWAVE];
-    __shared__ int red_i[NWAVE];
+    __shared__ real red_v[NWAVE];
+    __shared__ int red_i[NWAVE], s_act[NWAVE];
     __shared__ int s_last;
 
     Ctrl* const ctrl = a.ctrl;
@@ -1275,7 +1335,10 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> 
     const int G = gridDim.x, grp = blockIdx.x % NSEG;
     // only the patches of a nest (tapping grids) carry ring tiles; the other
     // variants compile without them (no registers held for their bounds)
-    const int nlist = a.skip ? ctrl->seg_off[a.slot][NSEG] : a.ntiles;
+    int off[NSEG + 1];
+#pragma unroll
+    for (int g = 0; g <= NSEG; ++g) off[g] = ctrl->seg_off[a.slot][g];
+    const int nlist = a.skip ? off[NSEG] : a.ntiles;
     const int count = nlist + (RING && a.skip ? a.nring : 0);   // list entries, then the ring tiles
     const real tau = (real)ctrl->tau;
     const real sdep = (real)ctrl->sdepth;
@@ -1287,25 +1350,30 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> 
     const bool own = !RING && a.skip && count <= G;
     int first = -1;
     if (own) {
-        const int g0 = b0 % NSEG, n0 = ctrl->seg_off[a.slot][g0 + 1] - ctrl->seg_off[a.slot][g0];
+        int n0 = 0;
+#pragma unroll
+        for (int g = 0; g < NSEG; ++g)
+            if (b0 % NSEG == g) n0 = off[g + 1] - off[g];
         const int e = spec_in && b0 / NSEG < n0 ? spec : list_entry_own(ctrl, a.lists, a.ntiles, a.slot, b0, G);
         first = e < 0 ? -1 : entry_tile(e);
     }
     const int npos = own ? (first >= 0 ? b0 + 1 : 0) : count;
 
-    real vmax = real(0);
-    bool bad = false;
     long long ncells = 0;
+    double vm = 0.0;      // thread 0: speed maximum and error of the workgroup's tiles
+    bool anybad = false;
 
     for (int p = blockIdx.x; p < npos; p += G) {
         const int tile = !a.skip ? p
                          : first >= 0 ? first
                          : RING && p >= nlist ? a.ring_tiles[p - nlist]
-                                              : entry_tile(list_entry(ctrl, a.lists, a.ntiles, a.slot, p));
+                                              : entry_tile(list_entry(off, a.lists, a.ntiles, a.slot, p));
         const int tx0 = (tile % a.ntx) * TX, ty0 = (tile / a.ntx) * TY;
         ncells += (long long)min(TX, nx - tx0) * min(TY, ny - ty0);
         const bool edge = tx0 < HALO || ty0 < HALO || tx0 + TX + HALO > nx || ty0 + TY + HALO > ny;
         constexpr bool FLD = MODE == MODE_FIELD;
+        real vmax = real(0);
+        bool bad = false;
         double msum = 0.0, lsum = 0.0, fsum = 0.0;
         int bits = 0, nbst = gen;
         const int fm = FLD ? (int)a.fmask[tile] : 0;
@@ -1315,59 +1383,63 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> 
         const double fvo = FLD && tid == 0 ? a.fvol[tile] : 0.0;
         const ListCtx lx{a.stamp, a.lists, a.hot, a.ntiles, a.slot ^ 1, grp, gen, 0, 0, tile, a.ntx, a.nty,
                          a.skip != 0 && !(RING && ring_tile(a, tile)), clk};
-        __syncthreads();   // LDS of the previous tile is free
+        // (the LDS of the previous tile is free: its last reads lie before the
+        // barrier of its block reductions)
         if (edge)
             tile_step<real, TX, TY, NT, LIM, true, MODE>(a, L, tx0, ty0, tau, sdep, vmax, bad, msum, lsum, fsum,
-                                                         fm, bits, lx, nbst);
+                                                         fm, bits, lx, nbst, s_act);
         else
             tile_step<real, TX, TY, NT, LIM, false, MODE>(a, L, tx0, ty0, tau, sdep, vmax, bad, msum, lsum, fsum,
-                                                          fm, bits, lx, nbst);
+                                                          fm, bits, lx, nbst, s_act);
         if constexpr (FLD) bits |= fm & 63;   // cells with rain are sources of the K1 rule
-        // block reductions: flags, volume and ledger partials
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) bits |= __shfl_xor(bits, o, 64);
+        // block reductions: flags, volume and ledger partials, speed
+        bits = wave_or(bits | (bad ? 128 : 0));
         msum = wave_sum(msum);
         lsum = wave_sum(lsum);
+        vmax = wave_max(vmax);
         if constexpr (FLD) fsum = wave_sum(fsum);
         if (lane == 0) {
-            red_i[wv] = bits; red_d[0][wv] = msum; red_d[1][wv] = lsum;
+            red_i[wv] = bits; red_d[0][wv] = msum; red_d[1][wv] = lsum; red_v[wv] = vmax;
             if constexpr (FLD) red_d[2][wv] = fsum;
         }
         __syncthreads();
-        if (wv == 0) {
+        if (tid == 0) {
+            double ms = 0.0, ls = 0.0;
+#pragma unroll
+            for (int q = 0; q < NWAVE; ++q) {
+                ms += red_d[0][q]; ls += red_d[1][q];
+                vm = fmax(vm, (double)red_v[q]);
+                anybad |= (red_i[q] & 128) != 0;
+            }
+            a.mass[tile] = ms;
+            a.ledger[tile] = led + ls * a.h_d * a.h_d;
+            if constexpr (FLD) {
+                double fs = 0.0;
+                for (int q = 0; q < NWAVE; ++q) fs += red_d[2][q];
+                a.fvol[tile] = fvo + fs * a.h_d * a.h_d;
+            }
+        }
+        if (a.skip && wv == NWAVE - 1) {
+            // next list: this tile if K1-active at layer n (appended
+            // already) or n+1, and the neighbours facing its wet edges
+            // (layer n+1) unless their stamps show them listed
             int bb = 0;
 #pragma unroll
             for (int q = 0; q < NWAVE; ++q) bb |= red_i[q];
-            if (lane == 0) {
-                double ms = 0.0, ls = 0.0;
-                for (int q = 0; q < NWAVE; ++q) { ms += red_d[0][q]; ls += red_d[1][q]; }
-                a.mass[tile] = ms;
-                a.ledger[tile] = led + ls * a.h_d * a.h_d;
-                if constexpr (FLD) {
-                    double fs = 0.0;
-                    for (int q = 0; q < NWAVE; ++q) fs += red_d[2][q];
-                    a.fvol[tile] = fvo + fs * a.h_d * a.h_d;
-                }
-            }
-            if (a.skip) {
-                // next list: this tile if K1-active at layer n (appended
-                // already) or n+1, and the neighbours facing its wet edges
-                // (layer n+1) unless their stamps show them listed
-                const int ti = tile % a.ntx, tj = tile / a.ntx;
-                const bool fresh = nbst < gen;
-                int cand = -1;
-                if (lane == 0 && !(bb & 64) && (bb & (1 | 32))) cand = tile;
-                constexpr bool PER = MODE == MODE_PERIODIC;   // neighbours wrap round the domain
-                if (lane == 1 && (bb & 2) && fresh && (ti > 0 || PER)) cand = ti > 0 ? tile - 1 : tile + a.ntx - 1;
-                if (lane == 2 && (bb & 4) && fresh && (ti < a.ntx - 1 || PER))
-                    cand = ti < a.ntx - 1 ? tile + 1 : tile - a.ntx + 1;
-                if (lane == 3 && (bb & 8) && fresh && (tj > 0 || PER))
-                    cand = tj > 0 ? tile - a.ntx : tile + (a.nty - 1) * a.ntx;
-                if (lane == 4 && (bb & 16) && fresh && (tj < a.nty - 1 || PER))
-                    cand = tj < a.nty - 1 ? tile + a.ntx : tile - (a.nty - 1) * a.ntx;
-                if (RING && cand >= 0 && ring_tile(a, cand)) cand = -1;
-                append_tiles(cand, 0, 0, gen, a.stamp, a.lists, a.hot, a.ntiles, a.slot ^ 1, grp);
-            }
+            const int ti = tile % a.ntx, tj = tile / a.ntx;
+            const bool fresh = nbst < gen;
+            int cand = -1;
+            if (lane == 0 && !(bb & 64) && (bb & (1 | 32))) cand = tile;
+            constexpr bool PER = MODE == MODE_PERIODIC;   // neighbours wrap round the domain
+            if (lane == 1 && (bb & 2) && fresh && (ti > 0 || PER)) cand = ti > 0 ? tile - 1 : tile + a.ntx - 1;
+            if (lane == 2 && (bb & 4) && fresh && (ti < a.ntx - 1 || PER))
+                cand = ti < a.ntx - 1 ? tile + 1 : tile - a.ntx + 1;
+            if (lane == 3 && (bb & 8) && fresh && (tj > 0 || PER))
+                cand = tj > 0 ? tile - a.ntx : tile + (a.nty - 1) * a.ntx;
+            if (lane == 4 && (bb & 16) && fresh && (tj < a.nty - 1 || PER))
+                cand = tj < a.nty - 1 ? tile + a.ntx : tile - (a.nty - 1) * a.ntx;
+            if (RING && cand >= 0 && ring_tile(a, cand)) cand = -1;
+            append_tiles(cand, 0, 0, gen, a.stamp, a.lists, a.hot, a.ntiles, a.slot ^ 1, grp);
         }
     }
 
@@ -1377,22 +1449,25 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> 
     // arrival is counted with the cells: when the count completes, every
     // workgroup's contributions have been performed, and no memory fence is
     // needed on the way (the tile outputs and list entries are for the next
-    // launch).  The last arrival of the last group finalises.
-    vmax = wave_max(vmax);
-    __syncthreads();
-    if (lane == 0) red_d[0][wv] = (double)vmax;
-    const int anybad = __syncthreads_or((int)bad);
+    // launch).  The last wave's appends run beside the speed's round trip; the
+    // barrier has them performed (each append uses its atomics' results)
+    // before the arrival is counted.  The last arrival of the last group
+    // finalises.
+    bool sent = true;
     if (tid == 0) {
-        double vm = 0.0;
-        for (int q = 0; q < NWAVE; ++q) vm = fmax(vm, red_d[0][q]);
         unsigned long long* const h64 = reinterpret_cast<unsigned long long*>(a.hot);
         const int err_was = anybad ? atomicCAS(&ctrl->err, 0, -4) : 0;
         unsigned long long sp = 0;
-        if (err_was != INT_MIN)   // always: waits for the error
+        if (err_was != INT_MIN && vm > 0.0)   // the first always: waits for the error
             sp = atomicMax(&h64[hot_spd(grp) / 2], (unsigned long long)__double_as_longlong(vm));
+        sent = sp != ~0ull;                   // always (no speed has these bits): waits for the maximum
+    }
+    __syncthreads();
+    if (tid == 0) {
+        unsigned long long* const h64 = reinterpret_cast<unsigned long long*>(a.hot);
         const int in_grp = (G - grp + NSEG - 1) / NSEG, ngrp = G < NSEG ? G : NSEG;
         bool last = false;
-        if (sp != ~0ull) {        // always (no speed has these bits): waits for the maximum
+        if (sent) {
             const unsigned long long old =
                 atomicAdd(&h64[hot_cnt(grp) / 2], ((unsigned long long)ncells << CNT_BITS) | 1ull);
             if ((int)(old & ((1ull << CNT_BITS) - 1)) == in_grp - 1)
@@ -1506,9 +1581,7 @@ __global__ __launch_bounds__(NT) void k_prepare(Args<real> a) {
     }
     vmax = wave_max(vmax);
     msum = wave_sum(msum);
-    int any = act;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) any |= __shfl_xor(any, o, 64);
+    const int any = wave_or(act);
     const int lane = tid & 63, wv = tid >> 6;
     if (lane == 0) { red_v[wv] = vmax; red_d[wv] = msum; red_i[wv] = any; }
     __syncthreads();
@@ -1595,29 +1668,48 @@ struct BatchArgs {
     int* lists;
     int list_cap;             // capacity of one list segment (all tiles of the batch)
     int slot;                 // list slot read by this step
-    long long* wg_cells;
 };
+
+// A scenario's arguments for a workgroup: `sid` is the same in every lane and
+// the array does not change while kernels run, so the fields come through the
+// scalar cache into scalar registers.  Read through a plain reference they
+// were fetched by vector loads inside every stage, each a memory round trip
+// after the tile's stores.
+template <typename real>
+__device__ __forceinline__ Args<real> scalar_args(const Args<real>* scen, int sid) {
+    typedef const __attribute__((address_space(4))) unsigned* cptr;
+    static_assert(sizeof(Args<real>) % 4 == 0 && alignof(Args<real>) >= 4, "copied as words");
+    const cptr src = (cptr)(uintptr_t)(scen + __builtin_amdgcn_readfirstlane(sid));
+    union U { Args<real> a; unsigned w[sizeof(Args<real>) / 4]; __device__ U() {} } u;
+#pragma unroll
+    for (unsigned k = 0; k < sizeof(Args<real>) / 4; ++k) u.w[k] = src[k];
+    return u.a;
+}
 
 template <typename real, int TX, int TY, int NT, int LIM>
 __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_batch_step(BatchArgs<real> ba) {
     constexpr int NWAVE = NT / 64;
     __shared__ Lds<real, TX, TY> L;
-    __shared__ double red_d[3][NWAVE];
-    __shared__ int red_i[NWAVE];
-    __shared__ long long red_l[NWAVE];
+    __shared__ double red_d[2][NWAVE];
+    __shared__ real red_v[NWAVE];
+    __shared__ int red_i[NWAVE], s_act[NWAVE];
     __shared__ int s_last;
 
     Ctrl* const lc = ba.lctrl;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int G = gridDim.x, grp = blockIdx.x % NSEG;
-    const int count = lc->seg_off[ba.slot][NSEG];
+    int off[NSEG + 1];
+#pragma unroll
+    for (int g = 0; g <= NSEG; ++g) off[g] = lc->seg_off[ba.slot][g];
+    const int count = off[NSEG];
     const int gen = (int)lc->step + 2;
     long long ncells = 0;
+    unsigned long long ack = 0, pend = 0;   // thread 0: results of the speed and error atomics
 
     for (int p = blockIdx.x; p < count; p += G) {
-        const int e = list_entry(lc, ba.lists, ba.list_cap, ba.slot, p);
+        const int e = __builtin_amdgcn_readfirstlane(list_entry(off, ba.lists, ba.list_cap, ba.slot, p));
         const int sid = entry_sid(e), tile = entry_tile(e);
-        const Args<real>& a = ba.scen[sid];
+        const Args<real> a = scalar_args(ba.scen, sid);
         Ctrl* const c = a.ctrl;
         if (c->err_gate) continue;   // a stopped scenario drops out of the lists
         const real tau = (real)c->tau, sdep = (real)c->sdepth;
@@ -1631,66 +1723,74 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_batch_step(Batch
         int bits = 0, nbst = gen;
         const double led = tid == 0 ? a.ledger[tile] : 0.0;
         const ListCtx lx{a.stamp, ba.lists, ba.hot, ba.list_cap, ba.slot ^ 1, grp, gen, sid, a.tile_base, tile,
-                         a.ntx, a.nty, a.skip != 0, clock_bits(a.ctrl->t)};
-        __syncthreads();   // LDS of the previous tile is free
+                         a.ntx, a.nty, a.skip != 0, clock_bits(c->t)};
         if (edge)
             tile_step<real, TX, TY, NT, LIM, true, MODE_PLAIN>(a, L, tx0, ty0, tau, sdep, vt, bad, msum, lsum, fnone,
-                                                               0, bits, lx, nbst);
+                                                               0, bits, lx, nbst, s_act);
         else
             tile_step<real, TX, TY, NT, LIM, false, MODE_PLAIN>(a, L, tx0, ty0, tau, sdep, vt, bad, msum, lsum, fnone,
-                                                                0, bits, lx, nbst);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) bits |= __shfl_xor(bits, o, 64);
-        bits |= __any(bad) ? 128 : 0;
+                                                                0, bits, lx, nbst, s_act);
+        bits = wave_or(bits | (bad ? 128 : 0));
         msum = wave_sum(msum);
         lsum = wave_sum(lsum);
         vt = wave_max(vt);
-        if (lane == 0) { red_i[wv] = bits; red_d[0][wv] = msum; red_d[1][wv] = lsum; red_d[2][wv] = (double)vt; }
+        if (lane == 0) { red_i[wv] = bits; red_d[0][wv] = msum; red_d[1][wv] = lsum; red_v[wv] = vt; }
         __syncthreads();
-        if (wv == 0) {
+        if (tid == 0) {
+            double ms = 0.0, ls = 0.0;
+            real vm = real(0);
+            int bb = 0;
+#pragma unroll
+            for (int q = 0; q < NWAVE; ++q) {
+                ms += red_d[0][q]; ls += red_d[1][q]; vm = rmax(vm, red_v[q]); bb |= red_i[q];
+            }
+            a.mass[tile] = ms;
+            a.ledger[tile] = led + ls * a.h_d * a.h_d;
+            // their results are waited for a tile later (or below)
+            ack |= pend;
+            pend = 0;
+            if (vm > real(0)) pend = atomic_max_prep(c, vm);
+            if (bb & 128) ack |= (unsigned long long)(unsigned)atomicCAS(&c->err, 0, -4);
+        }
+        if (a.skip && wv == NWAVE - 1) {
             int bb = 0;
 #pragma unroll
             for (int q = 0; q < NWAVE; ++q) bb |= red_i[q];
-            if (lane == 0) {
-                double ms = 0.0, ls = 0.0, vm = 0.0;
-                for (int q = 0; q < NWAVE; ++q) { ms += red_d[0][q]; ls += red_d[1][q]; vm = fmax(vm, red_d[2][q]); }
-                a.mass[tile] = ms;
-                a.ledger[tile] = led + ls * a.h_d * a.h_d;
-                if (vm > 0.0) atomic_max_prep(c, (real)vm);
-                if (bb & 128) atomicCAS(&c->err, 0, -4);
-            }
-            if (a.skip) {
-                const int ti = tile % a.ntx, tj = tile / a.ntx;
-                const bool fresh = nbst < gen;
-                int cand = -1;
-                if (lane == 0 && !(bb & 64) && (bb & (1 | 32))) cand = tile;
-                if (lane == 1 && (bb & 2) && ti > 0 && fresh) cand = tile - 1;
-                if (lane == 2 && (bb & 4) && ti < a.ntx - 1 && fresh) cand = tile + 1;
-                if (lane == 3 && (bb & 8) && tj > 0 && fresh) cand = tile - a.ntx;
-                if (lane == 4 && (bb & 16) && tj < a.nty - 1 && fresh) cand = tile + a.ntx;
-                append_tiles(cand, sid, a.tile_base, gen, a.stamp, ba.lists, ba.hot, ba.list_cap, ba.slot ^ 1, grp);
-            }
+            const int ti = tile % a.ntx, tj = tile / a.ntx;
+            const bool fresh = nbst < gen;
+            int cand = -1;
+            if (lane == 0 && !(bb & 64) && (bb & (1 | 32))) cand = tile;
+            if (lane == 1 && (bb & 2) && ti > 0 && fresh) cand = tile - 1;
+            if (lane == 2 && (bb & 4) && ti < a.ntx - 1 && fresh) cand = tile + 1;
+            if (lane == 3 && (bb & 8) && tj > 0 && fresh) cand = tile - a.ntx;
+            if (lane == 4 && (bb & 16) && tj < a.nty - 1 && fresh) cand = tile + a.ntx;
+            append_tiles(cand, sid, a.tile_base, gen, a.stamp, ba.lists, ba.hot, ba.list_cap, ba.slot ^ 1, grp);
         }
     }
 
-    // ---- completion: two-level counter; the last workgroup finalises every scenario
+    // ---- completion, as in k_step: every contribution is an atomic that has
+    // returned before the arrival is counted, so no workgroup writes back its
+    // L2; the last workgroup finalises every scenario
+    if (tid == 0) ack |= pend;
+    // the acknowledgements (never all ones: a speed is no NaN of that bit
+    // pattern) are only there to be waited for
+    const bool sent = ack != ~0ull;
+    __syncthreads();
     if (tid == 0) {
-        ba.wg_cells[blockIdx.x] = ncells;
-        __threadfence();
+        unsigned long long* const h64 = reinterpret_cast<unsigned long long*>(ba.hot);
         const int in_grp = (G - grp + NSEG - 1) / NSEG, ngrp = G < NSEG ? G : NSEG;
         bool last = false;
-        if (atomicAdd((unsigned*)&ba.hot[hot_done(grp)], 1u) == (unsigned)(in_grp - 1))
-            last = atomicAdd((unsigned*)&ba.hot[hot_done(NSEG)], 1u) == (unsigned)(ngrp - 1);
+        if (sent) {
+            const unsigned long long old =
+                atomicAdd(&h64[hot_cnt(grp) / 2], ((unsigned long long)ncells << CNT_BITS) | 1ull);
+            if ((int)(old & ((1ull << CNT_BITS) - 1)) == in_grp - 1)
+                last = atomicAdd((unsigned*)&ba.hot[hot_done(NSEG)], 1u) == (unsigned)(ngrp - 1);
+        }
         s_last = last;
     }
     __syncthreads();
     if (!s_last) return;
-    __threadfence();
-    long long cs = 0;
-    for (int k = tid; k < G; k += NT) cs += ba.wg_cells[k];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) cs += __shfl_xor(cs, o, 64);
-    if (lane == 0) red_l[wv] = cs;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     for (int k = tid; k < ba.n; k += NT) {
         const Args<real>& a = ba.scen[k];
         Ctrl c = *a.ctrl;   // all reads first, one write-back
@@ -1705,23 +1805,24 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_batch_step(Batch
         if (c.err) c.err_gate = c.err;
         *a.ctrl = c;
     }
-    __syncthreads();
-    if (tid == 0) {
+    if (tid == NT - 64) {   // beside the scenarios' wave
         Ctrl c = *lc;
         int nseg[NSEG];
-#pragma unroll
-        for (int g = 0; g < NSEG; ++g) nseg[g] = ba.hot[hot_seg(ba.slot ^ 1, g)];
+        unsigned long long* const h64 = reinterpret_cast<unsigned long long*>(ba.hot);
         long long cells = 0;
-        for (int q = 0; q < NWAVE; ++q) cells += red_l[q];
+#pragma unroll
+        for (int g = 0; g < NSEG; ++g) {
+            nseg[g] = ba.hot[hot_seg(ba.slot ^ 1, g)];
+            cells += (long long)(h64[hot_cnt(g) / 2] >> CNT_BITS);
+        }
         c.step += 1;
         c.tiles += count;
         c.cells += cells;
         *lc = c;
         close_segments_from(lc, nseg, ba.slot ^ 1);
-        for (int g = 0; g < NSEG; ++g) ba.hot[hot_seg(ba.slot, g)] = 0;
-        for (int g = 0; g <= NSEG; ++g) ba.hot[hot_done(g)] = 0;
+        for (int g = 0; g < NSEG; ++g) { ba.hot[hot_seg(ba.slot, g)] = 0; h64[hot_cnt(g) / 2] = 0ull; }
+        ba.hot[hot_done(NSEG)] = 0;
     }
-    __threadfence();
 }
 
 // After the per-scenario preparation kernels: first time steps and list offsets.

@@ -644,19 +644,34 @@ struct Lds {
 };
 
 // Copy mirror images into the positions of [x0, x1) x [y0, y1) (tile
-// coordinates) that lie outside the domain.  Bit q of sgx / sgy marks array
-// q as the x / y component of a vector (its sign flips across that wall).
+// coordinates) that lie outside the domain, up to HALO cells beyond it (the
+// reach of a step).  Bit q of sgx / sgy marks array q as the x / y component
+// of a vector (its sign flips across that wall).  Only the bands outside are
+// walked -- whole rows below and above the domain, then the cells left and
+// right of it -- which one pass of the workgroup covers on a tile at one wall
+// (testing every window cell took 1.2 us per call, three calls a tile).
 template <typename real, int TX, int TY, int NT>
 __device__ void fill_ghosts(int tx0, int ty0, int nx, int ny, int x0, int x1, int y0, int y1,
                             real* f0, real* f1, real* f2, int sgx, int sgy) {
     using G = Geo<TX, TY>;
-    const int w = x1 - x0, n = w * (y1 - y0);
+    x1 = min(x1, nx - tx0 + HALO);
+    y1 = min(y1, ny - ty0 + HALO);
+    const int xa = max(x0, -tx0), xb = min(x1, nx - tx0), ya = max(y0, -ty0), yb = min(y1, ny - ty0);
+    const int w = x1 - x0, rows = (ya - y0) + (y1 - yb), side = (xa - x0) + (x1 - xb);
+    const int nrow = rows * w, n = nrow + side * (yb - ya);
     for (int k = threadIdx.x; k < n; k += NT) {
-        const int x = x0 + k % w, y = y0 + k / w;
-        const int gx = tx0 + x, gy = ty0 + y;
-        if (gx >= 0 && gx < nx && gy >= 0 && gy < ny) continue;
+        int x, y;
+        if (k < nrow) {
+            const int r = k / w;
+            x = x0 + k - r * w;
+            y = r < ya - y0 ? y0 + r : yb + r - (ya - y0);
+        } else {
+            const int r = (k - nrow) / side, c = k - nrow - r * side;
+            x = c < xa - x0 ? x0 + c : xb + c - (xa - x0);
+            y = ya + r;
+        }
         int fx = 0, fy = 0;
-        const int mx = mirror(gx, nx, fx) - tx0, my = mirror(gy, ny, fy) - ty0;
+        const int mx = mirror(tx0 + x, nx, fx) - tx0, my = mirror(ty0 + y, ny, fy) - ty0;
         const int s = G::at(x, y), m = G::at(mx, my);
         real* fs[3] = {f0, f1, f2};
 #pragma unroll
@@ -787,7 +802,12 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
     // period away, computed there exactly as in its own tile, so the walls'
     // ghost fills are not needed; nx and ny are multiples of the tile shape
     constexpr bool PER = MODE == MODE_PERIODIC;
-    const int tid = threadIdx.x, nx = a.nx, ny = a.ny;
+    // opaque: the stages' index arithmetic stays inside the tile loop instead
+    // of being hoisted into registers that spill (358 instructions ahead of
+    // the first tile's loads)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int nx = a.nx, ny = a.ny;
     auto wrapx = [&](int g) { if constexpr (PER) { g %= nx; if (g < 0) g += nx; } return g; };
     auto wrapy = [&](int g) { if constexpr (PER) { g %= ny; if (g < 0) g += ny; } return g; };
     const real eps = a.eps, half_tau = real(0.5) * tau, r = tau * a.ih;
@@ -1148,6 +1168,17 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
         if (nb >= 0) nbst = lx.stamp[lx.tile_base + nb];
     }
 
+    // c_f of the epilogue's cells again from memory (L2; P1 overwrote its LDS
+    // copy), under way while FY computes
+    constexpr int NOWN = (TX * TY + NT - 1) / NT;
+    real cfn[NOWN];
+#pragma unroll
+    for (int j = 0; j < NOWN; ++j) {
+        const int k = tid + j * NT, x = k % TX, y = k / TX;
+        const bool in = k < TX * TY && inside(x, y);
+        cfn[j] = a.cf[in ? (ty0 + y) * nx + tx0 + x : 0];
+    }
+
     // ---- FY + final update: columns -1..TX, runs along y with the low faces
     // of their cells, consecutive lanes holding consecutive runs of a column:
     // the side below a run comes from the lane before, the flux above it from
@@ -1207,20 +1238,31 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
 #pragma unroll
                 for (int f = 0; f < RFY + 1; ++f) { FH[f] = real(0); Fn[f] = real(0); Ft[f] = real(0); }
             }
+            // x fluxes and Q_t of the run's cells in one round of LDS reads
+            // (those of rows -2 and TY+1 are not used)
+            real fH[RFY][2], fN[RFY][2], fT[RFY][2], qxt[RFY], qyt[RFY];
+#pragma unroll
+            for (int i = 0; i < RFY; ++i) {
+                const int s = G::at(x, y0 + i);
+                fH[i][0] = L.HX[s]; fH[i][1] = L.HX[s + 1];
+                fN[i][0] = L.HY[s]; fN[i][1] = L.HY[s + 1];
+                fT[i][0] = L.H[s]; fT[i][1] = L.H[s + 1];
+                qxt[i] = L.GX[s]; qyt[i] = L.GY[s];
+            }
 #pragma unroll
             for (int i = 0; i < RFY; ++i) {
                 const int y = y0 + i;
                 if (!live || y < -1 || y > TY || !inside(x, y)) continue;
                 const int s = G::at(x, y);
-                const real dxH = L.HX[s] - L.HX[s + 1];
-                const real dxQx = L.HY[s] - L.HY[s + 1];
-                const real dxQy = L.H[s] - L.H[s + 1];
+                const real dxH = fH[i][0] - fH[i][1];
+                const real dxQx = fN[i][0] - fN[i][1];
+                const real dxQy = fT[i][0] - fT[i][1];
                 const real Ht = cl[i + 1].H, dH = r * (dxH + (FH[i] - FH[i + 1]));
                 real Hn = Ht + dH;
                 if constexpr (F32)
                     Hn = round_stochastic(Ht, dH, Hn, cell_hash((unsigned)((ty0 + y) * nx + tx0 + x), lx.clk));
-                const real qx = L.GX[s] + r * (dxQx + (Ft[i] - Ft[i + 1]));
-                const real qy = L.GY[s] + r * (dxQy + (Fn[i] - Fn[i + 1]));
+                const real qx = qxt[i] + r * (dxQx + (Ft[i] - Ft[i + 1]));
+                const real qy = qyt[i] + r * (dxQy + (Fn[i] - Fn[i + 1]));
                 const real Hc = rmax(Hn, real(0));
                 const bool w = Hc > eps;
                 const real qxo = w ? qx : real(0), qyo = w ? qy : real(0);
@@ -1238,9 +1280,9 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
                     if constexpr (TAP) {
                         if (tap_here) {
                             if (a.tap_r > 0)
-                                tap_lines(a, tx0 + x, ty0 + y, tau, L.HX[s], L.HY[s], L.H[s], FH[i], Fn[i], Ft[i]);
+                                tap_lines(a, tx0 + x, ty0 + y, tau, fH[i][0], fN[i][0], fT[i][0], FH[i], Fn[i], Ft[i]);
                             else
-                                tap_faces(a, tx0 + x, ty0 + y, tau, L.HX[s], L.HY[s], L.H[s], FH[i], Fn[i], Ft[i]);
+                                tap_faces(a, tx0 + x, ty0 + y, tau, fH[i][0], fN[i][0], fT[i][0], FH[i], Fn[i], Ft[i]);
                         }
                     }
                 }
@@ -1256,26 +1298,16 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
 
     // ---- epilogue: CFL speed of layer n+1 on the tile, K1 bits of layer n+1
     {
-        constexpr int NT_CELLS = TX * TY, NRING = 2 * (TX + TY);
+        constexpr int NRING = 2 * (TX + TY);
         int own = 0, eW = 0, eE = 0, eS = 0, eN = 0, rg = 0;
-        for (int k = tid; k < NT_CELLS + NRING; k += NT) {
-            int x, y;
-            if (k < NT_CELLS) {
-                x = k % TX; y = k / TX;
-            } else {
-                const int q = k - NT_CELLS;   // ring: S row, N row, W column, E column
-                if (q < TX) { x = q; y = -1; }
-                else if (q < 2 * TX) { x = q - TX; y = TY; }
-                else if (q < 2 * TX + TY) { x = -1; y = q - 2 * TX; }
-                else { x = TX; y = q - 2 * TX - TY; }
-            }
-            if (!inside(x, y)) continue;
+#pragma unroll
+        for (int j = 0; j < NOWN; ++j) {
+            const int k = tid + j * NT, x = k % TX, y = k / TX;
+            if (k >= TX * TY || !inside(x, y)) continue;
             const int s = G::at(x, y);
             const real H = L.NH[s];
             const bool w = H > eps;
-            const bool ws = w || source(x, y);
-            if (k >= NT_CELLS) { rg |= ws; continue; }
-            if (ws) {
+            if (w || source(x, y)) {
                 own = 1;
                 eW |= x == 0; eE |= x == TX - 1; eS |= y == 0; eN |= y == TY - 1;
             }
@@ -1287,12 +1319,15 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
                     nb.ux[q] = L.GX[sn[q]]; nb.uy[q] = L.GY[sn[q]]; nb.w[q] = L.NH[sn[q]] > eps;
                 }
                 const real ux = L.GX[s], uy = L.GY[s];
-                // c_f again from memory (L2): P1 overwrote its LDS copy
-                const real cf = a.cf[(ty0 + y) * nx + tx0 + x];
                 real fx, fy;
                 soft_forces(a, H, ux, uy, nb, fx, fy);
-                vmax = rmax(vmax, cfl_speed(a, H, cf, ux, uy, fx, fy));
+                vmax = rmax(vmax, cfl_speed(a, H, cfn[j], ux, uy, fx, fy));
             }
+        }
+        for (int q = tid; q < NRING; q += NT) {   // ring: S row, N row, W column, E column
+            const int x = q < 2 * TX ? q % TX : (q < 2 * TX + TY ? -1 : TX);
+            const int y = q < 2 * TX ? (q < TX ? -1 : TY) : (q - 2 * TX) % TY;
+            if (inside(x, y)) rg |= L.NH[G::at(x, y)] > eps || source(x, y);
         }
         bits |= own | (eW << 1) | (eE << 2) | (eS << 3) | (eN << 4) | (rg << 5);
     }
@@ -1330,7 +1365,6 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> 
     const int b0 = blockIdx.x;
     const bool spec_in = !RING && a.skip && b0 / NSEG < a.ntiles;
     const int spec = spec_in ? a.lists[(a.slot * NSEG + b0 % NSEG) * a.ntiles + b0 / NSEG] : 0;
-    if (ctrl->err_gate) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int G = gridDim.x, grp = blockIdx.x % NSEG;
     // only the patches of a nest (tapping grids) carry ring tiles; the other
@@ -1358,6 +1392,9 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> 
         first = e < 0 ? -1 : entry_tile(e);
     }
     const int npos = own ? (first >= 0 ? b0 + 1 : 0) : count;
+    // a stopped run: tested after every read above is under way, so that the
+    // control block costs one round trip
+    if (ctrl->err_gate) return;
 
     long long ncells = 0;
     double vm = 0.0;      // thread 0: speed maximum and error of the workgroup's tiles

@@ -134,8 +134,8 @@ const Launcher kLaunchers[] = {
     LAUNCHERS(float, 32, 32, SWE_F32_THREADS, 32, TAP_STEP),
     LAUNCHERS(float, 64, 16, 512, 32, NO_TAP_STEP),
     LAUNCHERS(float, 16, 16, 256, 32, NO_TAP_STEP),
-    LAUNCHERS(double, 16, 16, 256, 64, TAP_STEP),
-    LAUNCHERS(double, 32, 16, 256, 64, NO_TAP_STEP),
+    LAUNCHERS(double, 16, 16, 512, 64, TAP_STEP),
+    LAUNCHERS(double, 32, 16, 512, 64, NO_TAP_STEP),
 };
 
 const Launcher* find_launcher(int precision, int tx, int ty, int limiter) {

@@ -814,15 +814,17 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
     // normalised cubic-B-spline SPH gradient weights (smoothing length h):
     // al = 1/(12 sqrt2 - 14), be = (3 sqrt2 - 4)/(12 sqrt2 - 14), 2 al + 4 be = 1
     const real al = real(0.33663655161388173), be = real(0.08168172419305914);
-    // Cells per thread along the run of each stage.  FP32 kernels run four
-    // waves per SIMD (128 VGPRs), which short runs fit without spilling: 2 in
-    // P1/P2, 3 in FX/FY where the cell count divides, so that one pass of a
-    // 512-thread workgroup covers a 32-wide tile.  FP64 keeps runs of 4 in
-    // P1/P2; its flux runs are short, for more lanes at work.
+    // Cells per thread along the run of each stage, for 512 threads at four
+    // waves per SIMD (128 VGPRs).  FP32: 2 in P1/P2, 3 in FX/FY where the cell
+    // count divides, so that one pass of the workgroup covers a 32-wide tile.
+    // FP64 tiles are small and their arithmetic is a long dependent chain per
+    // cell (IEEE divisions, cbrt): one cell per thread keeps the chain short
+    // and every SIMD at work.  With 256 threads and runs of 4 a 256-tile step
+    // took 19.6 us, P1 and P2 more than half of it on three waves; so 16.3.
     constexpr bool F32 = sizeof(real) == 4;
-    constexpr int RP = F32 ? 2 : 4;
-    constexpr int RFX = (TX + 4) % 3 == 0 ? 3 : (F32 && TX > 32 ? 4 : 2);
-    constexpr int RFY = (TY + 4) % 3 == 0 ? 3 : 2;
+    constexpr int RP = F32 ? 2 : 1;
+    constexpr int RFX = F32 ? ((TX + 4) % 3 == 0 ? 3 : TX > 32 ? 4 : 2) : (TX > 16 ? 2 : 1);
+    constexpr int RFY = F32 ? ((TY + 4) % 3 == 0 ? 3 : 2) : 1;
     constexpr int NWAVE = NT / 64;
     static_assert((TX + 8) % RP == 0 && (TX + 4) % RFX == 0 && (TY + 4) % RFY == 0,
                   "run lengths must tile the stage rows");
@@ -902,7 +904,7 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
     int e_old = lx.gen, e_base = 0;
     if (early) e_old = atomicMax(&lx.stamp[lx.tile_base + lx.tile], lx.gen);
 
-    // ---- P1: forces at t_n and predictor on tile + 4, runs of 4 along x
+    // ---- P1: forces at t_n and predictor on tile + 4, runs along x
     {
         constexpr int NRW = (TX + 8) / RP, NRH = TY + 8, NR = NRW * NRH;
         for (int k = tid; k < NR; k += NT) {
@@ -1010,9 +1012,10 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
 
     // ---- P2: forces at t_{n+1/2}, corrector, sources on tile + 3
     {
-        constexpr int NRW = (TX + 8) / RP, NRH = TY + 6, NR = NRW * NRH;
+        static_assert((TX + 6) % RP == 0, "run lengths must tile the stage rows");
+        constexpr int NRW = (TX + 6) / RP, NRH = TY + 6, NR = NRW * NRH;
         for (int k = tid; k < NR; k += NT) {
-            const int y = k % NRH - 3, x0 = (k / NRH) * RP - 4;
+            const int y = k % NRH - 3, x0 = (k / NRH) * RP - 3;
             real hx[RP + 2], hy[RP + 2], Hr[RP + 2];
             bool wr[RP + 2];
 #pragma unroll
@@ -1324,7 +1327,9 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
                 vmax = rmax(vmax, cfl_speed(a, H, cfn[j], ux, uy, fx, fy));
             }
         }
-        for (int q = tid; q < NRING; q += NT) {   // ring: S row, N row, W column, E column
+        // ring: S row, N row, W column, E column, from the last thread down
+        // (the first ones hold the own cells of a small tile)
+        for (int q = NT - 1 - tid; q < NRING; q += NT) {
             const int x = q < 2 * TX ? q % TX : (q < 2 * TX + TY ? -1 : TX);
             const int y = q < 2 * TX ? (q < TX ? -1 : TY) : (q - 2 * TX) % TY;
             if (inside(x, y)) rg |= L.NH[G::at(x, y)] > eps || source(x, y);
@@ -1342,7 +1347,7 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
 #define SWE_WAVES_PER_SIMD_F32 4
 #endif
 #ifndef SWE_WAVES_PER_SIMD_F64
-#define SWE_WAVES_PER_SIMD_F64 2
+#define SWE_WAVES_PER_SIMD_F64 4
 #endif
 template <typename real> constexpr int waves_per_simd() {
     return sizeof(real) == 4 ? SWE_WAVES_PER_SIMD_F32 : SWE_WAVES_PER_SIMD_F64;

@@ -8,6 +8,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -20,6 +21,7 @@
 
 #include "../../include/swe.h"
 #include "swe_step.hpp"
+#include "swe_xfer.hpp"
 
 using swe::Args;
 using swe::Ctrl;
@@ -149,6 +151,9 @@ const Launcher* find_launcher(int precision, int tx, int ty, int limiter) {
 }  // namespace
 
 struct swe_s {
+    swe_s() { xfer_retain(); }
+    ~swe_s() { xfer_release(); }
+    swe_s(const swe_s&) = delete;
     int nx = 0, ny = 0, precision = 32, rsize = 4;
     int ntx = 0, nty = 0, ntiles = 0, grid = 0, grid_max = 0;   // step launch grid, its default
     double h = 0.0;
@@ -297,35 +302,93 @@ void build_args(swe_t* s) {
 }
 
 int sync_ctrl(swe_t* s, Ctrl* out) {
-    HIPCHK(hipMemcpyAsync(out, s->ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipStreamSynchronize(s->stream));
+    HIPCHK(xfer_read(out, s->ctrl, sizeof(Ctrl), s->stream));
     return 0;
 }
 
 // Upload a host FP64 field as the stencil type.
-int upload(swe_t* s, void* dst, const double* src, double fill) {
-    const size_t n = (size_t)s->nx * s->ny;
-    std::vector<unsigned char> buf(n * s->rsize);
-    if (s->precision == 32) {
-        float* f = (float*)buf.data();
-        for (size_t i = 0; i < n; ++i) f[i] = (float)(src ? src[i] : fill);
-    } else {
-        double* d = (double*)buf.data();
-        for (size_t i = 0; i < n; ++i) d[i] = src ? src[i] : fill;
-    }
-    HIPCHK(hipMemcpyAsync(dst, buf.data(), n * s->rsize, hipMemcpyHostToDevice, s->stream));
-    HIPCHK(hipStreamSynchronize(s->stream));
+template <typename real>
+hipError_t upload_t(swe_t* s, void* dst, const double* src) {
+    const swe::FieldPair<real> f{(real*)dst, (real*)dst};
+    return xfer_put<real>(s->stream, 1, &f, (size_t)s->nx * s->ny, [&](int, size_t first, size_t cnt, real* o) {
+        for (size_t i = 0; i < cnt; ++i) o[i] = (real)src[first + i];
+    });
+}
+int upload(swe_t* s, void* dst, const double* src) {
+    HIPCHK(s->precision == 32 ? upload_t<float>(s, dst, src) : upload_t<double>(s, dst, src));
     return 0;
+}
+
+// Static fields: bed (closed gates raised far above any level), c_f = g n_M^2.
+template <typename real>
+hipError_t put_static(hipStream_t st, void* bed, void* cf, size_t n, const double* b, const double* n_M,
+                      const uint8_t* solid, double g) {
+    const swe::FieldPair<real> f[2] = {{(real*)bed, (real*)bed}, {(real*)cf, (real*)cf}};
+    return xfer_put<real>(st, 2, f, n, [=](int q, size_t first, size_t cnt, real* o) {
+        for (size_t k = 0; k < cnt; ++k) {
+            const size_t i = first + k;
+            const bool gate = solid && solid[i];
+            o[k] = q == 0 ? (real)(gate ? swe::GATE_BED : b[i]) : (real)(gate || !n_M ? 0.0 : g * n_M[i] * n_M[i]);
+        }
+    });
+}
+
+// A layer into both buffers of each pair (the other one must hold the same
+// layer for skipped tiles); dry cells are at rest, closed gates dry.
+template <typename real>
+hipError_t put_layer(hipStream_t st, void* const (&Hb)[2], void* const (&Qxb)[2], void* const (&Qyb)[2], size_t n,
+                     const double* H, const double* Qx, const double* Qy, const uint8_t* solid, double eps) {
+    const swe::FieldPair<real> f[3] = {{(real*)Hb[0], (real*)Hb[1]}, {(real*)Qxb[0], (real*)Qxb[1]},
+                                       {(real*)Qyb[0], (real*)Qyb[1]}};
+    return xfer_put<real>(st, 3, f, n, [=](int q, size_t first, size_t cnt, real* o) {
+        const double* h = H ? H + first : nullptr;
+        const double* Q = q == 1 ? Qx : Qy;
+        if (!h || (q > 0 && !Q)) {
+            for (size_t k = 0; k < cnt; ++k) o[k] = real(0);
+            return;
+        }
+        const double* v = q > 0 ? Q + first : h;
+        const double floor = q > 0 ? eps : -1.0;
+        for (size_t k = 0; k < cnt; ++k) o[k] = (real)(h[k] > floor ? v[k] : 0.0);
+        if (solid)
+            for (size_t k = 0; k < cnt; ++k)
+                if (solid[first + k]) o[k] = real(0);
+    });
+}
+
+bool all_finite(const double* x, size_t n) { return xfer_within(x, n, -DBL_MAX, DBL_MAX); }
+bool layer_ok(size_t n, const double* H, const double* Qx, const double* Qy) {
+    return xfer_within(H, n, 0.0, DBL_MAX) && all_finite(Qx, n) && all_finite(Qy, n);
+}
+
+// The rectangle (x0, y0, w x h) of the current layer of a grid of nx columns.
+int get_layer(hipStream_t st, int precision, const Ctrl* ctrl, void* const (&Hb)[2], void* const (&Qxb)[2],
+              void* const (&Qyb)[2], int nx, int x0, int y0, int w, int h, double* H, double* Qx, double* Qy) {
+    double* const out[3] = {H, Qx, Qy};
+    if (precision == 32) {
+        float* const a[3] = {(float*)Hb[0], (float*)Qxb[0], (float*)Qyb[0]};
+        float* const b[3] = {(float*)Hb[1], (float*)Qxb[1], (float*)Qyb[1]};
+        HIPCHK(xfer_get<float>(st, ctrl, a, b, nx, x0, y0, w, h, out));
+    } else {
+        double* const a[3] = {(double*)Hb[0], (double*)Qxb[0], (double*)Qyb[0]};
+        double* const b[3] = {(double*)Hb[1], (double*)Qxb[1], (double*)Qyb[1]};
+        HIPCHK(xfer_get<double>(st, ctrl, a, b, nx, x0, y0, w, h, out));
+    }
+    return 0;
+}
+
+int grid_for_cells(long long n) {
+    long long b = (n + 255) / 256;
+    return (int)(b < 1 ? 1 : (b > 4096 ? 4096 : b));
 }
 
 // Recompute the layer bookkeeping of the current buffer pair: wet tiles,
 // next time step, volume partials.
 int prepare(swe_t* s) {
     const int par = (int)(s->launched & 1);
-    HIPCHK(hipMemsetAsync(s->stamp, 0, sizeof(int) * s->ntiles, s->stream));
-    HIPCHK(hipMemsetAsync(s->hot, 0, sizeof(int) * swe::HOT_INTS, s->stream));
-    char* cb = (char*)s->ctrl;
-    HIPCHK(hipMemsetAsync(cb + offsetof(Ctrl, prep_speed), 0, sizeof(unsigned long long), s->stream));
+    hipLaunchKernelGGL(swe::k_prepare_clear, dim3(grid_for_cells(s->ntiles)), dim3(256), 0, s->stream, s->ctrl, s->hot,
+                       s->stamp, s->ntiles);
+    HIPCHK(hipGetLastError());
     // k_prepare appends to the list slot `par` and reads the buffer pair `par`
     HIPCHK(s->L->prepare(s->args[par].data(), s->ntiles, s->stream));
     HIPCHK(s->L->prepare_finish(s->args[par].data(), s->stream));
@@ -336,26 +399,12 @@ int prepare(swe_t* s) {
 int set_state_impl(swe_t* s, const double* H, const double* Qx, const double* Qy,
                    const uint8_t* solid) {
     const size_t n = (size_t)s->nx * s->ny;
-    std::vector<double> h(n), qx(n), qy(n);
-    for (size_t i = 0; i < n; ++i) {
-        double hh = H ? H[i] : 0.0, a = Qx ? Qx[i] : 0.0, b = Qy ? Qy[i] : 0.0;
-        if (!std::isfinite(hh) || !std::isfinite(a) || !std::isfinite(b) || hh < 0.0) {
-            set_err("state: depth must be finite and >= 0, discharges finite");
-            return SWE_EINVAL;
-        }
-        if (solid && solid[i]) hh = a = b = 0.0;
-        if (!(hh > s->p.eps)) a = b = 0.0;   // dry cells are at rest
-        h[i] = hh; qx[i] = a; qy[i] = b;
+    if (!layer_ok(n, H, Qx, Qy)) {
+        set_err("state: depth must be finite and >= 0, discharges finite");
+        return SWE_EINVAL;
     }
-    const int par = (int)(s->launched & 1);
-    int rc;
-    if ((rc = upload(s, s->Hb[par], h.data(), 0.0))) return rc;
-    if ((rc = upload(s, s->Qxb[par], qx.data(), 0.0))) return rc;
-    if ((rc = upload(s, s->Qyb[par], qy.data(), 0.0))) return rc;
-    // the other buffer of the pair must hold the same layer for skipped tiles
-    if ((rc = upload(s, s->Hb[par ^ 1], h.data(), 0.0))) return rc;
-    if ((rc = upload(s, s->Qxb[par ^ 1], qx.data(), 0.0))) return rc;
-    if ((rc = upload(s, s->Qyb[par ^ 1], qy.data(), 0.0))) return rc;
+    HIPCHK(s->precision == 32 ? put_layer<float>(s->stream, s->Hb, s->Qxb, s->Qyb, n, H, Qx, Qy, solid, s->p.eps)
+                              : put_layer<double>(s->stream, s->Hb, s->Qxb, s->Qyb, n, H, Qx, Qy, solid, s->p.eps));
     return prepare(s);
 }
 
@@ -466,11 +515,6 @@ int set_dt_now(swe_t* s, double tau) {
     return 0;
 }
 
-int grid_for_cells(long long n) {
-    long long b = (n + 255) / 256;
-    return (int)(b < 1 ? 1 : (b > 4096 ? 4096 : b));
-}
-
 int finish(swe_t* s) {
     Ctrl c;
     int rc = sync_ctrl(s, &c);
@@ -529,10 +573,8 @@ static swe_t* create_grid(int nx, int ny, double dx, const double* b, const doub
         set_err("swe_create: grid has too many tiles for the tile list (at most 2^20 - 1)"); return nullptr;
     }
     const size_t n = (size_t)nx * ny;
-    for (size_t i = 0; i < n; ++i) {
-        if (!std::isfinite(b[i]) || (n_M && (!std::isfinite(n_M[i]) || n_M[i] < 0.0))) {
-            set_err("swe_create: bed must be finite and Manning n finite and >= 0"); return nullptr;
-        }
+    if (!all_finite(b, n) || !xfer_within(n_M, n, 0.0, DBL_MAX)) {
+        set_err("swe_create: bed must be finite and Manning n finite and >= 0"); return nullptr;
     }
     int nin = 0;
     if (p->inlet_ni > 0 && p->inlet_nj > 0) {
@@ -606,17 +648,8 @@ static swe_t* create_grid(int nx, int ny, double dx, const double* b, const doub
     CK(hipMemsetAsync(s->ctrl, 0, sizeof(Ctrl), s->stream));
     CK(hipMemsetAsync(s->ledger, 0, sizeof(double) * s->ntiles, s->stream));
 
-    // static fields: bed (closed gates raised far above any level), c_f = g n_M^2
-    {
-        std::vector<double> bb(b, b + n), cf(n, 0.0);
-        for (size_t i = 0; i < n; ++i) {
-            if (p->solid && p->solid[i]) bb[i] = swe::GATE_BED;
-            else if (n_M) cf[i] = p->g * n_M[i] * n_M[i];
-        }
-        if (upload(s, s->bed, bb.data(), 0.0) || upload(s, s->cf, cf.data(), 0.0)) {
-            free_all(s); delete s; return nullptr;
-        }
-    }
+    CK(s->precision == 32 ? put_static<float>(s->stream, s->bed, s->cf, n, b, n_M, p->solid, p->g)
+                          : put_static<double>(s->stream, s->bed, s->cf, n, b, n_M, p->solid, p->g));
 
     // grid of the step kernel: enough resident workgroups to fill the chip
     int dev = 0, cus = 0, occ = 0;
@@ -699,28 +732,9 @@ int swe_run_timed(swe_t* s, long nsteps, double* kernel_ms) {
 
 int swe_get_state(swe_t* s, double* H, double* Qx, double* Qy) {
     if (!s) { set_err("swe_get_state: NULL handle"); return SWE_EINVAL; }
-    Ctrl c;
-    int rc = sync_ctrl(s, &c);
-    if (rc) return rc;
-    // step k reads buffer k&1 and writes buffer (k+1)&1, so after c.step
-    // completed steps the current layer is in buffer c.step&1
-    const int par = (int)(c.step & 1);
-    const size_t n = (size_t)s->nx * s->ny;
-    std::vector<unsigned char> buf(n * s->rsize);
-    double* outs[3] = {H, Qx, Qy};
-    void* srcs[3] = {s->Hb[par], s->Qxb[par], s->Qyb[par]};
-    for (int k = 0; k < 3; ++k) {
-        if (!outs[k]) continue;
-        HIPCHK(hipMemcpyAsync(buf.data(), srcs[k], n * s->rsize, hipMemcpyDeviceToHost, s->stream));
-        HIPCHK(hipStreamSynchronize(s->stream));
-        if (s->precision == 32) {
-            const float* f = (const float*)buf.data();
-            for (size_t i = 0; i < n; ++i) outs[k][i] = f[i];
-        } else {
-            std::memcpy(outs[k], buf.data(), n * sizeof(double));
-        }
-    }
-    return 0;
+    // step k reads buffer k&1 and writes buffer (k+1)&1: the current layer is
+    // in the buffer of the completed steps' parity
+    return get_layer(s->stream, s->precision, s->ctrl, s->Hb, s->Qxb, s->Qyb, s->nx, 0, 0, s->nx, s->ny, H, Qx, Qy);
 }
 
 int swe_set_state(swe_t* s, const double* H, const double* Qx, const double* Qy) {
@@ -752,9 +766,7 @@ double swe_mass(swe_t* s) {
     if (!s) return NAN;
     hipLaunchKernelGGL(swe::k_sum_tiles, dim3(1), dim3(1024), 0, s->stream, s->mass, s->ntiles, s->scalar);
     double v = NAN;
-    if (hipMemcpyAsync(&v, s->scalar, sizeof(double), hipMemcpyDeviceToHost, s->stream) != hipSuccess ||
-        hipStreamSynchronize(s->stream) != hipSuccess)
-        return NAN;
+    if (xfer_read(&v, s->scalar, sizeof(double), s->stream) != hipSuccess) return NAN;
     return v * s->h * s->h;
 }
 
@@ -780,9 +792,7 @@ double swe_ledger(swe_t* s) {
     if (!s) return NAN;
     hipLaunchKernelGGL(swe::k_sum_tiles, dim3(1), dim3(1024), 0, s->stream, s->ledger, s->ntiles, s->scalar);
     double v = NAN;
-    if (hipMemcpyAsync(&v, s->scalar, sizeof(double), hipMemcpyDeviceToHost, s->stream) != hipSuccess ||
-        hipStreamSynchronize(s->stream) != hipSuccess)
-        return NAN;
+    if (xfer_read(&v, s->scalar, sizeof(double), s->stream) != hipSuccess) return NAN;
     return v;
 }
 
@@ -862,7 +872,7 @@ int swe_set_source_field(swe_t* s, const double* sigma) {
             HIPCHK(hipMalloc((void**)&s->fvol, sizeof(double) * s->ntiles));
             HIPCHK(hipMemsetAsync(s->fvol, 0, sizeof(double) * s->ntiles, s->stream));
         }
-        if ((rc = upload(s, s->sigma, sg.data(), 0.0))) return rc;
+        if ((rc = upload(s, s->sigma, sg.data()))) return rc;
         HIPCHK(hipMemcpyAsync(s->fmask, fm.data(), s->ntiles, hipMemcpyHostToDevice, s->stream));
         HIPCHK(hipStreamSynchronize(s->stream));
         s->field = true;
@@ -877,9 +887,7 @@ double swe_field_volume(swe_t* s) {
     if (!s->fvol) return 0.0;
     hipLaunchKernelGGL(swe::k_sum_tiles, dim3(1), dim3(1024), 0, s->stream, s->fvol, s->ntiles, s->scalar);
     double v = NAN;
-    if (hipMemcpyAsync(&v, s->scalar, sizeof(double), hipMemcpyDeviceToHost, s->stream) != hipSuccess ||
-        hipStreamSynchronize(s->stream) != hipSuccess)
-        return NAN;
+    if (xfer_read(&v, s->scalar, sizeof(double), s->stream) != hipSuccess) return NAN;
     return v;
 }
 
@@ -1120,6 +1128,9 @@ struct BScen {
 }  // namespace
 
 struct swe_batch_s {
+    swe_batch_s() { xfer_retain(); }
+    ~swe_batch_s() { xfer_release(); }
+    swe_batch_s(const swe_batch_s&) = delete;
     int n = 0, precision = 32, rsize = 4, grid = 0, total_tiles = 0;
     const Launcher* L = nullptr;
     hipStream_t stream = nullptr;
@@ -1186,9 +1197,8 @@ void free_batch(swe_batch_t* b) {
 
 int batch_sync_ctrls(swe_batch_t* b, std::vector<Ctrl>& c, Ctrl* lc) {
     c.resize(b->n);
-    HIPCHK(hipMemcpyAsync(c.data(), b->ctrls, sizeof(Ctrl) * b->n, hipMemcpyDeviceToHost, b->stream));
-    if (lc) HIPCHK(hipMemcpyAsync(lc, b->lctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, b->stream));
-    HIPCHK(hipStreamSynchronize(b->stream));
+    HIPCHK(xfer_read(c.data(), b->ctrls, sizeof(Ctrl) * b->n, b->stream));
+    if (lc) HIPCHK(xfer_read(lc, b->lctrl, sizeof(Ctrl), b->stream));
     return 0;
 }
 
@@ -1296,34 +1306,17 @@ swe_batch_t* swe_batch_create(int n, const int* nx, const int* ny, const double*
         BK(hipMalloc((void**)&c.ledger, sizeof(double) * c.ntiles));
         BK(hipMemsetAsync(c.ledger, 0, sizeof(double) * c.ntiles, B->stream));
         // static fields and the initial state (dry cells at rest, closed gates dry and raised)
-        std::vector<unsigned char> buf(bytes);
-        auto put = [&](void* dst, auto fn) -> hipError_t {
-            if (B->precision == 32) { float* f = (float*)buf.data(); for (size_t i = 0; i < ncell; ++i) f[i] = (float)fn(i); }
-            else { double* d = (double*)buf.data(); for (size_t i = 0; i < ncell; ++i) d[i] = fn(i); }
-            hipError_t e = hipMemcpyAsync(dst, buf.data(), bytes, hipMemcpyHostToDevice, B->stream);
-            if (e == hipSuccess) e = hipStreamSynchronize(B->stream);
-            return e;
-        };
         const double* bk = b[k];
         const double* nm = n_M ? n_M[k] : nullptr;
-        bool okv = true;
-        for (size_t i = 0; i < ncell && okv; ++i) {
-            okv = std::isfinite(bk[i]) && (!nm || (std::isfinite(nm[i]) && nm[i] >= 0.0));
-            const double hh = q.H0 ? q.H0[i] : 0.0, a = q.Qx0 ? q.Qx0[i] : 0.0, bb = q.Qy0 ? q.Qy0[i] : 0.0;
-            okv = okv && std::isfinite(hh) && hh >= 0.0 && std::isfinite(a) && std::isfinite(bb);
+        if (!all_finite(bk, ncell) || !xfer_within(nm, ncell, 0.0, DBL_MAX) ||
+            !layer_ok(ncell, q.H0, q.Qx0, q.Qy0)) {
+            set_err("swe_batch_create: non-finite or negative input"); free_batch(B); delete B; return nullptr;
         }
-        if (!okv) { set_err("swe_batch_create: non-finite or negative input"); free_batch(B); delete B; return nullptr; }
-        const uint8_t* so = q.solid;
-        const double eps = q.eps, g = q.g;
-        BK(put(c.bed, [&](size_t i) { return so && so[i] ? swe::GATE_BED : bk[i]; }));
-        BK(put(c.cf, [&](size_t i) { return (so && so[i]) || !nm ? 0.0 : g * nm[i] * nm[i]; }));
-        auto Hf = [&](size_t i) { return so && so[i] ? 0.0 : (q.H0 ? q.H0[i] : 0.0); };
-        auto Qf = [&](const double* Q, size_t i) { const double hh = Hf(i); return !(hh > eps) || !Q ? 0.0 : Q[i]; };
-        for (int t = 0; t < 2; ++t) {
-            BK(put(c.Hb[t], Hf));
-            BK(put(c.Qxb[t], [&](size_t i) { return Qf(q.Qx0, i); }));
-            BK(put(c.Qyb[t], [&](size_t i) { return Qf(q.Qy0, i); }));
-        }
+        BK(B->precision == 32 ? put_static<float>(B->stream, c.bed, c.cf, ncell, bk, nm, q.solid, q.g)
+                              : put_static<double>(B->stream, c.bed, c.cf, ncell, bk, nm, q.solid, q.g));
+        BK(B->precision == 32
+               ? put_layer<float>(B->stream, c.Hb, c.Qxb, c.Qyb, ncell, q.H0, q.Qx0, q.Qy0, q.solid, q.eps)
+               : put_layer<double>(B->stream, c.Hb, c.Qxb, c.Qyb, ncell, q.H0, q.Qx0, q.Qy0, q.solid, q.eps));
     }
     BK(hipMalloc((void**)&B->lctrl, sizeof(Ctrl)));
     BK(hipMalloc((void**)&B->ctrls, sizeof(Ctrl) * n));
@@ -1435,23 +1428,8 @@ int swe_batch_query(swe_batch_t* b, double* t, double* mass, double* inflow, dou
 
 int swe_batch_get_state(swe_batch_t* b, int k, double* H, double* Qx, double* Qy) {
     if (!b || k < 0 || k >= b->n) { set_err("swe_batch_get_state: invalid arguments"); return SWE_EINVAL; }
-    std::vector<Ctrl> c;
-    int rc = batch_sync_ctrls(b, c, nullptr);
-    if (rc) return rc;
     const BScen& s = b->sc[k];
-    const int par = (int)(c[k].step & 1);
-    const size_t n = (size_t)s.nx * s.ny;
-    std::vector<unsigned char> buf(n * b->rsize);
-    double* outs[3] = {H, Qx, Qy};
-    void* srcs[3] = {s.Hb[par], s.Qxb[par], s.Qyb[par]};
-    for (int q = 0; q < 3; ++q) {
-        if (!outs[q]) continue;
-        HIPCHK(hipMemcpyAsync(buf.data(), srcs[q], n * b->rsize, hipMemcpyDeviceToHost, b->stream));
-        HIPCHK(hipStreamSynchronize(b->stream));
-        if (b->precision == 32) { const float* f = (const float*)buf.data(); for (size_t i = 0; i < n; ++i) outs[q][i] = f[i]; }
-        else std::memcpy(outs[q], buf.data(), n * sizeof(double));
-    }
-    return 0;
+    return get_layer(b->stream, b->precision, b->ctrls + k, s.Hb, s.Qxb, s.Qyb, s.nx, 0, 0, s.nx, s.ny, H, Qx, Qy);
 }
 
 int swe_batch_work(swe_batch_t* b, long long* tile_steps, long long* cell_steps, int* total_tiles) {
@@ -2060,18 +2038,9 @@ int swe_nest_get_coarse(swe_nest_t* n, double* H, double* Qx, double* Qy) {
 int swe_nest_get_patch(swe_nest_t* n, int k, double* H, double* Qx, double* Qy) {
     if (!n || k < 0 || k >= n->np) { set_err("swe_nest_get_patch: invalid arguments"); return SWE_EINVAL; }
     swe_t* g = n->p[k];
-    const int G = swe::NEST_FRAME, nxe = g->nx, nxf = nxe - 2 * G, nyf = g->ny - 2 * G;
-    std::vector<double> a((size_t)nxe * g->ny), b(a.size()), c(a.size());
-    int rc = swe_get_state(g, a.data(), b.data(), c.data());
-    if (rc) return rc;
-    double* outs[3] = {H, Qx, Qy};
-    const std::vector<double>* srcs[3] = {&a, &b, &c};
-    for (int q = 0; q < 3; ++q) {
-        if (!outs[q]) continue;
-        for (int j = 0; j < nyf; ++j)
-            std::memcpy(outs[q] + (size_t)j * nxf, srcs[q]->data() + (size_t)(j + G) * nxe + G, sizeof(double) * nxf);
-    }
-    return 0;
+    const int G = swe::NEST_FRAME;
+    return get_layer(g->stream, g->precision, g->ctrl, g->Hb, g->Qxb, g->Qyb, g->nx, G, G, g->nx - 2 * G,
+                     g->ny - 2 * G, H, Qx, Qy);
 }
 
 }  // extern "C"
@@ -2081,6 +2050,9 @@ int swe_nest_get_patch(swe_nest_t* n, int k, double* H, double* Qx, double* Qy) 
 #include "swe_lc.hpp"
 
 struct swe_lc_s {
+    swe_lc_s() { xfer_retain(); }
+    ~swe_lc_s() { xfer_release(); }
+    swe_lc_s(const swe_lc_s&) = delete;
     int S = 32, So = 33, max_crops = 0;   // grid tile side; network output side S + 1
     hipStream_t stream = nullptr;
     bool own_stream = false;
@@ -2256,21 +2228,52 @@ int lc_opt_step(swe_lc_t* c, int n, double cnt, double lr, double* loss_dev) {
     return 0;
 }
 
-// Host FP64 crops (n, Sin, Sin, 6) -> bf16 act[0] with 16 channels.
-int lc_upload_crops(swe_lc_t* c, int n, const double* x) {
-    const int si = lc_in(c, 0);
-    const size_t npx = (size_t)n * si * si;
-    std::vector<unsigned short> h(npx * 16, 0);
-    for (size_t p = 0; p < npx; ++p)
-        for (int k = 0; k < 6; ++k) {
-            const float f = (float)x[p * 6 + k];
-            unsigned u;
-            std::memcpy(&u, &f, 4);
-            u += 0x7FFFu + ((u >> 16) & 1u);
-            h[p * 16 + k] = (unsigned short)(u >> 16);
+// The pool for a network's host data, waited for before it is let go.
+struct LcHold {
+    hipStream_t st;
+    XferHold hold;
+    unsigned char* base = nullptr;
+    explicit LcHold(hipStream_t s) : st(s) {}
+    ~LcHold() { (void)hipStreamSynchronize(st); }
+};
+
+// Host FP64 crops (n, Sin, Sin, 6) -> bf16 act[0] with 16 channels; with y,
+// labels and mask (n, So, So, 6) and the sum of the mask.  Rounded to FP32
+// into pinned memory by host threads, a crop range each, and expanded on the
+// device; queued on the stream, the pool stays held in `io`.
+int lc_put_crops(swe_lc_t* c, LcHold& io, int n, const double* x, const double* y, const double* mask, double* cnt) {
+    const size_t px = (size_t)lc_in(c, 0) * lc_in(c, 0), py = y ? (size_t)c->So * c->So * 6 : 0;
+    const size_t per = (px * 6 + 2 * py) * sizeof(float), all = n * per;
+    size_t size = io.hold.get(all <= XFER_THREADED ? all : XFER_SLOTS * XFER_SLOT, &io.base);
+    int threads = 1;
+    if (all > XFER_THREADED) threads = (int)std::min<size_t>(XFER_SLOTS, (all >> 20) + 1);
+    if (size / threads < per) threads = 1;
+    if (size < per) { set_err("swe_lc: no pinned memory for a crop"); return SWE_ENOMEM; }
+    const size_t slot = size / threads / 16 * 16;
+    const int fit = (int)std::min<size_t>(slot / per, (size_t)n), even = (n + threads - 1) / threads;
+    const int cp = fit < even ? fit : even, pieces = (n + cp - 1) / cp;
+    double part[XFER_SLOTS] = {};
+    const hipError_t e = xfer_parallel(pieces, threads, [&](int q, int t) -> hipError_t {
+        const size_t c0 = (size_t)q * cp, m = std::min<size_t>(cp, n - c0);
+        float* hx = (float*)(io.base + t * slot);
+        float* hy = hx + m * px * 6;
+        float* hm = hy + m * py;
+        if (q >= threads) {   // the slot's previous piece has been read
+            const hipError_t s = hipStreamSynchronize(c->stream);
+            if (s != hipSuccess) return s;
         }
-    HIPCHK(hipMemcpyAsync(c->act[0], h.data(), h.size() * 2, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
+        for (size_t k = 0; k < m * px * 6; ++k) hx[k] = (float)x[c0 * px * 6 + k];
+        for (size_t k = 0; k < m * py; ++k) hy[k] = (float)y[c0 * py + k];
+        for (size_t k = 0; k < m * py; ++k) { hm[k] = (float)mask[c0 * py + k]; part[t] += mask[c0 * py + k]; }
+        hipLaunchKernelGGL(L_::k_crops_in, dim3(grid_for((long long)m * px, 256)), dim3(256), 0, c->stream, hx, m * px,
+                           hy, hm, m * py, c->act[0] + c0 * px * 16, c->y + c0 * py, c->mask + c0 * py);
+        return hipGetLastError();
+    });
+    HIPCHK(e);
+    if (cnt) {
+        *cnt = 0.0;
+        for (double v : part) *cnt += v;
+    }
     return 0;
 }
 
@@ -2379,10 +2382,16 @@ int swe_lc_set_params(swe_lc_t* c, const double* params) {
 }
 
 static int lc_read_floats(swe_lc_t* c, const float* src, double* dst, size_t n) {
-    std::vector<float> h(n);
-    HIPCHK(hipMemcpyAsync(h.data(), src, sizeof(float) * n, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    for (size_t k = 0; k < n; ++k) dst[k] = h[k];
+    LcHold io(c->stream);
+    const size_t room = io.hold.get(std::min(n * sizeof(float), XFER_SLOT), &io.base) / sizeof(float);
+    if (!room) { set_err("swe_lc: no pinned memory"); return SWE_ENOMEM; }
+    for (size_t k0 = 0; k0 < n; k0 += room) {
+        const size_t m = std::min(room, n - k0);
+        HIPCHK(hipMemcpyAsync(io.base, src + k0, sizeof(float) * m, hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(hipStreamSynchronize(c->stream));
+        const float* h = (const float*)io.base;
+        for (size_t k = 0; k < m; ++k) dst[k0 + k] = h[k];
+    }
     return 0;
 }
 
@@ -2398,7 +2407,8 @@ int swe_lc_get_grads(swe_lc_t* c, double* grads) {
 
 int swe_lc_forward(swe_lc_t* c, int n, const double* x, double* out) {
     if (!c || !x || n < 1 || n > c->max_crops) { set_err("swe_lc_forward: invalid arguments"); return SWE_EINVAL; }
-    int rc = lc_upload_crops(c, n, x);
+    LcHold io(c->stream);
+    int rc = lc_put_crops(c, io, n, x, nullptr, nullptr, nullptr);
     if (rc) return rc;
     HIPCHK(lc_forward(c, n, nullptr, c->stream));
     c->last_n = n;
@@ -2416,7 +2426,8 @@ int swe_lc_forward(swe_lc_t* c, int n, const double* x, double* out) {
 
 int swe_lc_infer(swe_lc_t* c, int n, const double* x, double* out) {
     if (!c || !x || !out || n < 1 || n > c->max_crops) { set_err("swe_lc_infer: invalid arguments"); return SWE_EINVAL; }
-    int rc = lc_upload_crops(c, n, x);
+    LcHold io(c->stream);
+    int rc = lc_put_crops(c, io, n, x, nullptr, nullptr, nullptr);
     if (rc) return rc;
     HIPCHK(lc_infer(c, n, nullptr, c->stream));
     c->last_n = 0;   // the stored activations no longer belong to one forward
@@ -2457,17 +2468,15 @@ int swe_lc_train_step(swe_lc_t* c, int n, const double* x, const double* y, cons
     if (!c || !x || !y || !mask || n < 1 || n > c->max_crops || !(lr >= 0.0)) {
         set_err("swe_lc_train_step: invalid arguments"); return SWE_EINVAL;
     }
-    int rc = lc_upload_crops(c, n, x);
-    if (rc) return rc;
-    const size_t np = (size_t)n * c->So * c->So;
-    std::vector<float> hy(np * 6), hm(np * 6);
+    LcHold io(c->stream);
     double cnt = 0.0;
-    for (size_t k = 0; k < np * 6; ++k) { hy[k] = (float)y[k]; hm[k] = (float)mask[k]; cnt += mask[k]; }
-    HIPCHK(hipMemcpyAsync(c->y, hy.data(), sizeof(float) * hy.size(), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(c->mask, hm.data(), sizeof(float) * hm.size(), hipMemcpyHostToDevice, c->stream));
+    int rc = lc_put_crops(c, io, n, x, y, mask, &cnt);
+    if (rc) return rc;
     if ((rc = lc_opt_step(c, n, cnt, lr, c->loss))) return rc;
-    if (loss) HIPCHK(hipMemcpyAsync(loss, c->loss, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    // (the crops' pinned memory is read before the loss is written)
+    HIPCHK(hipMemcpyAsync(io.base, c->loss, sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
+    if (loss) std::memcpy(loss, io.base, sizeof(double));
     return 0;
 }
 

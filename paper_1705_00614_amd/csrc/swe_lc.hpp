@@ -1083,6 +1083,24 @@ __global__ void k_batch_copy(const int* __restrict__ idx, int nb, int So, const 
     }
 }
 
+// Host crops already rounded to FP32 (n, Sin, Sin, 6) into the network's bf16
+// input with 16 channels, and labels and mask of a training batch (ny floats
+// each, may be 0) beside them.
+__global__ void k_crops_in(const float* __restrict__ hx, size_t npx, const float* __restrict__ hy,
+                           const float* __restrict__ hm, size_t ny, unsigned short* __restrict__ x,
+                           float* __restrict__ y, float* __restrict__ m) {
+    const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x, nt = (size_t)gridDim.x * blockDim.x;
+    for (size_t p = t; p < npx; p += nt) {
+        unsigned h[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            h[k] = to_bf16(hx[p * 6 + 2 * k]) | ((unsigned)to_bf16(hx[p * 6 + 2 * k + 1]) << 16);
+        *reinterpret_cast<uint4*>(x + p * 16) = uint4{h[0], h[1], h[2], 0u};
+        *reinterpret_cast<uint4*>(x + p * 16 + 8) = uint4{0u, 0u, 0u, 0u};
+    }
+    for (size_t k = t; k < ny; k += nt) { y[k] = hy[k]; m[k] = hm[k]; }
+}
+
 // Labels of the data set re-expressed in new output scales: y *= old / new.
 __global__ void k_rescale(float* __restrict__ y, size_t n, const float* __restrict__ ratio) {
     for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x)

@@ -1644,6 +1644,15 @@ __global__ __launch_bounds__(NT) void k_prepare(Args<real> a) {
     }
 }
 
+// What k_prepare builds on: stamps, counters and the speed maximum cleared, in
+// one launch (three memsets of these sizes cost over 100 us of host time).
+__global__ void k_prepare_clear(Ctrl* c, int* hot, int* stamp, int ntiles) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+    for (int k = t; k < ntiles; k += nt) stamp[k] = 0;
+    for (int k = t; k < HOT_INTS; k += nt) hot[k] = 0;
+    if (t == 0) c->prep_speed = 0ull;
+}
+
 // Set the length of the next step (held steps; tau <= 0: the recorded CFL
 // step of the current layer) and its hydrograph scalars.  The tile list is
 // left alone.

@@ -1,0 +1,357 @@
+// swe_xfer.hpp -- transfers between the caller's FP64 arrays and the stencil
+// type's fields on the device.
+//
+// The caller's arrays are pageable, so a copy straight to or from them goes
+// through the runtime's staging in small pieces, one host thread converting
+// after each array: 4 GB/s on a 4096^2 state.  Here a kernel moves a piece of
+// a field between device memory and pinned host memory at the link's rate
+// (it picks the current layer of a ping-pong pair from the step count itself,
+// so that no round trip for the control block comes first), and several host
+// threads convert pieces while others are on the way.  Transfers of less than
+// XFER_THREADED bytes take one launch, one wait and the calling thread.
+//
+// The pinned memory is one pool per process, at most XFER_SLOTS slots of
+// XFER_SLOT bytes, taken by one transfer at a time (a mutex), allocated when a
+// transfer first needs it and given back when the last handle is destroyed.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include <sys/mman.h>
+
+#include <climits>
+#include <cstring>
+#include <mutex>
+#include <system_error>
+#include <thread>
+
+#include "swe_step.hpp"
+
+namespace swe {
+
+// One field as a ping-pong pair (b = a for a single buffer).
+template <typename real> struct FieldPair { real* a; real* b; };
+
+template <typename real, int N> struct XferFields {
+    FieldPair<real> f[N];
+    real* host[N];
+};
+
+// Copy cells [first, first + cnt) of the w-wide rectangle at (x0, y0) of each
+// field's current layer (rows of `pitch` cells) into host[q].
+template <typename real, int N>
+__global__ __launch_bounds__(256) void k_export(XferFields<real, N> x, const Ctrl* ctrl, int pitch, int x0, int y0,
+                                                int w, size_t first, size_t cnt) {
+    const int q = blockIdx.y;
+    const real* src = (ctrl->step & 1) ? x.f[q].b : x.f[q].a;
+    real* dst = x.host[q];
+    const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x, nt = (size_t)gridDim.x * blockDim.x;
+    if (w == pitch) {
+        src += (size_t)y0 * pitch + first;
+        constexpr int V = 16 / sizeof(real);
+        size_t done = 0;
+        if ((((uintptr_t)src | (uintptr_t)dst) & 15) == 0) {
+            const size_t nv = cnt / V;
+            for (size_t k = t; k < nv; k += nt)
+                reinterpret_cast<uint4*>(dst)[k] = reinterpret_cast<const uint4*>(src)[k];
+            done = nv * V;
+        }
+        for (size_t k = done + t; k < cnt; k += nt) dst[k] = src[k];
+    } else {
+        for (size_t k = t; k < cnt; k += nt) {
+            const size_t c = first + k;
+            dst[k] = src[(y0 + c / w) * pitch + x0 + c % w];
+        }
+    }
+}
+
+// Cells [first, first + cnt) of each field, both buffers of its pair, from
+// host[q].
+template <typename real, int N>
+__global__ __launch_bounds__(256) void k_import(XferFields<real, N> x, size_t first, size_t cnt) {
+    const int q = blockIdx.y;
+    real* a = x.f[q].a + first;
+    real* b = x.f[q].b + first;
+    const real* src = x.host[q];
+    const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x, nt = (size_t)gridDim.x * blockDim.x;
+    constexpr int V = 16 / sizeof(real);
+    size_t done = 0;
+    if ((((uintptr_t)a | (uintptr_t)b | (uintptr_t)src) & 15) == 0) {
+        const size_t nv = cnt / V;
+        for (size_t k = t; k < nv; k += nt) {
+            const uint4 v = reinterpret_cast<const uint4*>(src)[k];
+            reinterpret_cast<uint4*>(a)[k] = v;
+            if (b != a) reinterpret_cast<uint4*>(b)[k] = v;
+        }
+        done = nv * V;
+    }
+    for (size_t k = done + t; k < cnt; k += nt) { a[k] = src[k]; b[k] = src[k]; }
+}
+
+}  // namespace swe
+
+namespace {
+
+constexpr int XFER_SLOTS = 8;                    // pieces in flight = host threads of a large transfer
+constexpr size_t XFER_SLOT = size_t(4) << 20;
+constexpr size_t XFER_THREADED = size_t(2) << 20;
+
+struct XferPool {
+    std::mutex mu;              // held for the length of a transfer
+    unsigned char* base = nullptr;
+    size_t size = 0;
+    std::mutex users_mu;
+    int users = 0;              // live handles
+};
+XferPool& xfer_pool() {
+    static XferPool* p = new XferPool;   // never destroyed: handles may be freed at process exit
+    return *p;
+}
+void xfer_retain() {
+    XferPool& p = xfer_pool();
+    std::lock_guard<std::mutex> lk(p.users_mu);
+    ++p.users;
+}
+void xfer_release() {
+    XferPool& p = xfer_pool();
+    std::lock_guard<std::mutex> lk(p.users_mu);
+    if (--p.users > 0) return;
+    std::lock_guard<std::mutex> lm(p.mu);
+    if (p.base) (void)hipHostFree(p.base);
+    p.base = nullptr;
+    p.size = 0;
+}
+
+// The pool, held while this lives.
+struct XferHold {
+    std::unique_lock<std::mutex> lk{xfer_pool().mu};
+    // pinned memory for `bytes` (at least half a slot); where the
+    // system gives no more, what there is.  Returns its size, 0 for none.
+    size_t get(size_t bytes, unsigned char** base) {
+        XferPool& p = xfer_pool();
+        if (bytes < XFER_SLOT / 2) bytes = XFER_SLOT / 2;
+        if (p.size < bytes) {
+            void* q = nullptr;
+            if (hipHostMalloc(&q, bytes, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) {
+                if (p.base) (void)hipHostFree(p.base);
+                p.base = (unsigned char*)q;
+                p.size = bytes;
+            } else {
+                (void)hipGetLastError();
+                if (!p.size && bytes > XFER_SLOT / 2) return get(XFER_SLOT / 2, base);
+            }
+        }
+        *base = p.base;
+        return p.size;
+    }
+};
+
+// Run job(chunk, slot) for every chunk on up to `threads` <= XFER_SLOTS host
+// threads (the caller is one of them), thread t taking chunks t, t + T, ...
+// and slot t.  Returns the first error.
+template <class Job>
+hipError_t xfer_parallel(int chunks, int threads, Job job) {
+    int dev = 0;
+    const hipError_t e0 = hipGetDevice(&dev);
+    if (e0 != hipSuccess) return e0;
+    const int T = chunks < threads ? chunks : threads;
+    hipError_t err[XFER_SLOTS] = {};
+    auto work = [&](int t) {
+        for (int c = t; c < chunks && err[t] == hipSuccess; c += T) err[t] = job(c, t);
+    };
+    std::thread th[XFER_SLOTS];
+    int started = 1;
+    try {
+        for (; started < T; ++started)
+            th[started] = std::thread([&, t = started] {
+                err[t] = hipSetDevice(dev);
+                if (err[t] == hipSuccess) work(t);
+            });
+    } catch (const std::system_error&) {   // no more threads: the caller takes the rest
+    }
+    work(0);
+    for (int t = started; t < T; ++t) work(t);
+    for (int t = 1; t < started; ++t) th[t].join();
+    for (int t = 0; t < T; ++t)
+        if (err[t] != hipSuccess) return err[t];
+    return hipSuccess;
+}
+
+inline int xfer_grid(size_t cells) {
+    const size_t b = (cells + 1023) / 1024;
+    return (int)(b < 1 ? 1 : b > 1024 ? 1024 : b);
+}
+
+// Pages of a fresh array are faulted in by one call per piece instead of one
+// trap per 4 KB page (1.3 us each here: 11 ms for 32 MB, against 0.9 ms to
+// convert into them); pages already there, or an older kernel: no effect.
+inline void xfer_populate(void* p, size_t bytes) {
+#ifdef MADV_POPULATE_WRITE
+    const uintptr_t page = 4096, lo = ((uintptr_t)p + page - 1) & ~(page - 1), hi = ((uintptr_t)p + bytes) & ~(page - 1);
+    if (hi > lo) (void)madvise((void*)lo, hi - lo, MADV_POPULATE_WRITE);
+#else
+    (void)p; (void)bytes;
+#endif
+}
+
+// A transfer of nf fields of n cells through the pool: in one piece where
+// that is small, else split over threads with an event each.
+struct XferPlan {
+    XferHold hold;
+    unsigned char* base = nullptr;
+    bool whole = false;
+    size_t piece = 0, slot = 0;
+    int per = 0, threads = 0;
+    hipEvent_t ev[XFER_SLOTS] = {};
+    hipError_t prepare(int nf, size_t n, size_t rsize) {
+        const size_t all = nf * n * rsize;
+        if (all <= XFER_THREADED && hold.get(all, &base) >= all) {
+            whole = true;
+            return hipSuccess;
+        }
+        const size_t size = hold.get(XFER_SLOTS * XFER_SLOT, &base);
+        if (!size) return hipErrorOutOfMemory;
+        slot = size < XFER_SLOT ? size : XFER_SLOT;
+        threads = (int)(size / slot);
+        piece = (n * nf + threads - 1) / threads;   // about one piece a thread, at least 32768 cells, at most a slot
+        if (piece < 32768) piece = 32768;
+        if (piece > slot / rsize) piece = slot / rsize;
+        piece = (piece + 1023) / 1024 * 1024;
+        per = (int)((n + piece - 1) / piece);
+        for (int t = 0; t < threads; ++t) {
+            const hipError_t e = hipEventCreateWithFlags(&ev[t], hipEventDisableTiming);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
+    ~XferPlan() {
+        for (hipEvent_t v : ev)
+            if (v) (void)hipEventDestroy(v);
+    }
+};
+
+// The rectangle (x0, y0, w x h) of up to three fields' current layers into
+// FP64 host arrays (null: not wanted), after everything queued on `st`.
+template <typename real>
+hipError_t xfer_get(hipStream_t st, const swe::Ctrl* ctrl, real* const (&a)[3], real* const (&b)[3], int pitch, int x0,
+                    int y0, int w, int h, double* const (&out)[3]) {
+    int want[3], nf = 0;
+    for (int q = 0; q < 3; ++q)
+        if (out[q]) want[nf++] = q;
+    const size_t n = (size_t)w * h;
+    if (nf == 0) return hipStreamSynchronize(st);
+    auto convert = [](double* dst, const real* src, size_t cnt) {
+        if constexpr (sizeof(real) == 8) std::memcpy(dst, src, cnt * 8);
+        else for (size_t k = 0; k < cnt; ++k) dst[k] = (double)src[k];
+    };
+    XferPlan pl;
+    hipError_t e = pl.prepare(nf, n, sizeof(real));
+    if (e != hipSuccess) return e;
+    if (pl.whole) {
+        real* base = (real*)pl.base;
+        swe::XferFields<real, 3> x{};
+        for (int k = 0; k < nf; ++k) {
+            x.f[k] = {a[want[k]], b[want[k]]};
+            x.host[k] = base + k * n;
+        }
+        hipLaunchKernelGGL((swe::k_export<real, 3>), dim3(xfer_grid(n), nf), dim3(256), 0, st, x, ctrl, pitch, x0, y0, w,
+                           (size_t)0, n);
+        if ((e = hipGetLastError()) != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess) return e;
+        for (int k = 0; k < nf; ++k) convert(out[want[k]], base + k * n, n);
+        return hipSuccess;
+    }
+    e = xfer_parallel(nf * pl.per, pl.threads, [&](int c, int t) -> hipError_t {
+        const int q = want[c / pl.per];
+        const size_t first = (size_t)(c % pl.per) * pl.piece, cnt = n - first < pl.piece ? n - first : pl.piece;
+        real* slot = (real*)(pl.base + t * pl.slot);
+        const swe::XferFields<real, 1> x{{{a[q], b[q]}}, {slot}};
+        hipLaunchKernelGGL((swe::k_export<real, 1>), dim3(xfer_grid(cnt)), dim3(256), 0, st, x, ctrl, pitch, x0, y0, w,
+                           first, cnt);
+        hipError_t s = hipGetLastError();
+        if (s == hipSuccess) s = hipEventRecord(pl.ev[t], st);
+        xfer_populate(out[q] + first, cnt * sizeof(double));   // while the piece is on its way
+        if (s == hipSuccess) s = hipEventSynchronize(pl.ev[t]);
+        if (s == hipSuccess) convert(out[q] + first, slot, cnt);
+        return s;
+    });
+    if (e != hipSuccess) (void)hipStreamSynchronize(st);   // no piece is under way when the pool is let go
+    return e;
+}
+
+// Fields of n cells each from fill(q, first, cnt, dst), which writes cells
+// [first, first + cnt) of field q in the stencil type; both buffers of each
+// pair.  Returns once the device has them.
+template <typename real, class Fill>
+hipError_t xfer_put(hipStream_t st, int nf, const swe::FieldPair<real>* f, size_t n, Fill fill) {
+    XferPlan pl;
+    hipError_t e = pl.prepare(nf, n, sizeof(real));
+    if (e != hipSuccess) return e;
+    if (pl.whole && nf <= 3) {
+        real* base = (real*)pl.base;
+        swe::XferFields<real, 3> x{};
+        for (int q = 0; q < nf; ++q) {
+            fill(q, (size_t)0, n, base + q * n);
+            x.f[q] = f[q];
+            x.host[q] = base + q * n;
+        }
+        hipLaunchKernelGGL((swe::k_import<real, 3>), dim3(xfer_grid(n), nf), dim3(256), 0, st, x, (size_t)0, n);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        return hipStreamSynchronize(st);
+    }
+    e = xfer_parallel(nf * pl.per, pl.threads, [&](int c, int t) -> hipError_t {
+        const int q = c / pl.per;
+        const size_t first = (size_t)(c % pl.per) * pl.piece, cnt = n - first < pl.piece ? n - first : pl.piece;
+        real* slot = (real*)(pl.base + t * pl.slot);
+        fill(q, first, cnt, slot);
+        const swe::XferFields<real, 1> x{{f[q]}, {slot}};
+        hipLaunchKernelGGL((swe::k_import<real, 1>), dim3(xfer_grid(cnt)), dim3(256), 0, st, x, first, cnt);
+        hipError_t s = hipGetLastError();
+        if (s == hipSuccess) s = hipEventRecord(pl.ev[t], st);
+        return s == hipSuccess ? hipEventSynchronize(pl.ev[t]) : s;
+    });
+    if (e != hipSuccess) (void)hipStreamSynchronize(st);
+    return e;
+}
+
+// Whether every x[i], i < n, lies in [lo, hi] (false for NaN), on host threads
+// for a large n; a null x does.
+inline bool xfer_within(const double* x, size_t n, double lo, double hi) {
+    if (!x) return true;
+    constexpr size_t PART = size_t(1) << 18;
+    auto bad = [=](size_t i0, size_t i1) {
+        int v = 0;   // no early exit: the loop vectorises
+        for (size_t i = i0; i < i1; ++i) v |= !((x[i] >= lo) & (x[i] <= hi));
+        return v;
+    };
+    const size_t parts = (n + PART - 1) / PART;
+    int found[XFER_SLOTS] = {};
+    if (parts < 2 || parts > (size_t)INT_MAX ||
+        xfer_parallel((int)parts, XFER_SLOTS, [&](int c, int t) -> hipError_t {
+            const size_t i0 = c * PART;
+            found[t] |= bad(i0, n - i0 < PART ? n : i0 + PART);
+            return hipSuccess;
+        }) != hipSuccess)
+        return !bad(0, n);
+    for (int f : found)
+        if (f) return false;
+    return true;
+}
+
+// A few bytes of device memory after everything queued on `st`, through the
+// pool (a pageable destination costs 9 us more); straight where the pool is
+// in use.
+inline hipError_t xfer_read(void* dst, const void* src, size_t bytes, hipStream_t st) {
+    XferPool& p = xfer_pool();
+    std::unique_lock<std::mutex> lk(p.mu, std::try_to_lock);
+    hipError_t e;
+    if (!lk.owns_lock() || p.size < bytes) {
+        if ((e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
+        return hipStreamSynchronize(st);
+    }
+    if ((e = hipMemcpyAsync(p.base, src, bytes, hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
+    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    std::memcpy(dst, p.base, bytes);
+    return hipSuccess;
+}
+
+}  // namespace

@@ -820,7 +820,7 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
     // FP64 tiles are small and their arithmetic is a long dependent chain per
     // cell (IEEE divisions, cbrt): one cell per thread keeps the chain short
     // and every SIMD at work.  With 256 threads and runs of 4 a 256-tile step
-    // took 19.6 us, P1 and P2 more than half of it on three waves; so 16.3.
+    // took 18.5 us, P1 and P2 more than half of it on three waves; so 15.8.
     constexpr bool F32 = sizeof(real) == 4;
     constexpr int RP = F32 ? 2 : 1;
     constexpr int RFX = F32 ? ((TX + 4) % 3 == 0 ? 3 : TX > 32 ? 4 : 2) : (TX > 16 ? 2 : 1);
@@ -1561,87 +1561,113 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> 
 
 // ---------------------------------------------------------------- preparation kernel
 // Layer-0 (or restored layer) bookkeeping: CFL speed, wet tiles, volume
-// partials.  One workgroup per tile; needs only a 1-cell ring.
+// partials.  Needs only a 1-cell ring.  Workgroups stride over the tiles (at
+// most PREPARE_GRID of them, a multiple of NSEG) and send one speed maximum
+// each: the maxima go to one address, where atomics serialise at 11 ns, so
+// one per tile was most of the 143 us on 16 384 tiles.
+constexpr int PREPARE_GRID = 1024;
 template <typename real, int TX, int TY, int NT>
 __global__ __launch_bounds__(NT) void k_prepare(Args<real> a) {
-    constexpr int W = TX + 2, N = W * (TY + 2);
+    constexpr int W = TX + 2, N = W * (TY + 2), J = (N + NT - 1) / NT, NOWN = (TX * TY + NT - 1) / NT;
     constexpr int NWAVE = NT / 64;
     __shared__ real sH[N], sUx[N], sUy[N];
     __shared__ double red_d[NWAVE];
     __shared__ real red_v[NWAVE];
     __shared__ int red_i[NWAVE];
-    const int tid = threadIdx.x, tile = blockIdx.x;
-    const int tx0 = (tile % a.ntx) * TX, ty0 = (tile / a.ntx) * TY;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int nx = a.nx, ny = a.ny;
     const real eps = a.eps;
-    for (int k = tid; k < N; k += NT) {
-        const int lx = k % W - 1, ly = k / W - 1;
-        int fx = 0, fy = 0, gx, gy;
-        if (a.periodic) {   // the cell one period away, as it is
-            gx = (tx0 + lx + nx) % nx;
-            gy = (ty0 + ly + ny) % ny;
-        } else {
-            gx = mirror(tx0 + lx, nx, fx);
-            gy = mirror(ty0 + ly, ny, fy);
-        }
-        const int gi = gy * nx + gx;
-        const real H = a.Hi[gi];
-        real qx = a.Qxi[gi], qy = a.Qyi[gi];
-        if (fx & 1) qx = -qx;
-        if (fy & 1) qy = -qy;
-        const bool w = H > eps;
-        sH[k] = H;
-        sUx[k] = w ? Mth<real>::div(qx, H) : real(0);
-        sUy[k] = w ? Mth<real>::div(qy, H) : real(0);
-    }
-    __syncthreads();
-    real vmax = real(0);
-    double msum = 0.0;
-    int act = 0;
-    for (int k = tid; k < N; k += NT) {
-        const int lx = k % W - 1, ly = k / W - 1;
-        int gx = tx0 + lx, gy = ty0 + ly;
-        if (a.periodic) { gx = (gx + nx) % nx; gy = (gy + ny) % ny; }
-        if (gx < 0 || gx >= nx || gy < 0 || gy >= ny) continue;
-        const bool in_tile = lx >= 0 && lx < TX && ly >= 0 && ly < TY;
-        const bool corner = (lx < 0 || lx >= TX) && (ly < 0 || ly >= TY);
-        if (corner) continue;
-        const bool w = sH[k] > eps;
-        if (w || is_src(a, gx, gy) || (a.sigma && a.sigma[gy * nx + gx] > real(0))) act = 1;
-        if (!in_tile) continue;
-        const real H = sH[k];
-        msum += (double)H;
-        if (w) {
-            Nb4<real> nb;
-            const int sn[4] = {k - 1, k + 1, k - W, k + W};
+    real wgmax = real(0);   // thread 0
+    for (int tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x) {
+        const int tx0 = (tile % a.ntx) * TX, ty0 = (tile / a.ntx) * TY;
+        const bool edge = tx0 < 1 || ty0 < 1 || tx0 + TX >= nx || ty0 + TY >= ny;
+        // every load of the thread before any use, c_f of its own cells too
+        real vH[J], vX[J], vY[J], vC[NOWN];
+        int fl[J];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) { nb.ux[q] = sUx[sn[q]]; nb.uy[q] = sUy[sn[q]]; nb.w[q] = sH[sn[q]] > eps; }
-            real fx, fy;
-            soft_forces(a, H, sUx[k], sUy[k], nb, fx, fy);
-            vmax = rmax(vmax, cfl_speed(a, H, a.cf[gy * nx + gx], sUx[k], sUy[k], fx, fy));
+        for (int j = 0; j < J; ++j) {
+            const int k = min(tid + j * NT, N - 1), lx = k % W - 1, ly = k / W - 1;
+            int fx = 0, fy = 0, gx = tx0 + lx, gy = ty0 + ly;
+            if (edge) {
+                if (a.periodic) {   // the cell one period away, as it is
+                    gx = (gx + nx) % nx;
+                    gy = (gy + ny) % ny;
+                } else {
+                    gx = mirror(gx, nx, fx);
+                    gy = mirror(gy, ny, fy);
+                }
+            }
+            const int gi = gy * nx + gx;
+            vH[j] = a.Hi[gi];
+            vX[j] = a.Qxi[gi];
+            vY[j] = a.Qyi[gi];
+            fl[j] = (fx & 1) | ((fy & 1) << 1);
+        }
+#pragma unroll
+        for (int j = 0; j < NOWN; ++j) {
+            const int k = tid + j * NT, gx = tx0 + k % TX, gy = ty0 + k / TX;
+            vC[j] = a.cf[k < TX * TY && gx < nx && gy < ny ? gy * nx + gx : 0];
+        }
+        int act = 0;
+        __syncthreads();   // the previous tile's LDS and partials are read
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int k = tid + j * NT;
+            if (k >= N) continue;
+            const real H = vH[j], qx = (fl[j] & 1) ? -vX[j] : vX[j], qy = (fl[j] & 2) ? -vY[j] : vY[j];
+            const bool w = H > eps;
+            sH[k] = H;
+            sUx[k] = w ? Mth<real>::div(qx, H) : real(0);
+            sUy[k] = w ? Mth<real>::div(qy, H) : real(0);
+            // own cells and face neighbours inside the domain: K1 activity
+            if (!a.skip) continue;
+            const int lx = k % W - 1, ly = k / W - 1;
+            int gx = tx0 + lx, gy = ty0 + ly;
+            if (a.periodic) { gx = (gx + nx) % nx; gy = (gy + ny) % ny; }
+            const bool corner = (lx < 0 || lx >= TX) && (ly < 0 || ly >= TY);
+            if (!corner && gx >= 0 && gx < nx && gy >= 0 && gy < ny &&
+                (w || is_src(a, gx, gy) || (a.sigma && a.sigma[gy * nx + gx] > real(0))))
+                act = 1;
+        }
+        __syncthreads();
+        real vmax = real(0);
+        double msum = 0.0;
+#pragma unroll
+        for (int j = 0; j < NOWN; ++j) {
+            const int c = tid + j * NT, lx = c % TX, ly = c / TX;
+            if (c >= TX * TY || tx0 + lx >= nx || ty0 + ly >= ny) continue;
+            const int k = (ly + 1) * W + lx + 1;
+            const real H = sH[k];
+            msum += (double)H;
+            if (H > eps) {
+                Nb4<real> nb;
+                const int sn[4] = {k - 1, k + 1, k - W, k + W};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) { nb.ux[q] = sUx[sn[q]]; nb.uy[q] = sUy[sn[q]]; nb.w[q] = sH[sn[q]] > eps; }
+                real fx, fy;
+                soft_forces(a, H, sUx[k], sUy[k], nb, fx, fy);
+                vmax = rmax(vmax, cfl_speed(a, H, vC[j], sUx[k], sUy[k], fx, fy));
+            }
+        }
+        vmax = wave_max(vmax);
+        msum = wave_sum(msum);
+        const int any = wave_or(act);
+        if (lane == 0) { red_v[wv] = vmax; red_d[wv] = msum; red_i[wv] = any; }
+        __syncthreads();
+        if (tid == 0) {
+            double ms = 0.0;
+            for (int q = 0; q < NWAVE; ++q) { wgmax = rmax(wgmax, red_v[q]); ms += red_d[q]; }
+            a.mass[tile] = ms;
+        }
+        if (a.skip && wv == NWAVE - 1) {
+            int ac = 0;
+#pragma unroll
+            for (int q = 0; q < NWAVE; ++q) ac |= red_i[q];
+            append_tiles(lane == 0 && ac && !ring_tile(a, tile) ? tile : -1, a.sid, a.tile_base,
+                         (int)a.lctrl->step + 1, a.stamp, a.lists, a.hot, a.list_cap, a.slot, blockIdx.x % NSEG);
         }
     }
-    vmax = wave_max(vmax);
-    msum = wave_sum(msum);
-    const int any = wave_or(act);
-    const int lane = tid & 63, wv = tid >> 6;
-    if (lane == 0) { red_v[wv] = vmax; red_d[wv] = msum; red_i[wv] = any; }
-    __syncthreads();
-    if (tid == 0) {
-        real vm = real(0);
-        double ms = 0.0;
-        int ac = 0;
-        for (int q = 0; q < NWAVE; ++q) { vm = rmax(vm, red_v[q]); ms += red_d[q]; ac |= red_i[q]; }
-        a.mass[tile] = ms;
-        if (vm > real(0)) atomic_max_prep(a.ctrl, vm);
-    }
-    if (a.skip && wv == 0) {
-        int ac0 = 0;
-#pragma unroll
-        for (int q = 0; q < NWAVE; ++q) ac0 |= red_i[q];
-        append_tiles(lane == 0 && ac0 && !ring_tile(a, tile) ? tile : -1, a.sid, a.tile_base, (int)a.lctrl->step + 1,
-                     a.stamp, a.lists, a.hot, a.list_cap, a.slot, blockIdx.x % NSEG);
-    }
+    if (tid == 0 && wgmax > real(0)) atomic_max_prep(a.ctrl, wgmax);
 }
 
 // What k_prepare builds on: stamps, counters and the speed maximum cleared, in

@@ -614,6 +614,26 @@ __device__ __forceinline__ void tap_faces(const Args<real>& a, int gx, int gy, r
     }
 }
 
+// Element gi of a field through a uniform base and a 32-bit byte offset: a
+// grid has fewer than 2^20 tiles of at most 1024 FP32 or 512 FP64 cells, so
+// every field is smaller than 4 GB.
+template <typename real> __device__ __forceinline__ const real& elem(const real* p, int gi) {
+    return *(const real*)((const char*)p + (unsigned)gi * (unsigned)sizeof(real));
+}
+template <typename real> __device__ __forceinline__ real& elem(real* p, int gi) {
+    return *(real*)((char*)p + (unsigned)gi * (unsigned)sizeof(real));
+}
+
+// a / b of small numbers (a < n) as a 24-bit product and a shift: 32-bit
+// products run at a quarter of the rate.
+__host__ __device__ constexpr unsigned short_div_mul(int b) { return (65536u + b - 1) / b; }
+__host__ __device__ constexpr bool short_div_exact(int n, int b) {
+    for (int a = 0; a < n; ++a)
+        if ((int)((a * short_div_mul(b)) >> 16) != a / b) return false;
+    return true;
+}
+__device__ __forceinline__ int short_div(int a, int b) { return (int)(__umul24((unsigned)a, short_div_mul(b)) >> 16); }
+
 // ---------------------------------------------------------------- LDS of a tile
 
 // Row pitch is odd so that lanes walking down a column hit distinct banks.
@@ -623,6 +643,10 @@ struct Geo {
     static constexpr int H = TY + 2 * HALO;
     static constexpr int N = W * H;
     static __device__ __forceinline__ int at(int x, int y) { return (y + HALO) * W + x + HALO; }
+    // the same for y >= -HALO that the compiler cannot bound
+    static __device__ __forceinline__ int at24(int x, int y) {
+        return (int)__umul24((unsigned)(y + HALO), W) + x + HALO;
+    }
 };
 
 // Ten arrays in one layout, reused across the stages:
@@ -807,6 +831,8 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
     // the first tile's loads)
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
+    static_assert((NT & (NT - 1)) == 0, "power of two");
+    tid &= NT - 1;   // a known range: short divisions below
     const int nx = a.nx, ny = a.ny;
     auto wrapx = [&](int g) { if constexpr (PER) { g %= nx; if (g < 0) g += nx; } return g; };
     auto wrapy = [&](int g) { if constexpr (PER) { g %= ny; if (g < 0) g += ny; } return g; };
@@ -833,6 +859,15 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
     const bool src_here = PER ? a.ni > 0
                               : tx0 - HALO < a.i0 + a.ni && a.i0 < tx0 + TX + HALO && ty0 - HALO < a.j0 + a.nj &&
                                     a.j0 < ty0 + TY + HALO;
+    // global index of tile cell (x, y).  A tile away from the edges has a
+    // second row of tiles beside it, so its grid has fewer than 2^24 columns:
+    // one 24-bit multiply-add (full rate; a 32-bit product takes four times
+    // as long).
+    const int org = (ty0 - HALO) * nx + tx0;
+    auto cell = [&](int x, int y) {
+        if constexpr (EDGE) return (ty0 + y) * nx + tx0 + x;
+        else return org + (int)(__umul24((unsigned)(y + HALO), (unsigned)nx) + (unsigned)x);
+    };
     auto source = [&](int x, int y) { return src_here && is_src(a, wrapx(tx0 + x), wrapy(ty0 + y)); };
     auto inside = [&](int x, int y) {
         if constexpr (!EDGE || PER) return true;
@@ -852,15 +887,20 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
             const int k = tid + j * NT;
             if (k >= NL) continue;
             const int x = k % RW - HALO, y = k / RW - HALO;
-            int gx = tx0 + x, gy = ty0 + y, fx = 0, fy = 0;
-            if constexpr (PER) { gx = wrapx(gx); gy = wrapy(gy); }
-            else if constexpr (EDGE) { gx = mirror(gx, nx, fx); gy = mirror(gy, ny, fy); }
-            const int gi = gy * nx + gx;
-            vH[j] = a.Hi[gi];
-            vX[j] = a.Qxi[gi];
-            vY[j] = a.Qyi[gi];
-            vB[j] = a.bed[gi];
-            vC[j] = a.cf[gi];
+            int fx = 0, fy = 0, gi;
+            if constexpr (EDGE) {
+                int gx = tx0 + x, gy = ty0 + y;
+                if constexpr (PER) { gx = wrapx(gx); gy = wrapy(gy); }
+                else { gx = mirror(gx, nx, fx); gy = mirror(gy, ny, fy); }
+                gi = gy * nx + gx;
+            } else {
+                gi = cell(x, y);
+            }
+            vH[j] = elem(a.Hi, gi);
+            vX[j] = elem(a.Qxi, gi);
+            vY[j] = elem(a.Qyi, gi);
+            vB[j] = elem(a.bed, gi);
+            vC[j] = elem(a.cf, gi);
             vf[j] = (fx & 1) | ((fy & 1) << 1);
         }
         int act = 0;
@@ -1116,21 +1156,22 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
     // FP64 (runs of 4 -> 2, twice the lanes): 24.6 -> 21.8 us on 256 tiles.
     {
         constexpr int NRUN = (TX + 4) / RFX, RPW = 64 / NRUN, NU = (TY + 2 + RPW - 1) / RPW;
-        const int run = lane % NRUN, lrow = lane / NRUN;
+        static_assert(NU * RPW <= 128 && short_div_exact(64, NRUN), "24-bit index arithmetic");
+        const int lrow = short_div(lane, NRUN), run = lane - (int)__umul24(lrow, NRUN);
         for (int u = wv; u < NU; u += NWAVE) {
-            const int row = u * RPW + lrow, x0 = run * RFX - 2;
+            const int row = (u * RPW + lrow) & 127, x0 = run * RFX - 2;
             const bool live = lrow < RPW && row < TY + 2;   // other lanes: a copy of the last row, not stored
             const int y = (live ? row : TY + 1) - 1;
+            const int s0 = G::at24(x0, y);
             Cell<real> cl[RFX + 2];
 #pragma unroll
             for (int i = 0; i < RFX + 2; ++i) {
-                const int s = G::at(x0 - 1 + i, y);
+                const int s = s0 - 1 + i;
                 cl[i].H = L.UX[s]; cl[i].b = L.B[s]; cl[i].un = L.UY[s]; cl[i].ut = L.LM[s];
             }
             bool anyw = false;
 #pragma unroll
             for (int i = 0; i < RFX + 1; ++i) anyw |= cl[i].H > eps;
-            const int s0 = G::at(x0, y);
             if (!__any(anyw)) {   // dry on both sides of every face: zero fluxes
                 if (live) {
 #pragma unroll
@@ -1151,7 +1192,7 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
                     // face between cells gx-1 and gx: the east face of gx-1
                     const int gx = tx0 + x0 + f, gy = ty0 + y;
                     if (gx >= 1 && gx < nx && gy >= 0 && gy < ny)
-                        add_correction(a, a.corrE, gy * nx + gx - 1, cl[f].H, cl[f + 1].H, FH, Fn, Ft, true);
+                        add_correction(a, a.corrE, cell(x0 + f, y) - 1, cl[f].H, cl[f + 1].H, FH, Fn, Ft, true);
                 }
                 if (live) { L.HX[s0 + f] = FH; L.HY[s0 + f] = Fn; L.H[s0 + f] = Ft; }
             }
@@ -1179,7 +1220,7 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
     for (int j = 0; j < NOWN; ++j) {
         const int k = tid + j * NT, x = k % TX, y = k / TX;
         const bool in = k < TX * TY && inside(x, y);
-        cfn[j] = a.cf[in ? (ty0 + y) * nx + tx0 + x : 0];
+        cfn[j] = elem(a.cf, in ? cell(x, y) : 0);
     }
 
     // ---- FY + final update: columns -1..TX, runs along y with the low faces
@@ -1188,7 +1229,8 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
     // the lane after.  Runs cover cells -2..TY+1, of which -1..TY are updated.
     {
         constexpr int NRUN = (TY + 4) / RFY, CPW = 64 / NRUN, NU = (TX + 2 + CPW - 1) / CPW;
-        const int run = lane % NRUN, lcol = lane / NRUN;
+        static_assert(NU * CPW <= 128 && short_div_exact(64, NRUN), "24-bit index arithmetic");
+        const int lcol = short_div(lane, NRUN), run = lane - (int)__umul24(lcol, NRUN);
         // tap faces in this tile: a face belongs to the tile of the cell east
         // (x face) or north (y face) of it
         bool tap_here = false;
@@ -1204,13 +1246,14 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
             }
         }
         for (int u = wv; u < NU; u += NWAVE) {
-            const int col = u * CPW + lcol, y0 = run * RFY - 2;
+            const int col = (u * CPW + lcol) & 127, y0 = run * RFY - 2;
             const bool live = lcol < CPW && col < TX + 2;   // other lanes: a copy of the last column, not stored
             const int x = (live ? col : TX + 1) - 1;
+            const int s0 = G::at24(x, y0);
             Cell<real> cl[RFY + 2];
 #pragma unroll
             for (int i = 0; i < RFY + 2; ++i) {
-                const int s = G::at(x, y0 - 1 + i);
+                const int s = s0 + (i - 1) * W;
                 cl[i].H = L.UX[s]; cl[i].b = L.B[s]; cl[i].un = L.LM[s]; cl[i].ut = L.UY[s];
             }
             real FH[RFY + 1], Fn[RFY + 1], Ft[RFY + 1];
@@ -1230,7 +1273,7 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
                         // face between cells gy-1 and gy: the north face of gy-1
                         const int gx = tx0 + x, gy = ty0 + y0 + f;
                         if (gy >= 1 && gy < ny && gx >= 0 && gx < nx)
-                            add_correction(a, a.corrN, (gy - 1) * nx + gx, cl[f].H, cl[f + 1].H, FH[f], Fn[f], Ft[f],
+                            add_correction(a, a.corrN, cell(x, y0 + f) - nx, cl[f].H, cl[f + 1].H, FH[f], Fn[f], Ft[f],
                                            false);
                     }
                 }
@@ -1241,12 +1284,13 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
 #pragma unroll
                 for (int f = 0; f < RFY + 1; ++f) { FH[f] = real(0); Fn[f] = real(0); Ft[f] = real(0); }
             }
+            const int g0 = cell(x, y0);   // of the run's first cell
             // x fluxes and Q_t of the run's cells in one round of LDS reads
             // (those of rows -2 and TY+1 are not used)
             real fH[RFY][2], fN[RFY][2], fT[RFY][2], qxt[RFY], qyt[RFY];
 #pragma unroll
             for (int i = 0; i < RFY; ++i) {
-                const int s = G::at(x, y0 + i);
+                const int s = s0 + i * W;
                 fH[i][0] = L.HX[s]; fH[i][1] = L.HX[s + 1];
                 fN[i][0] = L.HY[s]; fN[i][1] = L.HY[s + 1];
                 fT[i][0] = L.H[s]; fT[i][1] = L.H[s + 1];
@@ -1256,14 +1300,14 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
             for (int i = 0; i < RFY; ++i) {
                 const int y = y0 + i;
                 if (!live || y < -1 || y > TY || !inside(x, y)) continue;
-                const int s = G::at(x, y);
+                const int s = s0 + i * W;
                 const real dxH = fH[i][0] - fH[i][1];
                 const real dxQx = fN[i][0] - fN[i][1];
                 const real dxQy = fT[i][0] - fT[i][1];
                 const real Ht = cl[i + 1].H, dH = r * (dxH + (FH[i] - FH[i + 1]));
                 real Hn = Ht + dH;
                 if constexpr (F32)
-                    Hn = round_stochastic(Ht, dH, Hn, cell_hash((unsigned)((ty0 + y) * nx + tx0 + x), lx.clk));
+                    Hn = round_stochastic(Ht, dH, Hn, cell_hash((unsigned)(g0 + i * nx), lx.clk));
                 const real qx = qxt[i] + r * (dxQx + (Ft[i] - Ft[i + 1]));
                 const real qy = qyt[i] + r * (dxQy + (Fn[i] - Fn[i + 1]));
                 const real Hc = rmax(Hn, real(0));
@@ -1273,12 +1317,12 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
                 L.GX[s] = w ? Mth<real>::div(qxo, Hc) : real(0);
                 L.GY[s] = w ? Mth<real>::div(qyo, Hc) : real(0);
                 if (x >= 0 && x < TX && y >= 0 && y < TY) {
-                    const int gi = (ty0 + y) * nx + tx0 + x;
-                    a.Ho[gi] = Hc;
-                    a.Qxo[gi] = qxo;
-                    a.Qyo[gi] = qyo;
+                    const int gi = g0 + i * nx;
+                    elem(a.Ho, gi) = Hc;
+                    elem(a.Qxo, gi) = qxo;
+                    elem(a.Qyo, gi) = qyo;
                     msum += (double)Hc;
-                    lsum += (double)(Hc - Hn);
+                    if (Hc != Hn) lsum += (double)(Hc - Hn);   // clamped: rare
                     bad |= !finite(Hn) || !finite(qx) || !finite(qy);
                     if constexpr (TAP) {
                         if (tap_here) {
@@ -1437,7 +1481,7 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> 
         // block reductions: flags, volume and ledger partials, speed
         bits = wave_or(bits | (bad ? 128 : 0));
         msum = wave_sum(msum);
-        lsum = wave_sum(lsum);
+        if (__any(lsum != 0.0)) lsum = wave_sum(lsum);
         vmax = wave_max(vmax);
         if constexpr (FLD) fsum = wave_sum(fsum);
         if (lane == 0) {
@@ -1809,7 +1853,7 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_batch_step(Batch
                                                                 0, bits, lx, nbst, s_act);
         bits = wave_or(bits | (bad ? 128 : 0));
         msum = wave_sum(msum);
-        lsum = wave_sum(lsum);
+        if (__any(lsum != 0.0)) lsum = wave_sum(lsum);
         vt = wave_max(vt);
         if (lane == 0) { red_i[wv] = bits; red_d[0][wv] = msum; red_d[1][wv] = lsum; red_v[wv] = vt; }
         __syncthreads();

@@ -64,6 +64,7 @@ struct Launcher {
                             hipEvent_t e1);  // displaced-particle corrector; may be null
     hipError_t (*step_per)(const void* args, int grid, hipStream_t st, hipEvent_t e0,
                            hipEvent_t e1);   // periodic domain; may be null
+    hipError_t (*step_grids)(const void* dargs, int n, int per, hipStream_t st);   // the grids of a nest; may be null
     hipError_t (*batch_step)(const void* bargs, int grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
     hipError_t (*batch_prepare_finish)(const void* bargs, hipStream_t st);
     hipError_t (*prepare)(const void* args, int grid, hipStream_t st);
@@ -75,6 +76,12 @@ template <typename real, int TX, int TY, int NT, int LIM, int MODE>
 hipError_t launch_step(const void* args, int grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
     const Args<real>& a = *static_cast<const Args<real>*>(args);
     hipExtLaunchKernelGGL((swe::k_step<real, TX, TY, NT, LIM, MODE>), dim3(grid), dim3(NT), 0, st, e0, e1, 0, a);
+    return hipGetLastError();
+}
+template <typename real, int TX, int TY, int NT, int LIM>
+hipError_t launch_step_grids(const void* dargs, int n, int per, hipStream_t st) {
+    hipLaunchKernelGGL((swe::k_step_grids<real, TX, TY, NT, LIM>), dim3(n * per), dim3(NT), 0, st,
+                       (const Args<real>*)dargs, n, per);
     return hipGetLastError();
 }
 template <typename real, int TX, int TY, int NT, int LIM>
@@ -111,8 +118,9 @@ int occupancy(int* blocks) {
                                         launch_step<real, TX, TY, NT, LIM, swe::MODE_CORR>, \
                                         launch_step<real, TX, TY, NT, LIM, swe::MODE_FIELD>, \
                                         launch_step<real, TX, TY, NT, LIM, swe::MODE_DISP>, \
-                                        launch_step<real, TX, TY, NT, LIM, swe::MODE_PERIODIC>
-#define NO_TAP_STEP(real, TX, TY, NT, LIM) nullptr, nullptr, nullptr, nullptr, nullptr
+                                        launch_step<real, TX, TY, NT, LIM, swe::MODE_PERIODIC>, \
+                                        launch_step_grids<real, TX, TY, NT, LIM>
+#define NO_TAP_STEP(real, TX, TY, NT, LIM) nullptr, nullptr, nullptr, nullptr, nullptr, nullptr
 #define LAUNCHER(real, TX, TY, NT, P, LIM, TAPS)                                                 \
     Launcher{TX, TY, NT, P, LIM, launch_step<real, TX, TY, NT, LIM, swe::MODE_PLAIN>,             \
              TAPS(real, TX, TY, NT, LIM),                                                        \
@@ -274,8 +282,7 @@ void fill_args(swe_t* s, int parity, Args<real>* a) {
 }
 
 // Step kernel of a grid: the tapping variant for members of a nest.
-hipError_t launch_grid_step(swe_t* s, int par, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr,
-                            hipStream_t on = nullptr) {
+hipError_t launch_grid_step(swe_t* s, int par, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr) {
     if (s->pre_step) {
         const hipError_t e = s->pre_step(s, par);
         if (e != hipSuccess) return e;
@@ -286,7 +293,7 @@ hipError_t launch_grid_step(swe_t* s, int par, hipEvent_t e0 = nullptr, hipEvent
              : s->p.sph_displaced            ? s->L->step_disp
              : s->p.periodic                 ? s->L->step_per
                                              : s->L->step;
-    return f(s->args[par].data(), s->grid, on ? on : s->stream, e0, e1);
+    return f(s->args[par].data(), s->grid, s->stream, e0, e1);
 }
 
 void build_args(swe_t* s) {
@@ -1468,6 +1475,7 @@ __global__ void swe::k_sum_tiles(const double* part, int n, double* out) {
 namespace {
 
 constexpr int NEST_GRAPH_STEPS = 8;   // coarse steps per captured graph (even)
+constexpr int NEST_GROUPS = 1024;     // workgroups of a launch over a nest's grids
 
 }  // namespace
 
@@ -1491,26 +1499,23 @@ struct swe_nest_s {
     long long launched = 0;          // coarse steps launched
     hipGraphExec_t graph = nullptr;
     std::vector<unsigned char> nargs;   // NestArgs<real>
-    // one side stream per patch (default priority): the first substep of
-    // every patch runs beside the coarse step, later substeps of patches 1..
-    // beside patch 0; forked from and joined back into the nest's stream
-    std::vector<hipStream_t> side;
-    hipEvent_t fork = nullptr;
-    hipEvent_t frame0 = nullptr;     // the first substep's frame is written
-    std::vector<hipEvent_t> join;
+    // step arguments on the device, [coarse parity][patch parity][coarse grid,
+    // then the patches], and the workgroups of each grid in a launch
+    void* dargs = nullptr;
+    int per = 0;
+    const void* grid_args(int pc, int pf, int first) const {
+        const size_t sz = precision == 32 ? sizeof(Args<float>) : sizeof(Args<double>);
+        return (const char*)dargs + sz * ((size_t)(pc * 2 + pf) * (np + 1) + first);
+    }
 };
 
 namespace {
 
 void free_nest(swe_nest_t* n) {
     if (n->graph) (void)hipGraphExecDestroy(n->graph);
-    for (hipStream_t q : n->side) if (q) { (void)hipStreamSynchronize(q); (void)hipStreamDestroy(q); }
-    if (n->fork) (void)hipEventDestroy(n->fork);
-    if (n->frame0) (void)hipEventDestroy(n->frame0);
-    for (hipEvent_t e : n->join) if (e) (void)hipEventDestroy(e);
     for (swe_t* q : n->p) if (q) swe_destroy(q);
     if (n->c) swe_destroy(n->c);
-    void* ptrs[] = {n->tap, n->ints, n->desc, n->ring_ledger, n->part, n->scalar};
+    void* ptrs[] = {n->tap, n->ints, n->desc, n->ring_ledger, n->part, n->scalar, n->dargs};
     for (void* q : ptrs) if (q) (void)hipFree(q);
 }
 
@@ -1570,42 +1575,17 @@ hipError_t nest_step_t(swe_nest_t* n) {
     const int pc = (int)(c->launched & 1);
     hipError_t e;
     // The previous close cleared the taps (creation did for the first step).
-    // Substep 0 takes its frame from layer n alone, so it runs beside the
-    // coarse step: its frame and every patch's first step on side streams
-    // forked before the coarse step and joined back before the next frame.
-    // Later substeps need layer n+1: frame on the nest's stream, patch 0
-    // there too, the others on side streams between a fork and a join.
-    const int np = (int)n->p.size();
-    if ((e = hipEventRecord(n->fork, n->stream)) != hipSuccess) return e;
-    for (int k = 0; k < np; ++k)
-        if ((e = hipStreamWaitEvent(n->side[k], n->fork, 0)) != hipSuccess) return e;
-    if ((e = launch_grid_step(c, pc)) != hipSuccess) return e;
-    c->launched++;
+    // Substep 0 takes its frame from layer n alone, so the patches' first step
+    // and the coarse step share one launch; later substeps need layer n+1.
     for (int s = 0; s < n->r; ++s) {
-        const int pf = (int)(n->p[0]->launched & 1);
-        const bool first = s == 0;
-        hipLaunchKernelGGL(swe::k_frame<real>, dim3(blocks_for(na.nframe, 256)), dim3(256), 0,
-                           first ? n->side[0] : n->stream, na, pf, pc, (real)((double)s / (double)n->r));
+        const int pf = (int)(n->p[0]->launched & 1), first = s == 0 ? 0 : 1;
+        hipLaunchKernelGGL(swe::k_frame<real>, dim3(blocks_for(na.nframe, 256)), dim3(256), 0, n->stream, na, pf, pc,
+                           (real)((double)s / (double)n->r));
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (first) {   // the other patches' first step waits for the frame
-            if ((e = hipEventRecord(n->frame0, n->side[0])) != hipSuccess) return e;
-            for (int k = 1; k < np; ++k)
-                if ((e = hipStreamWaitEvent(n->side[k], n->frame0, 0)) != hipSuccess) return e;
-        } else if (np > 1) {
-            if ((e = hipEventRecord(n->fork, n->stream)) != hipSuccess) return e;
-            for (int k = 1; k < np; ++k)
-                if ((e = hipStreamWaitEvent(n->side[k], n->fork, 0)) != hipSuccess) return e;
-        }
-        for (int k = 0; k < np; ++k) {
-            swe_t* q = n->p[k];
-            hipStream_t st = first || k ? n->side[k] : nullptr;   // nullptr: the nest's stream
-            if ((e = launch_grid_step(q, pf, nullptr, nullptr, st)) != hipSuccess) return e;
-            q->launched++;
-        }
-        for (int k = first ? 0 : 1; k < np; ++k) {
-            if ((e = hipEventRecord(n->join[k], n->side[k])) != hipSuccess) return e;
-            if ((e = hipStreamWaitEvent(n->stream, n->join[k], 0)) != hipSuccess) return e;
-        }
+        if ((e = c->L->step_grids(n->grid_args(pc, pf, first), n->np + 1 - first, n->per, n->stream)) != hipSuccess)
+            return e;
+        if (s == 0) c->launched++;
+        for (swe_t* q : n->p) q->launched++;
     }
     const Args<real>& an = *(const Args<real>*)c->args[pc ^ 1].data();
     if (n->feedback) {
@@ -1884,14 +1864,21 @@ swe_nest_t* swe_nest_create(int nx, int ny, double dx, const double* b, const do
         if (!g) { std::string m_ = g_err; free_nest(n); delete n; g_err = m_; return nullptr; }
         n->p.push_back(g);
     }
-    n->side.assign(npatch, nullptr);
-    n->join.assign(npatch, nullptr);
-    NK(hipEventCreateWithFlags(&n->fork, hipEventDisableTiming));
-    NK(hipEventCreateWithFlags(&n->frame0, hipEventDisableTiming));
-    for (int k = 0; k < npatch; ++k) {
-        NK(hipStreamCreateWithFlags(&n->side[k], hipStreamNonBlocking));
-        NK(hipEventCreateWithFlags(&n->join[k], hipEventDisableTiming));
+    // Workgroups of a grid in a launch: one per tile where the launch stays
+    // within NEST_GROUPS, twice what is resident at once (a workgroup strides
+    // over further tiles; one without a tile holds its place for a read of the
+    // control block only), and at least 64.
+    int tiles = n->c->ntiles;
+    for (swe_t* q : n->p) tiles = std::max(tiles, q->ntiles);
+    n->per = std::min((tiles + swe::NSEG - 1) / swe::NSEG, std::max(8, NEST_GROUPS / (swe::NSEG * (npatch + 1)))) * swe::NSEG;
+    std::vector<unsigned char> all;
+    for (int k = 0; k < 4; ++k) {
+        all.insert(all.end(), n->c->args[k >> 1].begin(), n->c->args[k >> 1].end());
+        for (swe_t* q : n->p) all.insert(all.end(), q->args[k & 1].begin(), q->args[k & 1].end());
     }
+    NK(hipMalloc(&n->dargs, all.size()));
+    NK(hipMemcpyAsync(n->dargs, all.data(), all.size(), hipMemcpyHostToDevice, n->stream));
+    NK(hipStreamSynchronize(n->stream));
     int rc = 0;
     if (n->precision == 32) {
         fill_nest_args<float>(n, nframe, ncov, nring, n->ints + o_rcell, n->ints + o_roff, n->ints + o_rface);

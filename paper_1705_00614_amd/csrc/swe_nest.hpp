@@ -112,8 +112,8 @@ __global__ void k_frame(NestArgs<real> n, int pf, int pc, real theta) {
     }
     const int ci = d.ci0 + floor_div(fi - G, n.r), cj = d.cj0 + floor_div(fj - G, n.r);
     const int gc = cj * n.nx + ci, gf = fj * nxe + fi;
-    // at theta = 0 the frame is layer n alone (layer n+1 may still be being
-    // computed beside this launch): both terms take layer n's value
+    // at theta = 0 the frame is layer n alone (layer n+1 is not computed yet):
+    // both terms take layer n's value
     const int pn = theta > real(0) ? pc ^ 1 : pc;
     const real u = real(1) - theta;
     const real Hm = u * n.Hc[pc][gc] + theta * n.Hc[pn][gc];

@@ -1397,8 +1397,9 @@ template <typename real> constexpr int waves_per_simd() {
     return sizeof(real) == 4 ? SWE_WAVES_PER_SIMD_F32 : SWE_WAVES_PER_SIMD_F64;
 }
 
+// One step of a grid by workgroup b0 of its G.
 template <typename real, int TX, int TY, int NT, int LIM, int MODE>
-__global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> a) {
+__device__ __forceinline__ void step_grid(const Args<real>& a, int b0, int G) {
     constexpr int NWAVE = NT / 64;
     __shared__ Lds<real, TX, TY> L;
     __shared__ double red_d[MODE == MODE_FIELD ? 3 : 2][NWAVE];
@@ -1411,11 +1412,10 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> 
     // (one memory round trip before the tile load, not two); it is used when
     // the list is no longer than the grid and its segment is long enough.
     constexpr bool RING = MODE == MODE_TAP;
-    const int b0 = blockIdx.x;
     const bool spec_in = !RING && a.skip && b0 / NSEG < a.ntiles;
     const int spec = spec_in ? a.lists[(a.slot * NSEG + b0 % NSEG) * a.ntiles + b0 / NSEG] : 0;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int G = gridDim.x, grp = blockIdx.x % NSEG;
+    const int grp = b0 % NSEG;
     // only the patches of a nest (tapping grids) carry ring tiles; the other
     // variants compile without them (no registers held for their bounds)
     int off[NSEG + 1];
@@ -1449,7 +1449,7 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> 
     double vm = 0.0;      // thread 0: speed maximum and error of the workgroup's tiles
     bool anybad = false;
 
-    for (int p = blockIdx.x; p < npos; p += G) {
+    for (int p = b0; p < npos; p += G) {
         const int tile = !a.skip ? p
                          : first >= 0 ? first
                          : RING && p >= nlist ? a.ring_tiles[p - nlist]
@@ -1601,6 +1601,41 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> 
         for (int g = 0; g < NSEG; ++g) { h64[hot_cnt(g) / 2] = 0ull; h64[hot_spd(g) / 2] = 0ull; }
         a.hot[hot_done(NSEG)] = 0;
     }
+}
+
+template <typename real, int TX, int TY, int NT, int LIM, int MODE>
+__global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> a) {
+    step_grid<real, TX, TY, NT, LIM, MODE>(a, blockIdx.x, gridDim.x);
+}
+
+// Arguments of scenario (or grid) `sid` for a workgroup: `sid` is the same in
+// every lane and the array does not change while kernels run, so the fields come through the
+// scalar cache into scalar registers.  Read through a plain reference they
+// were fetched by vector loads inside every stage, each a memory round trip
+// after the tile's stores.
+template <typename real>
+__device__ __forceinline__ Args<real> scalar_args(const Args<real>* scen, int sid) {
+    typedef const __attribute__((address_space(4))) unsigned* cptr;
+    static_assert(sizeof(Args<real>) % 4 == 0 && alignof(Args<real>) >= 4, "copied as words");
+    const cptr src = (cptr)(uintptr_t)(scen + __builtin_amdgcn_readfirstlane(sid));
+    union U { Args<real> a; unsigned w[sizeof(Args<real>) / 4]; __device__ U() {} } u;
+#pragma unroll
+    for (unsigned k = 0; k < sizeof(Args<real>) / 4; ++k) u.w[k] = src[k];
+    return u.a;
+}
+
+// One step of each of n independent grids (a nest's coarse grid and patches,
+// or its patches), G workgroups each: one launch instead of one per grid on
+// streams forked and joined around it, where each fork and join cost 5 to 10
+// us between 20 us steps (512 x 512 cells with 4 patches of 394 x 394, FP32:
+// 195 -> 126 us per coarse step of 4 substeps).  Groups of NSEG workgroups go to the grids in turn,
+// so that a grid's workgroup b runs on XCD b % NSEG as in a launch of its own
+// and the first workgroups of every grid -- those with tiles -- start first.
+template <typename real, int TX, int TY, int NT, int LIM>
+__global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step_grids(const Args<real>* grids, int n, int G) {
+    const int q = blockIdx.x / NSEG, grid = q % n;
+    const Args<real> a = scalar_args(grids, grid);
+    step_grid<real, TX, TY, NT, LIM, MODE_TAP>(a, (q / n) * NSEG + blockIdx.x % NSEG, G);
 }
 
 // ---------------------------------------------------------------- preparation kernel
@@ -1790,22 +1825,6 @@ struct BatchArgs {
     int list_cap;             // capacity of one list segment (all tiles of the batch)
     int slot;                 // list slot read by this step
 };
-
-// A scenario's arguments for a workgroup: `sid` is the same in every lane and
-// the array does not change while kernels run, so the fields come through the
-// scalar cache into scalar registers.  Read through a plain reference they
-// were fetched by vector loads inside every stage, each a memory round trip
-// after the tile's stores.
-template <typename real>
-__device__ __forceinline__ Args<real> scalar_args(const Args<real>* scen, int sid) {
-    typedef const __attribute__((address_space(4))) unsigned* cptr;
-    static_assert(sizeof(Args<real>) % 4 == 0 && alignof(Args<real>) >= 4, "copied as words");
-    const cptr src = (cptr)(uintptr_t)(scen + __builtin_amdgcn_readfirstlane(sid));
-    union U { Args<real> a; unsigned w[sizeof(Args<real>) / 4]; __device__ U() {} } u;
-#pragma unroll
-    for (unsigned k = 0; k < sizeof(Args<real>) / 4; ++k) u.w[k] = src[k];
-    return u.a;
-}
 
 template <typename real, int TX, int TY, int NT, int LIM>
 __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_batch_step(BatchArgs<real> ba) {

@@ -216,6 +216,24 @@ def test_patches_skip_dry_tiles_exactly(prec, vs_oracle, box):
         _compare(a, O, prec, "skip box %s" % (box,))
 
 
+@pytest.mark.parametrize("skip", [True, False])
+@pytest.mark.parametrize("n,boxes", [
+    (24, [(8, 9, 5, 4)]),                                                         # fewer tiles than workgroup groups
+    (200, [(4 + 32 * (k % 6), 4 + 32 * (k // 6), 3, 2) for k in range(36)]),      # 169 tiles, 64 workgroups per grid
+])
+def test_grids_share_a_launch(n, boxes, skip):
+    """The grids of a nest step in one launch with the same number of
+    workgroups each: more workgroups than a grid has tiles, and fewer than the
+    coarse grid has.  FP64 against the oracle, the module's bars."""
+    sc = S.random_state(n, n, seed=29, wet_frac=0.7, precision=64)
+    nest = S.nest(sc, boxes, r=2, seed=5, detail=0.3)
+    O = OracleNest(nest["coarse"], nest["patches"], r=2)
+    G = swe.Nest(nest, skip_dry=skip)
+    G.run(3)
+    O.run(3)
+    _compare(G, O, 64, label="n=%d" % n)
+
+
 def test_full_size_nest_first_coarse_steps_match_oracle():
     """The nested-grid benchmark workload at its full size (2048^2 coarse
     grid at 50 m with two 2048^2 patches at 12.5 m, dry-tile skipping) for

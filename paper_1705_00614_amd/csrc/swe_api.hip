@@ -1493,9 +1493,10 @@ struct swe_nest_s {
     double* part = nullptr;          // volume partials
     int npart = 0, chunk = 0;
     double* scalar = nullptr;
-    int nforce = 0, nregion = 0, nregion_cells = 0, nring = 0;
+    int nforce = 0, nring = 0;
     const int* force_tiles = nullptr;
-    const int* region = nullptr;
+    const int* region = nullptr;     // x0, y0, x1, y1 per patch: the covered box widened by 2 cells
+    int max_frame = 0, max_cov = 0, max_region = 0;   // cells, of the patch with the most
     long long launched = 0;          // coarse steps launched
     hipGraphExec_t graph = nullptr;
     std::vector<unsigned char> nargs;   // NestArgs<real>
@@ -1520,13 +1521,13 @@ void free_nest(swe_nest_t* n) {
 }
 
 template <typename real>
-void fill_nest_args(swe_nest_t* n, int nframe, int ncov, int nring, const int* ring_cell, const int* ring_off,
+void fill_nest_args(swe_nest_t* n, int nring, const int* ring_cell, const int* ring_off,
                     const int* ring_face) {
     n->nargs.assign(sizeof(swe::NestArgs<real>), 0);
     swe::NestArgs<real>* a = (swe::NestArgs<real>*)n->nargs.data();
     a->P = (const swe::NestPatch<real>*)n->desc;
     a->np = n->np; a->r = n->r; a->nx = n->c->nx; a->ny = n->c->ny;
-    a->nframe = nframe; a->ncov = ncov; a->nring = nring;
+    a->nring = nring;
     for (int k = 0; k < 2; ++k) {
         a->Hc[k] = (real*)n->c->Hb[k]; a->Qxc[k] = (real*)n->c->Qxb[k]; a->Qyc[k] = (real*)n->c->Qyb[k];
     }
@@ -1540,15 +1541,13 @@ void fill_nest_args(swe_nest_t* n, int nframe, int ncov, int nring, const int* r
 }
 
 template <typename real>
-int upload_desc(swe_nest_t* n, const std::vector<int>& frame_base, const std::vector<int>& cov_base,
-                const std::vector<int>& ftap, const std::vector<int>& ctap) {
+int upload_desc(swe_nest_t* n, const std::vector<int>& ftap, const std::vector<int>& ctap) {
     std::vector<swe::NestPatch<real>> d(n->np);
     for (int k = 0; k < n->np; ++k) {
         const swe_patch& b = n->box[k];
         swe::NestPatch<real>& e = d[k];
         e.ci0 = b.ci0; e.cj0 = b.cj0; e.cw = b.cw; e.ch = b.ch;
         e.nxe = n->p[k]->nx; e.nye = n->p[k]->ny;
-        e.frame_base = frame_base[k]; e.cov_base = cov_base[k];
         e.ftap = ftap[k]; e.ctap = ctap[k];
         for (int q = 0; q < 2; ++q) {
             e.Hf[q] = (real*)n->p[k]->Hb[q]; e.Qxf[q] = (real*)n->p[k]->Qxb[q]; e.Qyf[q] = (real*)n->p[k]->Qyb[q];
@@ -1579,8 +1578,8 @@ hipError_t nest_step_t(swe_nest_t* n) {
     // and the coarse step share one launch; later substeps need layer n+1.
     for (int s = 0; s < n->r; ++s) {
         const int pf = (int)(n->p[0]->launched & 1), first = s == 0 ? 0 : 1;
-        hipLaunchKernelGGL(swe::k_frame<real>, dim3(blocks_for(na.nframe, 256)), dim3(256), 0, n->stream, na, pf, pc,
-                           (real)((double)s / (double)n->r));
+        hipLaunchKernelGGL(swe::k_frame<real>, dim3(blocks_for(n->max_frame, 256), n->np), dim3(256), 0, n->stream, na,
+                           pf, pc, (real)((double)s / (double)n->r));
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if ((e = c->L->step_grids(n->grid_args(pc, pf, first), n->np + 1 - first, n->per, n->stream)) != hipSuccess)
             return e;
@@ -1590,15 +1589,13 @@ hipError_t nest_step_t(swe_nest_t* n) {
     const Args<real>& an = *(const Args<real>*)c->args[pc ^ 1].data();
     if (n->feedback) {
         const int pf = (int)(n->p[0]->launched & 1);
-        hipLaunchKernelGGL(swe::k_feedback<real>, dim3(blocks_for(na.ncov + na.nring, 256)), dim3(256), 0,
-                           n->stream, na, pf, pc ^ 1);
+        hipLaunchKernelGGL(swe::k_feedback<real>, dim3(blocks_for(std::max(n->max_cov, na.nring), 256), 1 + n->np),
+                           dim3(256), 0, n->stream, na, pf, pc ^ 1);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         const int nforce = c->p.skip_dry ? n->nforce : 0;
-        const int blocks = std::max(blocks_for(n->nregion_cells, 256 * swe::NEST_CLOSE_CELLS),
-                                    std::max(blocks_for(n->ntap, 256), blocks_for(nforce, 256)));
-        const int grid = std::max(1, std::min(blocks, swe::NEST_CLOSE_GRID));
-        hipLaunchKernelGGL(swe::k_nest_close<real>, dim3(grid), dim3(256), 0, n->stream, an, na, n->region,
-                           n->nregion, n->nregion_cells, n->force_tiles, nforce, n->ntap, pc ^ 1);
+        const int row = std::max(1, std::min(blocks_for(n->max_region, 256), swe::NEST_CLOSE_GRID / n->np));
+        hipLaunchKernelGGL(swe::k_nest_close<real>, dim3(row, n->np), dim3(256), 0, n->stream, an, na, n->region,
+                           n->force_tiles, nforce, n->ntap, pc ^ 1);
         return hipGetLastError();
     }
     const int tb = blocks_for(n->ntap, 256);
@@ -1617,8 +1614,8 @@ template <typename real>
 int nest_init_tau(swe_nest_t* n) {
     const swe::NestArgs<real>& na = *(const swe::NestArgs<real>*)n->nargs.data();
     const int pc = (int)(n->c->launched & 1), pf = (int)(n->p[0]->launched & 1);
-    hipLaunchKernelGGL(swe::k_frame<real>, dim3(blocks_for(na.nframe, 256)), dim3(256), 0, n->stream, na, pf, pc,
-                       (real)0);
+    hipLaunchKernelGGL(swe::k_frame<real>, dim3(blocks_for(n->max_frame, 256), n->np), dim3(256), 0, n->stream, na, pf,
+                       pc, (real)0);
     HIPCHK(hipGetLastError());
     for (swe_t* q : n->p) {
         int rc = prepare(q);
@@ -1726,15 +1723,13 @@ swe_nest_t* swe_nest_create(int nx, int ny, double dx, const double* b, const do
     } while (0)
 
     // ---- host layout: taps, rects, ring CSR, forced tiles, speed regions
-    std::vector<int> ctap(npatch), ftap(npatch), frame_base(npatch), cov_base(npatch);
-    int ntap = 0, nframe = 0, ncov = 0;
+    std::vector<int> ctap(npatch), ftap(npatch);
+    int ntap = 0;
     for (int k = 0; k < npatch; ++k) { ctap[k] = ntap; ntap += 3 * 2 * (patches[k].cw + patches[k].ch); }
     for (int k = 0; k < npatch; ++k) {
         const swe_patch& q = patches[k];
         ftap[k] = ntap; ntap += 3 * 2 * r * (q.cw + q.ch);
-        frame_base[k] = nframe;
-        nframe += (r * q.cw + 2 * G) * (r * q.ch + 2 * G) - r * q.cw * r * q.ch;
-        cov_base[k] = ncov; ncov += q.cw * q.ch;
+        n->max_frame = std::max(n->max_frame, swe::nest_frame_cells(r * q.cw + 2 * G, r * q.ch + 2 * G));
     }
     n->ntap = ntap;
     std::vector<int> ints;
@@ -1785,19 +1780,17 @@ swe_nest_t* swe_nest_create(int nx, int ny, double dx, const double* b, const do
     const int ntx = (nx + L->tx - 1) / L->tx, nty = (ny + L->ty - 1) / L->ty;
     std::vector<char> forced((size_t)ntx * nty, 0);
     const size_t o_region = ints.size();
-    int ncells = 0;
     for (int k = 0; k < npatch; ++k) {
         const swe_patch& q = patches[k];
         const int x0 = std::max(q.ci0 - 2, 0), y0 = std::max(q.cj0 - 2, 0);
         const int x1 = std::min(q.ci0 + q.cw + 2, nx), y1 = std::min(q.cj0 + q.ch + 2, ny);
-        int v[5] = {x0, y0, x1, y1, ncells};
-        ints.insert(ints.end(), v, v + 5);
-        ncells += (x1 - x0) * (y1 - y0);
+        const int v[4] = {x0, y0, x1, y1};
+        ints.insert(ints.end(), v, v + 4);
+        n->max_region = std::max(n->max_region, (x1 - x0) * (y1 - y0));
+        n->max_cov = std::max(n->max_cov, q.cw * q.ch);
         for (int tj = y0 / L->ty; tj <= (y1 - 1) / L->ty; ++tj)
             for (int ti = x0 / L->tx; ti <= (x1 - 1) / L->tx; ++ti) forced[(size_t)tj * ntx + ti] = 1;
     }
-    n->nregion = npatch;
-    n->nregion_cells = ncells;
     const size_t o_force = ints.size();
     for (size_t t = 0; t < forced.size(); ++t)
         if (forced[t]) ints.push_back((int)t);
@@ -1881,12 +1874,12 @@ swe_nest_t* swe_nest_create(int nx, int ny, double dx, const double* b, const do
     NK(hipStreamSynchronize(n->stream));
     int rc = 0;
     if (n->precision == 32) {
-        fill_nest_args<float>(n, nframe, ncov, nring, n->ints + o_rcell, n->ints + o_roff, n->ints + o_rface);
-        rc = upload_desc<float>(n, frame_base, cov_base, ftap, ctap);
+        fill_nest_args<float>(n, nring, n->ints + o_rcell, n->ints + o_roff, n->ints + o_rface);
+        rc = upload_desc<float>(n, ftap, ctap);
         if (!rc) rc = nest_init_tau<float>(n);
     } else {
-        fill_nest_args<double>(n, nframe, ncov, nring, n->ints + o_rcell, n->ints + o_roff, n->ints + o_rface);
-        rc = upload_desc<double>(n, frame_base, cov_base, ftap, ctap);
+        fill_nest_args<double>(n, nring, n->ints + o_rcell, n->ints + o_roff, n->ints + o_rface);
+        rc = upload_desc<double>(n, ftap, ctap);
         if (!rc) rc = nest_init_tau<double>(n);
     }
     if (!rc) rc = nest_finish(n);

@@ -53,7 +53,6 @@ template <typename real>
 struct NestPatch {
     int ci0, cj0, cw, ch;          // covered coarse box
     int nxe, nye;                  // extended fine grid (interior + frame)
-    int frame_base, cov_base;      // prefix sums over the patches: frame cells, covered cells
     int ftap, ctap;                // offsets of the patch's and the coarse box's taps
     real* Hf[2]; real* Qxf[2]; real* Qyf[2];
     const real* bf;
@@ -66,7 +65,7 @@ template <typename real>
 struct NestArgs {
     const NestPatch<real>* P;
     int np, r, nx, ny;             // patches, refinement, coarse grid
-    int nframe, ncov, nring;       // frame cells, covered cells, ring cells (all patches)
+    int nring;                     // ring cells (all patches)
     real* Hc[2]; real* Qxc[2]; real* Qyc[2];
     const real* bc;
     real* tap;
@@ -79,27 +78,24 @@ struct NestArgs {
     double hold;                   // held coarse step length (0: the CFL rule)
 };
 
-__device__ __forceinline__ int floor_div(int a, int r) { return a >= 0 ? a / r : -((-a + r - 1) / r); }
-
-template <typename real>
-__device__ __forceinline__ int find_patch(const NestPatch<real>* P, int np, int t, bool frame) {
-    int k = 0;
-    for (int q = 1; q < np; ++q) k += t >= (frame ? P[q].frame_base : P[q].cov_base);
-    return k;
+__host__ __device__ constexpr int nest_frame_cells(int nxe, int nye) {
+    return 2 * NEST_FRAME * (nxe + nye - 2 * NEST_FRAME);
 }
 
+__device__ __forceinline__ int floor_div(int a, int r) { return a >= 0 ? a / r : -((-a + r - 1) / r); }
 
 // Frame of every patch at time theta in [0, 1) of the coarse step, written to
 // the patch buffers pf; the coarse layers n and n+1 are in buffers pc, pc^1.
+// Bound by its chain of memory round trips (a few us with 30 k frame cells):
+// a row of workgroups per patch (blockIdx.y) makes the descriptor a scalar
+// load, and everything a cell may need is loaded before the first use.
 template <typename real>
-__global__ void k_frame(NestArgs<real> n, int pf, int pc, real theta) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n.nframe) return;
-    const int k = find_patch(n.P, n.np, t, true);
-    const NestPatch<real>& d = n.P[k];
+__global__ __launch_bounds__(256) void k_frame(NestArgs<real> n, int pf, int pc, real theta) {
+    const NestPatch<real>& d = n.P[blockIdx.y];
     constexpr int G = NEST_FRAME;
     const int nxe = d.nxe, nye = d.nye;
-    int m = t - d.frame_base, fi, fj;
+    int m = blockIdx.x * 256 + threadIdx.x, fi, fj;
+    if (m >= nest_frame_cells(nxe, nye)) return;
     if (m < G * nxe) {
         fj = m / nxe; fi = m % nxe;
     } else if (m < 2 * G * nxe) {
@@ -115,28 +111,58 @@ __global__ void k_frame(NestArgs<real> n, int pf, int pc, real theta) {
     // at theta = 0 the frame is layer n alone (layer n+1 is not computed yet):
     // both terms take layer n's value
     const int pn = theta > real(0) ? pc ^ 1 : pc;
+    const real h0 = n.Hc[pc][gc], h1 = n.Hc[pn][gc], x0 = n.Qxc[pc][gc], x1 = n.Qxc[pn][gc];
+    const real y0 = n.Qyc[pc][gc], y1 = n.Qyc[pn][gc], bc = n.bc[gc], bf = d.bf[gf];
     const real u = real(1) - theta;
-    const real Hm = u * n.Hc[pc][gc] + theta * n.Hc[pn][gc];
+    const real Hm = u * h0 + theta * h1;
     const bool w = Hm > n.eps;
-    const real eta = Hm + n.bc[gc];
-    const real Hf = w ? rmax(real(0), eta - d.bf[gf]) : real(0);
+    const real eta = Hm + bc;
+    const real Hf = w ? rmax(real(0), eta - bf) : real(0);
     d.Hf[pf][gf] = Hf;
     // the coarse velocity carried by the fine depth (not the coarse
     // discharge, which on a high spot of the fine bed would be a fast film)
-    d.Qxf[pf][gf] = w ? Hf * Mth<real>::div(u * n.Qxc[pc][gc] + theta * n.Qxc[pn][gc], Hm) : real(0);
-    d.Qyf[pf][gf] = w ? Hf * Mth<real>::div(u * n.Qyc[pc][gc] + theta * n.Qyc[pn][gc], Hm) : real(0);
+    d.Qxf[pf][gf] = w ? Hf * Mth<real>::div(u * x0 + theta * x1, Hm) : real(0);
+    d.Qyf[pf][gf] = w ? Hf * Mth<real>::div(u * y0 + theta * y1, Hm) : real(0);
+}
+
+// Sums of the r x r fine cells from offset g0 on, row by row.  N loads per
+// field are under way together (past the last cell it is loaded again and 0
+// added, which leaves a sum unchanged: none is -0).
+template <typename real, int N>
+__device__ __forceinline__ void block_sums(const NestPatch<real>& d, int pf, int r, int g0, double& sH, double& sX,
+                                           double& sY) {
+    int jj = 0, ii = 0;
+    for (int m0 = 0; m0 < r * r; m0 += N) {
+        real h[N], x[N], y[N];
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            const int g = g0 + jj * d.nxe + ii;
+            h[q] = d.Hf[pf][g]; x[q] = d.Qxf[pf][g]; y[q] = d.Qyf[pf][g];
+            if (m0 + q + 1 < r * r && ++ii == r) { ii = 0; ++jj; }
+        }
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            const bool in = m0 + q < r * r;
+            sH += in ? (double)h[q] : 0.0;
+            sX += in ? (double)x[q] : 0.0;
+            sY += in ? (double)y[q] : 0.0;
+        }
+    }
 }
 
 // Restriction of the fine layer (patch buffers pf) into the covered coarse
-// cells and the flux correction of the ring cells, both in coarse buffer po.
+// cells (row 1 + k of the grid: patch k) and the flux correction of the ring
+// cells (row 0), both in coarse buffer po.  Bound by its chains of memory
+// round trips: the loads of a fine block and of a ring face's taps go
+// together.
 template <typename real>
-__global__ void k_feedback(NestArgs<real> n, int pf, int po) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void k_feedback(NestArgs<real> n, int pf, int po) {
+    const int t = blockIdx.x * 256 + threadIdx.x;
     const int r = n.r;
-    if (t < n.ncov) {
-        const int k = find_patch(n.P, n.np, t, false);
-        const NestPatch<real>& d = n.P[k];
-        const int m = t - d.cov_base, cy = m / d.cw, cx = m % d.cw;
+    if (blockIdx.y > 0) {
+        const NestPatch<real>& d = n.P[blockIdx.y - 1];
+        if (t >= d.cw * d.ch) return;
+        const int cy = t / d.cw, cx = t % d.cw;
         const int gc = (d.cj0 + cy) * n.nx + d.ci0 + cx;
         // a block whose tiles hold no water at all (depth sums exactly 0, so
         // every depth and discharge is +0) restricts to zero without being read
@@ -150,13 +176,9 @@ __global__ void k_feedback(NestArgs<real> n, int pf, int po) {
             return;
         }
         double sH = 0.0, sX = 0.0, sY = 0.0;
-        for (int jj = 0; jj < r; ++jj)
-            for (int ii = 0; ii < r; ++ii) {
-                const int gf = (NEST_FRAME + cy * r + jj) * d.nxe + NEST_FRAME + cx * r + ii;
-                sH += (double)d.Hf[pf][gf];
-                sX += (double)d.Qxf[pf][gf];
-                sY += (double)d.Qyf[pf][gf];
-            }
+        const int g0 = fy0 * d.nxe + fx0;
+        if (r > 2) block_sums<real, 16>(d, pf, r, g0, sH, sX, sY);
+        else block_sums<real, 4>(d, pf, r, g0, sH, sX, sY);
         // the restricted cell follows the dry rule of every stored layer: no
         // discharge in a cell with H <= eps (the block mean of a few wet fine
         // cells can leave a dry coarse cell)
@@ -168,9 +190,11 @@ __global__ void k_feedback(NestArgs<real> n, int pf, int po) {
         n.Qyc[po][gc] = w ? (real)(sY * inv) : real(0);
         return;
     }
-    const int q = t - n.ncov;
+    const int q = t;
     if (q >= n.nring) return;
     const int gc = n.ring_cell[q];
+    const real Hc = n.Hc[po][gc], Qxc = n.Qxc[po][gc], Qyc = n.Qyc[po][gc];
+    const double led = n.ring_ledger[q];
     real dH = real(0), dQx = real(0), dQy = real(0);
     for (int e = n.ring_off[q]; e < n.ring_off[q + 1]; ++e) {
         const int k = n.ring_face[3 * e], side = n.ring_face[3 * e + 1], idx = n.ring_face[3 * e + 2];
@@ -180,13 +204,22 @@ __global__ void k_feedback(NestArgs<real> n, int pf, int po) {
         const int oc = side == 0 ? idx : side == 1 ? d.ch + idx : side == 2 ? 2 * d.ch + idx : 2 * d.ch + d.cw + idx;
         const int of = side == 0 ? r * idx : side == 1 ? nyf + r * idx
                      : side == 2 ? 2 * nyf + r * idx : 2 * nyf + nxf + r * idx;
-        real corr[3];
+        real corr[3], tc[3], fs[3] = {real(0), real(0), real(0)};
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            real fs = real(0);
-            for (int j = 0; j < r; ++j) fs += n.tap[d.ftap + c * pf_ + of + j];
-            corr[c] = (n.tap[d.ctap + c * pc_ + oc] - fs / (real)r) * n.ih;
+        for (int c = 0; c < 3; ++c) tc[c] = n.tap[d.ctap + c * pc_ + oc];
+        for (int j0 = 0; j0 < r; j0 += 4) {   // (as block_sums)
+            real v[3][4];
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[c][j] = n.tap[d.ftap + c * pf_ + of + min(j0 + j, r - 1)];
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) fs[c] += j0 + j < r ? v[c][j] : real(0);
         }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) corr[c] = (tc[c] - fs[c] / (real)r) * n.ih;
         // the covered box lies east of a W ring cell (its outflow face) and
         // north of an S ring cell
         const real sg = (side == 0 || side == 2) ? real(1) : real(-1);
@@ -194,27 +227,16 @@ __global__ void k_feedback(NestArgs<real> n, int pf, int po) {
         if (side < 2) { dQx += sg * corr[1]; dQy += sg * corr[2]; }
         else { dQy += sg * corr[1]; dQx += sg * corr[2]; }
     }
-    const real Hn = n.Hc[po][gc] + dH;
+    const real Hn = Hc + dH;
     const real Hcl = rmax(Hn, real(0));
-    n.ring_ledger[q] += (double)(Hcl - Hn) * n.h2;
+    n.ring_ledger[q] = led + (double)(Hcl - Hn) * n.h2;
     const bool w = Hcl > n.eps;
     // momentum weight: 0 up to NEST_MOMENTUM_DEPTH, 1 from twice that,
     // linear between (continuous: rounding cannot flip it)
     const real wm = rmin(real(1), rmax(real(0), Hcl / (real)NEST_MOMENTUM_DEPTH - real(1)));
     n.Hc[po][gc] = Hcl;
-    n.Qxc[po][gc] = w ? n.Qxc[po][gc] + wm * dQx : real(0);
-    n.Qyc[po][gc] = w ? n.Qyc[po][gc] + wm * dQy : real(0);
-}
-
-// Cell t of the cells the feedback can change: each covered box widened by
-// 2 cells (rects: x0, y0, x1, y1, cell prefix).
-__device__ __forceinline__ void region_cell(const int* rects, int nrect, int t, int& gx, int& gy) {
-    int k = 0;
-    for (int q = 1; q < nrect; ++q) k += t >= rects[5 * q + 4];
-    const int* R = rects + 5 * k;
-    const int m = t - R[4], w = R[2] - R[0];
-    gx = R[0] + m % w;
-    gy = R[1] + m / w;
+    n.Qxc[po][gc] = w ? Qxc + wm * dQx : real(0);
+    n.Qyc[po][gc] = w ? Qyc + wm * dQy : real(0);
 }
 
 // CFL speed of the new coarse layer (buffers of a's input) at cell (gx, gy);
@@ -223,6 +245,7 @@ template <typename real>
 __device__ real region_speed(const Args<real>& a, int gx, int gy) {
     const real eps = a.eps;
     real Hs[5], ux[5], uy[5];
+    const real cf = a.cf[gy * a.nx + gx];
     const int ox[5] = {0, -1, 1, 0, 0}, oy[5] = {0, 0, 0, -1, 1};
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
@@ -244,7 +267,7 @@ __device__ real region_speed(const Args<real>& a, int gx, int gy) {
     for (int q = 0; q < 4; ++q) { nb.ux[q] = ux[q + 1]; nb.uy[q] = uy[q + 1]; nb.w[q] = Hs[q + 1] > eps; }
     real fx, fy;
     soft_forces(a, Hs[0], ux[0], uy[0], nb, fx, fy);
-    return cfl_speed(a, Hs[0], a.cf[gy * a.nx + gx], ux[0], uy[0], fx, fy);
+    return cfl_speed(a, Hs[0], cf, ux[0], uy[0], fx, fy);
 }
 
 // Lengths of the next coarse step (tc, rounded to the stencil type) and of
@@ -278,22 +301,39 @@ __global__ void k_nest_set_dt(Args<real> a, NestArgs<real> n, double tc) {
 // stop all of them.  `slot` is the coarse list slot of the next step.  Run
 // by the first wave of a workgroup (threads 0..63), with every read of the
 // control blocks issued before the first write (two memory round trips, not
-// one per field and patch): lane k < np reads patch k's CFL step and error,
-// lane g < NSEG the coarse list's segment counter g; lane 0 then writes the
-// coarse control block and lane k patch k's steps.  With `region`, s_lane is
-// a speed maximum gathered besides the control block's, per lane (0 where
-// there is none).
+// one per field and patch): lane k < np reads patch k's CFL step and error
+// (NestReads, which nothing writes while the closing kernels run: they are
+// read when those start), lane g < NSEG the coarse list's segment counter g;
+// lane 0 then writes the coarse control block and lane k patch k's steps.
+// With `region`, s_lane is a speed maximum gathered besides the control
+// block's, per lane (0 where there is none).
+struct NestReads {
+    Ctrl* pc;
+    double speed, prep, t, tcf;
+    int cerr, perr;
+};
 template <typename real>
-__device__ void nest_tau_rule(const Args<real>& a, const NestArgs<real>& n, int slot, bool region, double s_lane) {
+__device__ __forceinline__ NestReads nest_reads(const Args<real>& a, const NestArgs<real>& n) {
     const int lane = threadIdx.x & 63;
-    Ctrl* const c = a.ctrl;
-    // reads
-    Ctrl* const pc = lane < n.np ? n.P[lane].ctrl : nullptr;
-    const double speed = c->speed, prep = prep_speed(c, real(0)), t = c->t;
-    const int cerr = c->err;
+    const Ctrl* const c = a.ctrl;
+    NestReads v;
+    v.pc = lane < n.np ? n.P[lane].ctrl : nullptr;
+    v.speed = c->speed;
+    v.prep = prep_speed(a.ctrl, real(0));
+    v.t = c->t;
+    v.cerr = c->err;
+    v.tcf = v.pc ? (double)n.r * v.pc->tau_cfl : __builtin_inf();
+    v.perr = v.pc ? v.pc->err : 0;
+    return v;
+}
+template <typename real>
+__device__ void nest_tau_rule(const Args<real>& a, const NestArgs<real>& n, const NestReads& v, int slot, bool region,
+                              double s_lane) {
+    const int lane = threadIdx.x & 63;
+    Ctrl *const c = a.ctrl, *const pc = v.pc;
+    const double speed = v.speed, prep = v.prep, t = v.t, tcf = v.tcf;
+    const int cerr = v.cerr, perr = v.perr;
     const int nseg = a.skip && lane < NSEG ? a.hot[hot_seg(slot, lane)] : 0;
-    const double tcf = pc ? (double)n.r * pc->tau_cfl : __builtin_inf();
-    const int perr = pc ? pc->err : 0;
     // the rule: tau_c = min(CFL step of the coarse speeds, r * CFL step of
     // every patch), unless held; min and max are exact in any order
     double S = s_lane, tp = tcf;
@@ -344,12 +384,12 @@ template <typename real>
 __global__ void k_nest_tau(Args<real> a, NestArgs<real> n, int slot, int ntap) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < ntap; i += gridDim.x * blockDim.x) n.tap[i] = real(0);
     if (blockIdx.x != 0 || threadIdx.x >= 64) return;
-    nest_tau_rule(a, n, slot, false, 0.0);
+    nest_tau_rule(a, n, nest_reads(a, n), slot, false, 0.0);
 }
 
-// The close of a two-way coarse step, one launch after k_feedback (at most
-// NEST_CLOSE_GRID workgroups of 256 threads, each striding over the work):
-// the CFL speed of the new coarse layer on the cells the feedback can change;
+// The close of a two-way coarse step, one launch after k_feedback (a row of
+// workgroups of 256 threads per patch, at most about NEST_CLOSE_GRID, each
+// striding over the work): the CFL speed of the new coarse layer on the cells the feedback can change;
 // the tiles round the covered boxes put on the coarse list of the next step
 // (list `slot`, generation of that list), so that the cells the feedback
 // changed are stepped and both buffers of the pair stay consistent; the taps
@@ -360,40 +400,31 @@ __global__ void k_nest_tau(Args<real> a, NestArgs<real> n, int slot, int ntap) {
 // issued only once the maximum has returned (so are the workgroup's
 // appends, whose results feed its list writes before the barrier), and the
 // last arrival of the last group reads and clears them.
-constexpr int NEST_CLOSE_GRID = 1024, NEST_CLOSE_CELLS = 4;
+// Bound by its chain of round trips, not by bytes: one cell per thread with
+// all its loads together, the appends by the workgroups from the last on
+// (the region's cells lie with the first of each row), and what the step
+// rule reads of the control blocks loaded at the start.
+constexpr int NEST_CLOSE_GRID = 1024;
 template <typename real>
-__global__ __launch_bounds__(256) void k_nest_close(Args<real> a, NestArgs<real> n, const int* rects, int nrect,
-                                                    int ncells, const int* force, int nforce, int ntap, int slot) {
+__global__ __launch_bounds__(256) void k_nest_close(Args<real> a, NestArgs<real> n, const int* rects,
+                                                    const int* force, int nforce, int ntap, int slot) {
     constexpr int NT = 256;
     __shared__ real red[NT / 64];
     __shared__ int s_last;
-    __shared__ int s_rect[5 * NEST_MAX_PATCHES];
-    const int tid = threadIdx.x, G = gridDim.x, grp = blockIdx.x % NSEG;
-    for (int i = tid; i < 5 * nrect; i += NT) s_rect[i] = rects[i];
-    __syncthreads();
-    // the region is mostly dry: the depths of NEST_CLOSE_CELLS cells per
-    // thread are loaded together, and only a wet cell loads its neighbours
+    const int tid = threadIdx.x, G = gridDim.x * gridDim.y, b = blockIdx.y * gridDim.x + blockIdx.x, grp = b % NSEG;
+    const int* const R = rects + 4 * blockIdx.y;   // x0, y0, x1, y1: the covered box widened by 2 cells
+    const int rx0 = R[0], ry0 = R[1], rw = R[2] - rx0, cells = rw * (R[3] - ry0);
+    NestReads reads = {};
+    if (tid < 64) reads = nest_reads(a, n);
     real vmax = real(0);
-    for (int t0 = blockIdx.x * NT * NEST_CLOSE_CELLS + tid; t0 < ncells; t0 += G * NT * NEST_CLOSE_CELLS) {
-        int gx[NEST_CLOSE_CELLS], gy[NEST_CLOSE_CELLS];
-        real hc[NEST_CLOSE_CELLS];
-#pragma unroll
-        for (int u = 0; u < NEST_CLOSE_CELLS; ++u) {
-            const int t = t0 + u * NT;
-            gx[u] = gy[u] = 0;
-            if (t < ncells) region_cell(s_rect, nrect, t, gx[u], gy[u]);
-            hc[u] = t < ncells ? a.Hi[gy[u] * a.nx + gx[u]] : real(0);
-        }
-#pragma unroll
-        for (int u = 0; u < NEST_CLOSE_CELLS; ++u)
-            if (hc[u] > a.eps) vmax = rmax(vmax, region_speed(a, gx[u], gy[u]));
-    }
+    for (int t = blockIdx.x * NT + tid; t < cells; t += gridDim.x * NT)
+        vmax = rmax(vmax, region_speed(a, rx0 + t % rw, ry0 + t / rw));
     const int gen = (int)a.ctrl->step + 1;
     // whole workgroups take each round (the append votes per wave)
-    for (int t0 = blockIdx.x * NT; t0 < nforce; t0 += G * NT)
+    for (int t0 = (G - 1 - b) * NT; t0 < nforce; t0 += G * NT)
         append_tiles(t0 + tid < nforce ? force[t0 + tid] : -1, 0, 0, gen, a.stamp, a.lists, a.hot, a.ntiles, slot,
                      grp);
-    for (int t = blockIdx.x * NT + tid; t < ntap; t += G * NT) n.tap[t] = real(0);
+    for (int t = b * NT + tid; t < ntap; t += G * NT) n.tap[t] = real(0);
     vmax = wave_max(vmax);
     if ((tid & 63) == 0) red[tid >> 6] = vmax;
     __syncthreads();
@@ -416,7 +447,7 @@ __global__ __launch_bounds__(256) void k_nest_close(Args<real> a, NestArgs<real>
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     if (tid < 64) {
         const double sg = tid < NSEG ? __longlong_as_double((long long)h64[hot_spd(tid) / 2]) : 0.0;
-        nest_tau_rule(a, n, slot, true, sg);
+        nest_tau_rule(a, n, reads, slot, true, sg);
         if (tid < NSEG) { h64[hot_cnt(tid) / 2] = 0ull; h64[hot_spd(tid) / 2] = 0ull; }
         if (tid == 0) a.hot[hot_done(NSEG)] = 0;
     }

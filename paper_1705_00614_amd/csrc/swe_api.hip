@@ -193,7 +193,7 @@ struct swe_s {
     // learned flux corrections (east and north faces, 3 planes each)
     void* corrE = nullptr;
     void* corrN = nullptr;
-    int* claims = nullptr;      // unit claims of an attached network's pre-step, one per step parity
+    int* net_units = nullptr;   // blocks an attached network runs before a step (k_net_units)
     bool corr = false;
     double corr_hmin = 0.0;
     // line taps (training labels): coarsening factor and buffers
@@ -419,7 +419,7 @@ void free_all(swe_t* s) {
     if (s->graph) (void)hipGraphExecDestroy(s->graph);
     void* ptrs[] = {s->Hb[0], s->Hb[1], s->Qxb[0], s->Qxb[1], s->Qyb[0], s->Qyb[1], s->bed, s->cf,
                     s->ctrl, s->hot, s->lists, s->stamp, s->mass, s->ledger,
-                    s->scalar, s->corrE, s->corrN, s->claims, s->tapx, s->tapy, s->sigma, s->fmask, s->fvol};
+                    s->scalar, s->corrE, s->corrN, s->net_units, s->tapx, s->tapy, s->sigma, s->fmask, s->fvol};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
@@ -1058,7 +1058,6 @@ static int ensure_corr_buffers(swe_t* s) {
     const size_t n = 3 * (size_t)s->nx * s->ny;
     HIPCHK(hipMalloc(&s->corrE, n * s->rsize));
     HIPCHK(hipMalloc(&s->corrN, n * s->rsize));
-    HIPCHK(hipMalloc((void**)&s->claims, 2 * sizeof(int)));
     HIPCHK(hipMemsetAsync(s->corrE, 0, n * s->rsize, s->stream));
     HIPCHK(hipMemsetAsync(s->corrN, 0, n * s->rsize, s->stream));
     HIPCHK(hipStreamSynchronize(s->stream));
@@ -2474,13 +2473,18 @@ hipError_t lc_pre_step_t(swe_t* s, int par) {
     const int slot = par;
     const int nmax = s->ntiles;
     c->last_n = 0;   // the stored activations are not those of one forward
-    if (So >= NET_T) {   // gather, network and scatter in one launch
-        const int ns = (So + NET_T - 1) / NET_T;
+    const int ns = (So + NET_T - 1) / NET_T;
+    if (So >= NET_T && ns <= L_::NET_MAX_SIDE) {   // gather, network and scatter in one launch
+        const int nseg = nmax < L_::NET_SEGS ? nmax : L_::NET_SEGS, cap = L_::net_seg_cap(nmax, ns);
+        hipLaunchKernelGGL((L_::k_net_units<NET_T, real>), dim3(nseg), dim3(256), 0, s->stream, a, slot, S, ns, cap,
+                           s->net_units);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
         const long long units = (long long)nmax * ns * ns;
         const int grid = (int)(units < c->net_blocks ? units : c->net_blocks);
         hipLaunchKernelGGL((L_::k_net_grid<NET_T, NET_NTH, real>), dim3(grid > 0 ? grid : 1), dim3(NET_NTH), 0,
-                           s->stream, a, slot, S, c->dscale, c->dscale + 6, (real*)s->corrE, (real*)s->corrN, c->wf,
-                           c->params, s->claims);
+                           s->stream, a, S, c->dscale, c->dscale + 6, (real*)s->corrE, (real*)s->corrN, c->wf,
+                           c->params, s->net_units, nseg, cap);
         return hipGetLastError();
     }
     const int* cnt = s->p.skip_dry ? &s->ctrl->seg_off[slot][swe::NSEG] : nullptr;
@@ -2523,8 +2527,10 @@ int swe_lc_attach(swe_lc_t* c, swe_t* s) {
     HIPCHK(hipStreamSynchronize(c->stream));
     int rc = ensure_corr_buffers(s);
     if (rc) return rc;
-    HIPCHK(hipMemsetAsync(s->claims, 0, 2 * sizeof(int), s->stream));   // outside any captured graph
-    HIPCHK(hipStreamSynchronize(s->stream));
+    const int ns = (c->So + NET_T - 1) / NET_T;
+    if (!s->net_units)
+        HIPCHK(hipMalloc((void**)&s->net_units,
+                         sizeof(int) * L_::NET_SEGS * (1 + (size_t)L_::net_seg_cap(s->ntiles, ns))));
     drop_graph(s);
     s->lc = c;
     s->pre_step = lc_pre_step;

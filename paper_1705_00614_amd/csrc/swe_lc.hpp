@@ -60,6 +60,12 @@ __device__ __forceinline__ unsigned short to_bf16(float f) {
     u += 0x7FFFu + ((u >> 16) & 1u);
     return (unsigned short)(u >> 16);
 }
+// Two values rounded to nearest even as bf16, packed (one instruction).
+__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2{lo, hi}), b16x2));
+}
 __device__ __forceinline__ float from_bf16(unsigned short h) { return __uint_as_float((unsigned)h << 16); }
 
 __device__ __forceinline__ bf16x4 load4(const unsigned short* p) {
@@ -190,12 +196,17 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const unsigned short* __restri
 // intermediate activations in LDS: the block's (T+8)^2 input window comes in
 // from HBM once and only the FP32 output goes out, so an inference costs one
 // launch instead of four and no activation round trips through HBM.  The
-// weights of every layer are staged in LDS once per workgroup; each layer is
-// the same per-pixel MFMA sequence as k_conv_fwd (taps in order, one MFMA per
-// tap and output tile, the same bias, tanh and bf16 rounding), so the output
-// equals the layer-by-layer forward.  A crop of side So is covered by
+// weights of the two middle layers are staged in LDS once per workgroup, the
+// smaller ones of the outer layers go from L2 to registers; that leaves LDS
+// for two workgroups per CU, whose MFMAs, activations and LDS reads overlap
+// (each alone takes 2 to 3 us of a block).  Each layer is the same per-pixel
+// MFMA sequence as k_conv_fwd (taps in order, one MFMA per tap and output
+// tile, the same bias, tanh and bf16 rounding), with the operands exchanged so
+// that a lane holds four channels of a pixel and stores them together; the
+// output equals the layer-by-layer forward.  A crop of side So is covered by
 // ceil(So / T) blocks per side, the last one shifted back to end at So (its
 // overlap is recomputed and written with the same values).
+constexpr int w_elems(int l) { return 9 * COUT[l] * CIN[l]; }
 template <int T>
 struct alignas(16) NetLds {
     static constexpr int P16 = 24, P32 = 40;      // pixel strides (bf16): channels + 8 against bank conflicts
@@ -206,10 +217,34 @@ struct alignas(16) NetLds {
     static constexpr int A = (T + 8) * (T + 8) * P16 > blk16(T + 4) * P32 ? (T + 8) * (T + 8) * P16
                                                                            : blk16(T + 4) * P32;
     static constexpr int B = blk16(T + 6) * P32;
-    unsigned short w[NWB];                        // bf16 weights of all layers, [tap][CO][CI]
+    unsigned short w[w_elems(1) + w_elems(2)];    // bf16 weights of layers 1 and 2, [tap][CO][CI]
     float bias[NL][32];
     unsigned short a[A];                          // input window, then layer-1 output
     unsigned short b[B];                          // layer-0 output, then layer-2 output
+};
+
+// The thread's lane, opaque to the compiler: the addresses made from it are
+// not kept in registers over a workgroup's units (they would spill).
+__device__ __forceinline__ int opaque_lane() {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    return tid & 63;
+}
+
+// A layer's weights as MFMA operands: lane m + 16 kq holds channels
+// (CI / 4) kq .. of output channel t * 16 + m, for every tap.
+template <int CI, int CO>
+struct WFrag {
+    typename AFrag<CI>::Q v[9][CO / 16];
+    __device__ __forceinline__ void load(const unsigned short* w) {
+        const int lane = opaque_lane(), m = lane & 15, kq = lane >> 4;
+#pragma unroll
+        for (int t = 0; t < CO / 16; ++t)
+#pragma unroll
+            for (int tap = 0; tap < 9; ++tap)
+                v[tap][t] = *reinterpret_cast<const typename AFrag<CI>::Q*>(w + (tap * CO + t * 16 + m) * CI +
+                                                                           (CI / 4) * kq);
+    }
 };
 
 // One layer over the LDS plane `in` (side Win, pixel stride PI) into `out`
@@ -220,108 +255,78 @@ struct NoWriter {
 };
 template <int CI, int CO, bool LAST, int Win, int NTH, class Wr>
 __device__ __forceinline__ void net_layer(const unsigned short* in, int PI, unsigned short* out, int PO,
-                                          const unsigned short* w, const float* bias, int cob, const Wr& wr) {
+                                          const WFrag<CI, CO>& W, const float* bias, int cob, const Wr& wr) {
     constexpr int NT = CO / 16, Wout = Win - 2, P = Wout * Wout, blocks = (P + 15) / 16, nw = NTH / 64;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int lane = opaque_lane(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int m = lane & 15, kq = lane >> 4;
-    if (wv >= blocks) return;
-    typename AFrag<CI>::Q B[9][NT];
+#pragma unroll 1
+    for (int blk = wv; blk < blocks; blk += nw) {
+        const int pix = blk * 16 + m, p = min(pix, P - 1);
+        const int oy = p / Wout, ox = p % Wout;
+        const unsigned short* ip = in + (oy * Win + ox) * PI + (CI / 4) * kq;
+        f32x4 acc[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+        for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int tap = 0; tap < 9; ++tap)
-            B[tap][t] = *reinterpret_cast<const typename AFrag<CI>::Q*>(w + (tap * CO + t * 16 + m) * CI + (CI / 4) * kq);
-    float bb[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) bb[t] = t * 16 + m < cob ? bias[t * 16 + m] : 0.f;
-    // two blocks per pass (blk and blk + nw): four independent MFMA chains
-    // and sixteen independent activations per lane hide more latency at two
-    // waves per SIMD; a missing second block (wave-uniform) is computed on
-    // clamped pixels and not stored
-    for (int blk = wv; blk < blocks; blk += 2 * nw) {
-        const bool two = blk + nw < blocks;
-        int oy[2], ox[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int p = min((blk + h * nw) * 16 + m, P - 1);
-            oy[h] = p / Wout;
-            ox[h] = p % Wout;
-        }
-        f32x4 acc[2][NT];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[h][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {   // block-major: block 0's activations can overlap block 1's MFMAs
-#pragma unroll
-            for (int tap = 0; tap < 9; ++tap) {
-                const unsigned short* ip = in + ((oy[h] + tap / 3) * Win + ox[h] + tap % 3) * PI + (CI / 4) * kq;
-                const typename AFrag<CI>::Q av = *reinterpret_cast<const typename AFrag<CI>::Q*>(ip);
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    if constexpr (CI == 32)
-                        acc[h][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as8(av), as8(B[tap][t]), acc[h][t], 0, 0, 0);
-                    else
-                        acc[h][t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as4(av), as4(B[tap][t]), acc[h][t], 0, 0,
-                                                                              0);
-                }
-            }
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            if (h == 1 && !two) break;
-            const int p0 = (blk + h * nw) * 16;
+        for (int tap = 0; tap < 9; ++tap) {
+            const typename AFrag<CI>::Q av =
+                *reinterpret_cast<const typename AFrag<CI>::Q*>(ip + ((tap / 3) * Win + tap % 3) * PI);
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                const int ch = t * 16 + m;
+                if constexpr (CI == 32)
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as8(W.v[tap][t]), as8(av), acc[t], 0, 0, 0);
+                else
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as4(W.v[tap][t]), as4(av), acc[t], 0, 0, 0);
+            }
+        }
+        // lane: pixel blk * 16 + m, channels t * 16 + 4 * kq + i
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int pp = p0 + 4 * kq + i;
-                    const float v = acc[h][t][i] + bb[t];
-                    if constexpr (LAST) {
-                        if (pp >= P) continue;
-                        wr(pp / Wout, pp % Wout, ch, ch < cob ? v : 0.f);
-                    } else {
-                        out[pp * PO + ch] = to_bf16(tanh_act(v));   // pp < blocks * 16: inside the padded plane
-                    }
+        for (int t = 0; t < NT; ++t) {
+            const int ch = t * 16 + 4 * kq;
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = acc[t][i] + bias[ch + i];
+            if constexpr (LAST) {
+                if (pix < P) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) wr(oy, ox, ch + i, ch + i < cob ? v[i] : 0.f);
                 }
+            } else {   // pix < blocks * 16: inside the padded plane
+                *reinterpret_cast<uint2*>(out + pix * PO + ch) =
+                    uint2{pack_bf16(tanh_act(v[0]), tanh_act(v[1])), pack_bf16(tanh_act(v[2]), tanh_act(v[3]))};
             }
         }
     }
 }
 
-// All units of n crops through the four layers.  The source `src` (a
-// read-only descriptor; what it fetches is held in three 16-byte registers
-// of the caller, plain locals so that they stay in VGPRs) provides the
-// input windows and the output writers:
-//   src.load(u, q0, q1, q2)    fetch unit u's input window,
-//   src.store(lds, q0, q1, q2) put it into the LDS plane (pixel stride 24)
-//                              and return this thread's vote to run the unit,
-//   src.source_near(c, oy0, ox0) whether the unit must run whatever the votes,
-//   src.writer(c, oy0, ox0) the last layer's writer for a block of crop c,
-//   src.begin()                once per workgroup, before anything else,
-//   src.claim(u)               (thread 0) the unit after u of this workgroup.
-// A workgroup's first unit is its index; the next unit's window is fetched
-// while the current one computes.
+// A workgroup's share (blockIdx.x, then every gridDim.x-th) of `units` blocks
+// through the four layers.  The source `src` (a read-only descriptor; what it
+// fetches is held in three 16-byte registers of the caller, plain locals so
+// that they stay in VGPRs) provides the input windows and the output writers:
+//   src.find(u, s)             the thread that knows unit u's id writes it to *s,
+//   src.load(id, q0, q1, q2)   fetch a unit's input window,
+//   src.store(lds, q0, q1, q2) put it into the LDS plane (pixel stride 24),
+//   src.writer(id)             the last layer's writer.
+// The next unit's window is fetched while the current one computes.
 template <int T, int NTH, class Src>
 __device__ __forceinline__ void net_run(const Src& src, NetLds<T>& L, const unsigned short* __restrict__ wf,
-                                        const float* __restrict__ params, int So, int n) {
+                                        const float* __restrict__ params, int units) {
     using N = NetLds<T>;
-    const int ns = (So + T - 1) / T, units = n * ns * ns;
-    src.begin();
     if ((int)blockIdx.x >= units) return;
     const int tid = threadIdx.x;
     constexpr int W0 = T + 2 * HALO;
+    __shared__ int s_unit;
+    src.find((int)blockIdx.x, &s_unit);
     // every global load of the weight staging is issued before the first
     // store (one memory round trip, not one per piece)
     {
-        constexpr int NV = NWB / 8, J = (NV + NTH - 1) / NTH;
+        constexpr int NV = (w_elems(1) + w_elems(2)) / 8, J = (NV + NTH - 1) / NTH;
+        static_assert(wb_off(2) == wb_off(1) + w_elems(1), "layers 1 and 2 follow each other");
         uint4 v[J];
 #pragma unroll
         for (int j = 0; j < J; ++j) {
             const int k = min(tid + j * NTH, NV - 1);   // clamped: the tail re-reads the last piece
-            v[j] = reinterpret_cast<const uint4*>(wf)[k];
+            v[j] = reinterpret_cast<const uint4*>(wf + wb_off(1))[k];
         }
 #pragma unroll
         for (int j = 0; j < J; ++j)
@@ -334,37 +339,41 @@ __device__ __forceinline__ void net_run(const Src& src, NetLds<T>& L, const unsi
         const int off = l == 0 ? b0 : l == 1 ? b1 : l == 2 ? b2 : b3;
         L.bias[l][ch] = ch < (l == NL - 1 ? COUT_REAL[NL - 1] : 32) ? params[off + ch] : 0.f;
     }
+    __syncthreads();
+    int id = __builtin_amdgcn_readfirstlane(s_unit);
     uint4 q0, q1, q2;
-    src.load(blockIdx.x, q0, q1, q2);
-    // the next unit's index, by iteration parity: thread 0 writes one slot
-    // before the vote's barrier while slow threads may still read the other
-    __shared__ int s_next[2];
-    for (int u = blockIdx.x, it = 0; u < units; ++it) {
-        const int c = u / (ns * ns), sub = u % (ns * ns);
-        const int oy0 = min((sub / ns) * T, So - T), ox0 = min((sub % ns) * T, So - T);
-        // a unit whose outputs no face would take is skipped (grid source:
-        // the block's cells and their face neighbours all at most the
-        // correction depth and none of them a source cell); its corrections
-        // keep older values, which the step never applies there
-        const int deep = src.store(L.a, q0, q1, q2);
-        if (tid == 0) s_next[it & 1] = src.claim(u);
-        const bool run = __syncthreads_or(deep) || src.source_near(c, oy0, ox0);
-        const int next = s_next[it & 1];
-        if (next < units) src.load(next, q0, q1, q2);
-        u = next;
-        if (!run) continue;
+    src.load(id, q0, q1, q2);
+    for (int u = blockIdx.x;; ) {
+        WFrag<16, 32> w0;
+        w0.load(wf + wb_off(0));
+        src.store(L.a, q0, q1, q2);
+        __syncthreads();
+        const int un = u + (int)gridDim.x, cur = id;
+        if (un < units) src.find(un, &s_unit);
         const NoWriter nw;
-        net_layer<16, 32, false, W0, NTH>(L.a, N::P16, L.b, N::P32, L.w + wb_off(0), L.bias[0], 32, nw);
+        net_layer<16, 32, false, W0, NTH>(L.a, N::P16, L.b, N::P32, w0, L.bias[0], 32, nw);
         __syncthreads();
-        net_layer<32, 32, false, W0 - 2, NTH>(L.b, N::P32, L.a, N::P32, L.w + wb_off(1), L.bias[1], 32, nw);
+        if (un < units) {
+            id = __builtin_amdgcn_readfirstlane(s_unit);
+            src.load(id, q0, q1, q2);
+        }
+        {
+            WFrag<32, 32> w;
+            w.load(L.w);
+            net_layer<32, 32, false, W0 - 2, NTH>(L.b, N::P32, L.a, N::P32, w, L.bias[1], 32, nw);
+            __syncthreads();
+            w.load(L.w + w_elems(1));
+            net_layer<32, 32, false, W0 - 4, NTH>(L.a, N::P32, L.b, N::P32, w, L.bias[2], 32, nw);
+        }
+        WFrag<32, 16> w3;
+        w3.load(wf + wb_off(3));
         __syncthreads();
-        net_layer<32, 32, false, W0 - 4, NTH>(L.a, N::P32, L.b, N::P32, L.w + wb_off(2), L.bias[2], 32, nw);
-        __syncthreads();
-        net_layer<32, 16, true, W0 - 6, NTH>(L.b, N::P32, nullptr, 0, L.w + wb_off(3), L.bias[3], COUT_REAL[3],
-                                             src.writer(c, oy0, ox0));
+        net_layer<32, 16, true, W0 - 6, NTH>(L.b, N::P32, nullptr, 0, w3, L.bias[3], COUT_REAL[3], src.writer(cur));
         // the next unit's input goes to L.a, last read by layer 2 (before the
         // barrier above); layer 3 reads L.b, next written after the barrier
         // that follows the next input
+        if (un >= units) break;
+        u = un;
     }
 }
 
@@ -386,9 +395,16 @@ struct CropSource {
     const unsigned short* x;
     float* y;
     int So, ns, tid;
+    __device__ __forceinline__ int origin(int u, int& oy0, int& ox0) const {
+        const int sub = u % (ns * ns);
+        oy0 = min((sub / ns) * T, So - T);
+        ox0 = min((sub % ns) * T, So - T);
+        return u / (ns * ns);
+    }
+    __device__ __forceinline__ void find(int u, int* s) const { if (tid == 0) *s = u; }
     __device__ __forceinline__ void load(int u, uint4& q0, uint4& q1, uint4&) const {
-        const int Sin = So + 2 * HALO, c = u / (ns * ns), sub = u % (ns * ns);
-        const int oy0 = min((sub / ns) * T, So - T), ox0 = min((sub % ns) * T, So - T);
+        int oy0, ox0;
+        const int Sin = So + 2 * HALO, c = origin(u, oy0, ox0);
         const unsigned short* xc = x + (size_t)c * Sin * Sin * 16;
         const int k0 = tid, k1 = tid + NTH;
         q0 = *reinterpret_cast<const uint4*>(xc + ((size_t)(oy0 + (k0 >> 1) / W0) * Sin + ox0 + (k0 >> 1) % W0) *
@@ -397,29 +413,30 @@ struct CropSource {
             q1 = *reinterpret_cast<const uint4*>(xc + ((size_t)(oy0 + (k1 >> 1) / W0) * Sin + ox0 + (k1 >> 1) % W0) *
                                                           16 + 8 * (k1 & 1));
     }
-    // returns 1: crops handed in are always run
-    __device__ __forceinline__ int store(unsigned short* a, const uint4& q0, const uint4& q1, const uint4&) const {
+    __device__ __forceinline__ void store(unsigned short* a, const uint4& q0, const uint4& q1, const uint4&) const {
         *reinterpret_cast<uint4*>(a + (tid >> 1) * NetLds<T>::P16 + 8 * (tid & 1)) = q0;
         if (tid + NTH < XV) *reinterpret_cast<uint4*>(a + ((tid + NTH) >> 1) * NetLds<T>::P16 + 8 * (tid & 1)) = q1;
-        return 1;
     }
-    __device__ __forceinline__ bool source_near(int, int, int) const { return true; }
-    __device__ __forceinline__ void begin() const {}
-    __device__ __forceinline__ int claim(int u) const { return u + (int)gridDim.x; }   // a fixed stride
-    __device__ __forceinline__ CropWriter writer(int c, int oy0, int ox0) const { return CropWriter{y, So, c, oy0, ox0}; }
+    __device__ __forceinline__ CropWriter writer(int u) const {
+        int oy0, ox0;
+        const int c = origin(u, oy0, ox0);
+        return CropWriter{y, So, c, oy0, ox0};
+    }
 };
 
 // x: crops [n][So+8][So+8][16] bf16; y: [n][So][So][16] FP32 (channels >= 6
 // zero); wf: bf16 weights of all layers; params: packed FP32 parameters (the
 // biases are read from there).  Requires So >= T; n from the device or host.
+constexpr int NET_WAVES = 4;   // waves per SIMD of the fused kernels: two workgroups of 512 threads per CU
 template <int T, int NTH>
-__global__ __launch_bounds__(NTH) void k_net_fwd(const unsigned short* __restrict__ x, float* __restrict__ y,
+__global__ __launch_bounds__(NTH, NET_WAVES) void k_net_fwd(const unsigned short* __restrict__ x, float* __restrict__ y,
                                                  const unsigned short* __restrict__ wf,
                                                  const float* __restrict__ params, int So, const int* cnt_dev,
                                                  int cnt_host) {
     __shared__ NetLds<T> L;
-    const CropSource<T, NTH> src{x, y, So, (So + T - 1) / T, (int)threadIdx.x};
-    net_run<T, NTH>(src, L, wf, params, So, crop_count(cnt_dev, cnt_host));
+    const int ns = (So + T - 1) / T;
+    const CropSource<T, NTH> src{x, y, So, ns, (int)threadIdx.x};
+    net_run<T, NTH>(src, L, wf, params, crop_count(cnt_dev, cnt_host) * ns * ns);
 }
 
 // ------------------------------------------------------------------ backward data
@@ -917,40 +934,109 @@ struct CorrWriter {
     }
 };
 
+// The blocks of a grid's active tiles whose corrections some face can take,
+// found before the network runs, so that its workgroups share just these (two
+// thirds of the blocks of a flood lie in shallow water; tested by the
+// network's workgroups, each block skipped cost one 3 to 4 us of dependent
+// round trips).  A block runs if one of its output cells or their face
+// neighbours is deeper than the correction depth -- the step corrects a face
+// only where its cells are -- or lies in the inlet rectangle (the depth that
+// decides is the one after the Lagrangian stage, which is the stored one
+// except on source cells).  A block not run keeps older corrections, which
+// the step never applies there.  Workgroup w of the grid (at most NET_SEGS)
+// takes the tiles at list positions w, w + gridDim.x, ... and writes its
+// blocks (tile * ns^2 + block) into its own segment of `units`, their number
+// into units[w]: nothing to clear, and no order but the list's.
+constexpr int NET_SEGS = 512;
+constexpr int NET_MAX_SIDE = 5;   // blocks per side whose squares fit a mask word
+__host__ __device__ constexpr int net_seg_cap(int ntiles, int ns) { return (ntiles + NET_SEGS - 1) / NET_SEGS * ns * ns; }
+template <int T, typename real>
+__global__ __launch_bounds__(256) void k_net_units(Args<real> a, int slot, int S, int ns, int cap,
+                                                   int* __restrict__ units) {
+    __shared__ unsigned s_mask[2];
+    const int tid = threadIdx.x, So = S + 1, W = So + 2, P = W * W;
+    const int n = a.skip ? a.ctrl->seg_off[slot][NSEG] : a.ntiles;
+    int* const seg = units + NET_SEGS + blockIdx.x * cap;
+    int cnt = 0;
+    if (tid < 2) s_mask[tid] = 0u;
+    __syncthreads();
+    for (int p = blockIdx.x, it = 0; p < n; p += gridDim.x, it ^= 1) {
+        const int tile = __builtin_amdgcn_readfirstlane(crop_tile(a, slot, p));
+        unsigned mask = 0u;
+        constexpr int J = 5;
+        for (int k0 = tid; k0 < P; k0 += 256 * J) {
+            real h[J];
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int k = min(k0 + 256 * j, P - 1);   // (the last pixel again)
+                h[j] = a.Hi[crop_cell(a, tile, S, HALO - 1 + k % W, HALO - 1 + k / W)];
+            }
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int k = min(k0 + 256 * j, P - 1), x = k % W, y = k / W;
+                if (!(h[j] > a.corr_hmin)) continue;
+                unsigned mx = 0u;
+                for (int q = 0; q < ns; ++q) {
+                    const int o = min(q * T, So - T);
+                    if (x >= o && x <= o + T + 1) mx |= 1u << q;
+                }
+                for (int q = 0; q < ns; ++q) {
+                    const int o = min(q * T, So - T);
+                    if (y >= o && y <= o + T + 1) mask |= mx << (q * ns);
+                }
+            }
+        }
+        mask = (unsigned)wave_or((int)mask);
+        if ((tid & 63) == 0 && mask) atomicOr(&s_mask[it], mask);
+        __syncthreads();
+        if (tid < 64) {
+            bool run = false;
+            if (tid < ns * ns) {
+                // the block's first face neighbour
+                const int x0 = (tile % a.ntx) * S - 2 + min((tid % ns) * T, So - T);
+                const int y0 = (tile / a.ntx) * S - 2 + min((tid / ns) * T, So - T);
+                const bool source = a.ni > 0 && a.nj > 0 && x0 < a.i0 + a.ni && a.i0 < x0 + T + 2 &&
+                                    y0 < a.j0 + a.nj && a.j0 < y0 + T + 2;
+                run = source || (s_mask[it] >> tid & 1u);
+            }
+            const unsigned long long m = __ballot(run);
+            if (run) seg[cnt + __popcll(m & ((1ull << tid) - 1))] = tile * ns * ns + tid;
+            cnt += __popcll(m);
+            // (this word is added to again after the next barrier only)
+            if (tid == 0) s_mask[it] = 0u;
+        }
+    }
+    if (tid == 0) units[blockIdx.x] = cnt;
+}
+
 // Source of the input windows straight from a grid's current layer (what
 // k_gather does into HBM): thread tid < (T+8)^2 fetches the five stored
 // values of one window pixel and turns them into its features at the store.
+// Thread w holds the range [lo, hi) of units in segment w of k_net_units.
 template <int T, int NTH, typename real>
 struct GridSource {
     static constexpr int W0 = T + 2 * HALO;
     static_assert(W0 * W0 <= NTH, "one window pixel per thread");
     static_assert(5 * sizeof(real) <= 48, "five stored values in three 16-byte registers");
     const Args<real>* a;
-    int slot, S, So, ns, tid;
+    int S, So, ns, tid;
     const float* iscale;
     real* corrE;
     real* corrN;
     const float* oscale;
-    // units after the first are claimed from claims[slot] (workgroups that
-    // run blocks take fewer); the pre-step of the next step, which uses the
-    // other slot, finds that one cleared by this launch (both are zero when
-    // the network is attached)
-    int* claims;
-    __device__ __forceinline__ void begin() const {
-        if (blockIdx.x == 0 && tid == 0) claims[slot ^ 1] = 0;
-    }
-    __device__ __forceinline__ int claim(int) const { return atomicAdd(&claims[slot], 1) + (int)gridDim.x; }
-    __device__ __forceinline__ int origin(int u, int& tile, int& oy0, int& ox0) const {
-        const int c = u / (ns * ns), sub = u % (ns * ns);
+    const int* seg;
+    int lo, hi;
+    __device__ __forceinline__ void find(int u, int* s) const { if (u >= lo && u < hi) *s = seg[u - lo]; }
+    __device__ __forceinline__ int origin(int id, int& oy0, int& ox0) const {
+        const int sub = id % (ns * ns);
         oy0 = min((sub / ns) * T, So - T);
         ox0 = min((sub % ns) * T, So - T);
-        tile = crop_tile(*a, slot, c);
-        return c;
+        return id / (ns * ns);
     }
-    __device__ __forceinline__ void load(int u, uint4& q0, uint4& q1, uint4& q2) const {
+    __device__ __forceinline__ void load(int id, uint4& q0, uint4& q1, uint4& q2) const {
         if (tid >= W0 * W0) return;
-        int tile, oy0, ox0;
-        origin(u, tile, oy0, ox0);
+        int oy0, ox0;
+        const int tile = origin(id, oy0, ox0);
         const int gi = crop_cell(*a, tile, S, ox0 + tid % W0, oy0 + tid / W0);
         real v[6] = {a->Hi[gi], a->Qxi[gi], a->Qyi[gi], a->bed[gi], a->cf[gi], real(0)};
         uint4 q[3];
@@ -958,55 +1044,65 @@ struct GridSource {
         __builtin_memcpy(q, v, sizeof v);
         q0 = q[0]; q1 = q[1]; q2 = q[2];
     }
-    // returns 1 if this window pixel is one of the block's output cells or
-    // their face neighbours (pixels HALO-1 .. HALO+T of each axis) and deeper
-    // than the correction depth: the step corrects a face only where its
-    // cells are (the stored depth is the depth after the Lagrangian stage
-    // except on source cells, which source_near covers)
-    __device__ __forceinline__ int store(unsigned short* lds, const uint4& q0, const uint4& q1, const uint4& q2) const {
-        if (tid >= W0 * W0) return 0;
+    __device__ __forceinline__ void store(unsigned short* lds, const uint4& q0, const uint4& q1, const uint4& q2) const {
+        if (tid >= W0 * W0) return;
         const uint4 q[3] = {q0, q1, q2};
         real v[6];
         __builtin_memcpy(v, q, sizeof v);
         unsigned short f[6];
         features(*a, CellIn<real>{v[0], v[1], v[2], v[3], v[4]}, iscale, f);
-        const uint4 lo = {f[0] | ((unsigned)f[1] << 16), f[2] | ((unsigned)f[3] << 16), f[4] | ((unsigned)f[5] << 16), 0u};
-        *reinterpret_cast<uint4*>(lds + tid * NetLds<T>::P16) = lo;
+        const uint4 lo4 = {f[0] | ((unsigned)f[1] << 16), f[2] | ((unsigned)f[3] << 16), f[4] | ((unsigned)f[5] << 16), 0u};
+        *reinterpret_cast<uint4*>(lds + tid * NetLds<T>::P16) = lo4;
         *reinterpret_cast<uint4*>(lds + tid * NetLds<T>::P16 + 8) = uint4{0u, 0u, 0u, 0u};
-        const int px = tid % W0, py = tid / W0;
-        const bool near = px >= HALO - 1 && px <= HALO + T && py >= HALO - 1 && py <= HALO + T;
-        return near && v[0] > a->corr_hmin;
     }
-    // whether the block's cells or their face neighbours meet the inlet
-    // rectangle (their depth after the Lagrangian stage includes the source)
-    __device__ __forceinline__ bool source_near(int c, int oy0, int ox0) const {
-        if (a->ni <= 0 || a->nj <= 0) return false;
-        const int tile = crop_tile(*a, slot, c);
-        const int x0 = (tile % a->ntx) * S - 2 + ox0, y0 = (tile / a->ntx) * S - 2 + oy0;   // first neighbour
-        return x0 < a->i0 + a->ni && a->i0 < x0 + T + 2 && y0 < a->j0 + a->nj && a->j0 < y0 + T + 2;
-    }
-    __device__ __forceinline__ CorrWriter<real> writer(int c, int oy0, int ox0) const {
-        const int tile = crop_tile(*a, slot, c);
+    __device__ __forceinline__ CorrWriter<real> writer(int id) const {
+        int oy0, ox0;
+        const int tile = origin(id, oy0, ox0);
         return CorrWriter<real>{corrE, corrN, oscale, a->nx, a->ny, (tile % a->ntx) * S - 1 + ox0,
                                 (tile / a->ntx) * S - 1 + oy0};
     }
 };
 
-// Before a step of a grid with an attached network: crops of the active
-// tiles of list `slot`, the four layers and the corrections of those tiles
-// in one launch (the work of k_gather, the four forward layers and
-// k_scatter, with the same arithmetic per value).  Requires S + 1 >= T.
+// Before a step of a grid with an attached network, after k_net_units: crops
+// of the blocks it lists, the four layers and the corrections in one launch
+// (the work of k_gather, the four forward layers and k_scatter, with the same
+// arithmetic per value).  Requires S + 1 >= T and nseg <= NTH segments.
+// 1024 x 1024 cells with 85 active tiles (303 of 765 blocks to run): one
+// workgroup per CU that tested its blocks itself and claimed further ones took
+// 37.6 us a step; k_net_units 5.4 and this 19.3 us, nearly all of it one
+// block's chain (list, window, four layers), as 303 blocks start at once.
 template <int T, int NTH, typename real>
-__global__ __launch_bounds__(NTH) void k_net_grid(Args<real> a, int slot, int S, const float* __restrict__ iscale,
-                                                  const float* __restrict__ oscale, real* __restrict__ corrE,
-                                                  real* __restrict__ corrN, const unsigned short* __restrict__ wf,
-                                                  const float* __restrict__ params, int* __restrict__ claims) {
+__global__ __launch_bounds__(NTH, NET_WAVES) void k_net_grid(Args<real> a, int S, const float* __restrict__ iscale,
+                                                             const float* __restrict__ oscale, real* __restrict__ corrE,
+                                                             real* __restrict__ corrN,
+                                                             const unsigned short* __restrict__ wf,
+                                                             const float* __restrict__ params,
+                                                             const int* __restrict__ units, int nseg, int cap) {
+    static_assert(NET_SEGS <= NTH, "a segment per thread");
     __shared__ NetLds<T> L;
+    __shared__ int s_wave[NTH / 64];
+    // units before segment tid, and in all
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int mine = tid < nseg ? units[tid] : 0;
+    int hi = mine, before = 0, total = 0;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(hi, o, 64);
+        if (lane >= o) hi += v;
+    }
+    if (lane == 63) s_wave[wv] = hi;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NTH / 64; ++q) {
+        const int v = s_wave[q];
+        if (q < wv) before += v;
+        total += v;
+    }
+    hi += before;
     const int So = S + 1;
-    const GridSource<T, NTH, real> src{&a, slot, S, So, (So + T - 1) / T, (int)threadIdx.x, iscale, corrE, corrN,
-                                       oscale, claims};
-    const int n = a.skip ? a.ctrl->seg_off[slot][NSEG] : a.ntiles;
-    net_run<T, NTH>(src, L, wf, params, So, n);
+    const GridSource<T, NTH, real> src{&a,   S,     So,    (So + T - 1) / T, tid, iscale, corrE, corrN,
+                                       oscale, units + NET_SEGS + tid * cap, hi - mine, hi};
+    net_run<T, NTH>(src, L, wf, params, __builtin_amdgcn_readfirstlane(total));
 }
 
 // Training labels of n crops (coarse tiles tiles[p], (S+1)^2 cells from the

@@ -371,6 +371,30 @@ def test_reattached_network_starts_afresh():
             net.detach(A)
 
 
+@pytest.mark.parametrize("nx,ny,prec,skip", [(744, 736, 32, True), (40, 33, 32, False), (372, 368, 64, False)])
+def test_blocks_listed_for_the_network(nx, ny, prec, skip):
+    """The blocks the network runs are listed in one segment per workgroup of
+    the listing: segments of two tiles (552 tiles, every one wet, ragged at
+    the edge), and fewer tiles than segments, with and without the tile list.
+    Bitwise equal to a twin given host-placed corrections."""
+    from paper_1705_00614_amd import scenarios as S
+    sc = S.random_state(nx, ny, seed=17, wet_frac=0.9, precision=prec)
+    W, b = LN.init_params(31)
+    out_scale = OUT_SCALE * 0.1
+    A, B = swe.Solver(sc, skip_dry=skip), swe.Solver(sc, skip_dry=skip)
+    net = swe.Net(A.work()["tile"][0], A.work()["ntiles"], IN_SCALE, out_scale)
+    net.set_params(swe.lc_pack(W, b))
+    for g in (A, B):
+        g.set_correction_depth(0.05)
+    net.attach(A)
+    for k in range(3):
+        _host_corrections(net, B, out_scale)
+        A.run(1)
+        B.run(1)
+        for fa, fb in zip(A.state(), B.state()):
+            assert np.array_equal(fa, fb), k
+
+
 # ---------------------------------------------------------------- training data
 
 def test_line_taps_match_oracle_faces():

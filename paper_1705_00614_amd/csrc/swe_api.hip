@@ -2772,8 +2772,8 @@ int swe_lc_fit(swe_lc_t* c, int iters, int batch, double lr, unsigned long long 
         HIPCHK(hipMemcpyAsync(c->idx, pick.data(), sizeof(int) * (size_t)nb * m, hipMemcpyHostToDevice, c->stream));
         int rc = 0;
         for (int it = 0; it < m && !rc; ++it) {
-            hipLaunchKernelGGL(L_::k_batch_copy, dim3(2048), dim3(256), 0, c->stream, c->idx + (size_t)it * nb, nb, So,
-                               c->dX, c->dY, c->dM, c->act[0], c->y, c->mask);
+            hipLaunchKernelGGL(L_::k_batch_copy, dim3(nb * L_::BATCH_WG), dim3(256), 0, c->stream,
+                               c->idx + (size_t)it * nb, So, c->dX, c->dY, c->dM, c->act[0], c->y, c->mask);
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) { set_hip_err("swe_lc_fit", e); rc = SWE_EHIP; }
             else rc = lc_opt_step(c, nb, cnt[it], lr, c->loss + it);

@@ -85,12 +85,13 @@ __device__ __forceinline__ int crop_count(const int* dev, int host) { return dev
 // y = act(conv3x3_valid(x) + b); x [n][Sin][Sin][CI] bf16, y [n][Sout][Sout][CO]
 // (bf16 with tanh, or FP32 linear for the last layer).
 //
-// A wave keeps its B operands (the layer's weights for every tap and output
-// tile) in registers for all its items, and loads the A operands of its next
-// 16-pixel item while the MFMAs of the current one run.  With 32 input
-// channels a tap is one 16x16x32 bf16 MFMA (lane group kq holds channels
-// 8kq..8kq+7 of A and B, one 16-byte load each); with 16 input channels a
-// tap is one 16x16x16 MFMA.
+// A wave keeps the layer's weights for every tap and output tile in registers
+// for all its items, and loads the pixels of its next 16-pixel item while the
+// MFMAs of the current one run.  With 32 input channels a tap is one 16x16x32
+// bf16 MFMA (lane group kq holds channels 8kq..8kq+7 of both operands, one
+// 16-byte load each); with 16 input channels a tap is one 16x16x16 MFMA.  The
+// weights are the first operand, so that a lane ends up with four consecutive
+// channels of one pixel.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ bf16x8 as8(const uint4& q) { return __builtin_bit_cast(bf16x8, q); }
@@ -143,8 +144,8 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const unsigned short* __restri
     const int total = n * blocks, stride = gridDim.x * 4;
     int item = blockIdx.x * 4 + wv;
     if (item >= total) return;
-    // B operands: lane (m, kq) holds w[tap][t*16 + m][k] for its k of each
-    // chunk, as A holds x[pixel m][k]
+    // weights: lane (m, kq) holds w[tap][t*16 + m][k] for its k of each chunk,
+    // as the pixels' operand holds x[pixel m][k]
     typename AFrag<CI>::Q B[9][NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
@@ -152,9 +153,11 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const unsigned short* __restri
         for (int tap = 0; tap < 9; ++tap)
             B[tap][t] = *reinterpret_cast<const typename AFrag<CI>::Q*>(wf + (tap * CO + t * 16 + m) * CI +
                                                                          (CI / 4) * kq);
-    float bb[NT];
+    float bb[NT][4];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) bb[t] = t * 16 + m < cob ? bias[t * 16 + m] : 0.f;
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bb[t][i] = t * 16 + 4 * kq + i < cob ? bias[t * 16 + 4 * kq + i] : 0.f;
     AFrag<CI> cur, nxt;
     load_a<CI>(cur, x, item, blocks, Sin, Sout, P, m, kq);
     for (; item < total; item += stride) {
@@ -168,23 +171,27 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const unsigned short* __restri
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 if constexpr (CI == 32)
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as8(cur.v[tap]), as8(B[tap][t]), acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as8(B[tap][t]), as8(cur.v[tap]), acc[t], 0, 0, 0);
                 else
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as4(cur.v[tap]), as4(B[tap][t]), acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as4(B[tap][t]), as4(cur.v[tap]), acc[t], 0, 0, 0);
             }
-        // lane holds rows (pixels) p0 + 4*kq + i, column (channel) t*16 + m
-        const int c = item / blocks, p0 = (item % blocks) * 16;
+        // lane: pixel p0 + m, channels t * 16 + 4 * kq + i, stored together
+        const int c = item / blocks, pp = (item % blocks) * 16 + m;
+        if (pp < P) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int ch = t * 16 + m;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int pp = p0 + 4 * kq + i;
-                if (pp >= P) continue;
-                const float v = acc[t][i] + bb[t];
+            for (int t = 0; t < NT; ++t) {
+                const int ch = t * 16 + 4 * kq;
                 const size_t o = ((size_t)c * P + pp) * CO + ch;
-                if constexpr (LAST) static_cast<float*>(y)[o] = ch < cob ? v : 0.f;
-                else static_cast<unsigned short*>(y)[o] = to_bf16(tanh_act(v));
+                float v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = acc[t][i] + bb[t][i];
+                if constexpr (LAST)
+                    *reinterpret_cast<float4*>(static_cast<float*>(y) + o) =
+                        float4{ch < cob ? v[0] : 0.f, ch + 1 < cob ? v[1] : 0.f, ch + 2 < cob ? v[2] : 0.f,
+                               ch + 3 < cob ? v[3] : 0.f};
+                else
+                    *reinterpret_cast<uint2*>(static_cast<unsigned short*>(y) + o) =
+                        uint2{pack_bf16(tanh_act(v[0]), tanh_act(v[1])), pack_bf16(tanh_act(v[2]), tanh_act(v[3]))};
             }
         }
         cur = nxt;
@@ -450,14 +457,14 @@ __global__ __launch_bounds__(NTH, NET_WAVES) void k_net_fwd(const unsigned short
 template <int CI, int CO>
 struct BwdItem {
     uint2 g[9][CO / 16];
-    unsigned short a[CI / 16][4];
+    uint2 a[CI / 16];
     int in;      // taps inside the output plane, one bit each
 };
 template <int CI, int CO>
 __device__ __forceinline__ void load_bwd(BwdItem<CI, CO>& f, const unsigned short* __restrict__ g,
                                          const unsigned short* __restrict__ a_in, int item, int blocks, int Sin, int P,
                                          int m, int kq) {
-    const int Sout = Sin - 2, c = item / blocks, p0 = (item % blocks) * 16, p = min(p0 + m, P - 1);
+    const int Sout = Sin - 2, c = item / blocks, p = min((item % blocks) * 16 + m, P - 1);
     const int qy = p / Sin, qx = p % Sin;
     const unsigned short* gc = g + (size_t)c * Sout * Sout * CO + 4 * kq;
     f.in = 0;
@@ -472,9 +479,7 @@ __device__ __forceinline__ void load_bwd(BwdItem<CI, CO>& f, const unsigned shor
     }
 #pragma unroll
     for (int t = 0; t < CI / 16; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            f.a[t][i] = a_in[((size_t)c * P + min(p0 + 4 * kq + i, P - 1)) * CI + t * 16 + m];
+        f.a[t] = *reinterpret_cast<const uint2*>(a_in + ((size_t)c * P + p) * CI + t * 16 + 4 * kq);
 }
 
 template <int CI, int CO>
@@ -511,18 +516,24 @@ __global__ __launch_bounds__(256) void k_conv_bwd_data(const unsigned short* __r
                 if (!((cur.in >> tap) & 1)) a = bf16x4{0, 0, 0, 0};
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, as4(B[tap][h][t]), acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(as4(B[tap][h][t]), a, acc[t], 0, 0, 0);
             }
-        const int c = item / blocks, p0 = (item % blocks) * 16;
+        // lane: pixel p0 + m, channels t * 16 + 4 * kq + i
+        const int c = item / blocks, pp = (item % blocks) * 16 + m;
+        if (pp < P) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
+            for (int t = 0; t < NT; ++t) {
+                const bf16x4 a4 = as4(cur.a[t]);
+                float v[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int pp = p0 + 4 * kq + i;
-                if (pp >= P) continue;
-                const float a = from_bf16(cur.a[t][i]);
-                g_in[((size_t)c * P + pp) * CI + t * 16 + m] = to_bf16(acc[t][i] * (1.f - a * a));
+                for (int i = 0; i < 4; ++i) {
+                    const float a = from_bf16((unsigned short)a4[i]);
+                    v[i] = acc[t][i] * (1.f - a * a);
+                }
+                *reinterpret_cast<uint2*>(g_in + ((size_t)c * P + pp) * CI + t * 16 + 4 * kq) =
+                    uint2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
             }
+        }
         cur = nxt;
     }
 }
@@ -809,16 +820,32 @@ __global__ void k_loss(const float* __restrict__ out, const float* __restrict__ 
                        unsigned short* __restrict__ g, int npix, float inv_count, double* __restrict__ part) {
     __shared__ double red[4];
     double s = 0.0;
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < npix * 16; k += gridDim.x * blockDim.x) {
-        const int p = k / 16, ch = k % 16;
-        float gv = 0.f;
-        if (ch < 6) {
-            const float d = out[k] - y[p * 6 + ch];
-            const float mk = mask[p * 6 + ch];
-            gv = mk * d * inv_count;
-            s += 0.5 * (double)(mk * d * d) * (double)inv_count;
+    // (the stride is a multiple of 16: a thread keeps its channel); the loads
+    // of J elements go together, their sum in order
+    constexpr int J = 8;
+    const int n = npix * 16, nt = gridDim.x * blockDim.x, ch = threadIdx.x % 16;
+    for (int k0 = blockIdx.x * blockDim.x + threadIdx.x; k0 < n; k0 += J * nt) {
+        float o[J], t[J], w[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int k = k0 + j * nt;
+            const bool in = ch < 6 && k < n;
+            o[j] = in ? out[k] : 0.f;
+            t[j] = in ? y[k / 16 * 6 + ch] : 0.f;
+            w[j] = in ? mask[k / 16 * 6 + ch] : 0.f;
         }
-        g[k] = to_bf16(gv);
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int k = k0 + j * nt;
+            if (k >= n) break;
+            float gv = 0.f;
+            if (ch < 6) {
+                const float d = o[j] - t[j], mk = w[j];
+                gv = mk * d * inv_count;
+                s += 0.5 * (double)(mk * d * d) * (double)inv_count;
+            }
+            g[k] = to_bf16(gv);
+        }
     }
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
@@ -1158,24 +1185,24 @@ __global__ void k_labels(const int* __restrict__ tiles, int n, int S, int ntx, i
 }
 
 // Minibatch: crops idx[b] of the data set into the network's input, label
-// and mask buffers.
-__global__ void k_batch_copy(const int* __restrict__ idx, int nb, int So, const unsigned short* __restrict__ X,
-                             const float* __restrict__ Y, const float* __restrict__ M, unsigned short* __restrict__ x,
-                             float* __restrict__ y, float* __restrict__ m) {
-    const int Sin = So + 2 * HALO;
-    const size_t px = (size_t)Sin * Sin * 16, py = (size_t)So * So * 6;
-    const size_t total = (size_t)nb * (px + 2 * py);
-    for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < total; k += (size_t)gridDim.x * blockDim.x) {
-        if (k < (size_t)nb * px) {
-            const size_t b = k / px, o = k % px;
-            x[k] = X[(size_t)idx[b] * px + o];
-        } else if (k < (size_t)nb * (px + py)) {
-            const size_t kk = k - (size_t)nb * px, b = kk / py, o = kk % py;
-            y[kk] = Y[(size_t)idx[b] * py + o];
-        } else {
-            const size_t kk = k - (size_t)nb * (px + py), b = kk / py, o = kk % py;
-            m[kk] = M[(size_t)idx[b] * py + o];
-        }
+// and mask buffers, BATCH_WG workgroups per crop; in pieces of 16 bytes (32 per
+// input pixel) and 8 bytes (24 per output pixel), which every crop's start
+// and size are multiples of.
+constexpr int BATCH_WG = 8;
+__global__ __launch_bounds__(256) void k_batch_copy(const int* __restrict__ idx, int So,
+                                                    const unsigned short* __restrict__ X, const float* __restrict__ Y,
+                                                    const float* __restrict__ M, unsigned short* __restrict__ x,
+                                                    float* __restrict__ y, float* __restrict__ m) {
+    const int Sin = So + 2 * HALO, b = blockIdx.x / BATCH_WG, t = blockIdx.x % BATCH_WG * 256 + threadIdx.x;
+    const size_t src = idx[b];
+    const int nx = Sin * Sin * 2, ny = So * So * 3;
+    const uint4* const Xb = reinterpret_cast<const uint4*>(X) + src * nx;
+    const uint2 *const Yb = reinterpret_cast<const uint2*>(Y) + src * ny, *const Mb = reinterpret_cast<const uint2*>(M) + src * ny;
+    uint4* const xb = reinterpret_cast<uint4*>(x) + (size_t)b * nx;
+    uint2 *const yb = reinterpret_cast<uint2*>(y) + (size_t)b * ny, *const mb = reinterpret_cast<uint2*>(m) + (size_t)b * ny;
+    for (int k = t; k < nx || k < ny; k += BATCH_WG * 256) {
+        if (k < nx) xb[k] = Xb[k];
+        if (k < ny) { yb[k] = Yb[k]; mb[k] = Mb[k]; }
     }
 }
 

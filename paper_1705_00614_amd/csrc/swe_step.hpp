@@ -1609,10 +1609,10 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> 
 }
 
 // Arguments of scenario (or grid) `sid` for a workgroup: `sid` is the same in
-// every lane and the array does not change while kernels run, so the fields come through the
-// scalar cache into scalar registers.  Read through a plain reference they
-// were fetched by vector loads inside every stage, each a memory round trip
-// after the tile's stores.
+// every lane and the array does not change while kernels run, so the fields
+// come through the scalar cache into scalar registers.  Read through a plain
+// reference they were fetched by vector loads inside every stage, each a
+// memory round trip after the tile's stores.
 template <typename real>
 __device__ __forceinline__ Args<real> scalar_args(const Args<real>* scen, int sid) {
     typedef const __attribute__((address_space(4))) unsigned* cptr;

@@ -2324,7 +2324,7 @@ swe_lc_t* swe_lc_create(int tile, int max_crops, const double* in_scale, const d
     LK(hipMalloc((void**)&c->y, sizeof(float) * (size_t)max_crops * c->So * c->So * 6));
     LK(hipMalloc((void**)&c->mask, sizeof(float) * (size_t)max_crops * c->So * c->So * 6));
     LK(hipMalloc((void**)&c->part, sizeof(float) * L_::part_off(L_::NL)));
-    c->loss_blocks = 256;
+    c->loss_blocks = 1024;
     LK(hipMalloc((void**)&c->loss_part, sizeof(double) * c->loss_blocks));
     LK(hipMalloc((void**)&c->loss, sizeof(double) * LC_RING));
     LK(hipMemsetAsync(c->params, 0, sizeof(float) * L_::NPARAM, c->stream));

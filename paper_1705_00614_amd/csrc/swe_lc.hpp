@@ -825,13 +825,13 @@ __global__ __launch_bounds__(OPT_NTH) void k_opt(OptArgs a) {
 // ------------------------------------------------------------------ loss
 // g = bf16(mask (out - y) / count) for the 6 real channels (zero padding to
 // 16); per-block loss partials 1/2 sum mask (out - y)^2 / count.
-__global__ void k_loss(const float* __restrict__ out, const float* __restrict__ y, const float* __restrict__ mask,
+__global__ __launch_bounds__(256) void k_loss(const float* __restrict__ out, const float* __restrict__ y, const float* __restrict__ mask,
                        unsigned short* __restrict__ g, int npix, float inv_count, double* __restrict__ part) {
     __shared__ double red[4];
     double s = 0.0;
     // (the stride is a multiple of 16: a thread keeps its channel); the loads
     // of J elements go together, their sum in order
-    constexpr int J = 8;
+    constexpr int J = 5;
     const int n = npix * 16, nt = gridDim.x * blockDim.x, ch = threadIdx.x % 16;
     for (int k0 = blockIdx.x * blockDim.x + threadIdx.x; k0 < n; k0 += J * nt) {
         float o[J], t[J], w[J];

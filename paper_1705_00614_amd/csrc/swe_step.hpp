@@ -21,16 +21,27 @@
 //           wet bits, FP64 volume and clamp partials
 //
 // Work layout: in P1, P2 and FX a thread owns a run of cells along x, in FY
-// a run along y (2-4 cells, per stage and precision), so neighbour values and
+// a run along y (1-4 cells, per stage and precision), so neighbour values and
 // limited slopes are loaded and computed once per run instead of once per
-// use.  Lanes of a wave stride
-// LDS rows (row pitch odd) or columns, which keeps LDS accesses free of bank
-// conflicts.  Wet/dry decisions are selects, not branches.
+// use; in FX and FY a run's neighbour side comes from the next lane.  Lanes of
+// a wave stride LDS rows (row pitch odd) or columns.  Wet/dry decisions are
+// selects, not branches.
 //
 // The tile list of the next step is built by the workgroups themselves
 // (atomic de-duplicated append), and the last workgroup to finish turns the
 // maximum speed into the next time step and the next hydrograph volume in
 // FP64.  A step is therefore exactly one kernel launch with no host work.
+//
+// What bounds a step: with several tiles per workgroup slot, VALU issue (82 %
+// busy on the 2048^2 lake; the LDS 40 %); with at most one, a tile's chain of
+// stages and barriers (about 17 us of the 19); the memory floor, 20 us for that
+// lake's 2900 tiles, is far below.  FP32, before and after the reconstruction
+// once per cell, DPP reductions, band-wise ghosts, early loads and 24-bit
+// index arithmetic: 2048^2 lake 107.3 -> 87.5 us, 4096^2 flood with about 500
+// tiles 35.6 -> 28.9 us, 4096^2 fully wet 637 -> 500 us.  1024 threads per 32 x 32
+// tile (one workgroup per CU, whose barriers then idle it) took 118.6 and 37.4
+// us on the first two; an LDS pitch of 45, 93.2 us on the lake; the next tile's
+// fields prefetched into registers, 94.9 us; P1 by runs of 4, 88.5 us.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -1628,9 +1639,10 @@ __device__ __forceinline__ Args<real> scalar_args(const Args<real>* scen, int si
 // or its patches), G workgroups each: one launch instead of one per grid on
 // streams forked and joined around it, where each fork and join cost 5 to 10
 // us between 20 us steps (512 x 512 cells with 4 patches of 394 x 394, FP32:
-// 195 -> 126 us per coarse step of 4 substeps).  Groups of NSEG workgroups go to the grids in turn,
-// so that a grid's workgroup b runs on XCD b % NSEG as in a launch of its own
-// and the first workgroups of every grid -- those with tiles -- start first.
+// 195 -> 126 us per coarse step of 4 substeps).  Groups of NSEG workgroups go
+// to the grids in turn, so that a grid's workgroup b runs on XCD b % NSEG as
+// in a launch of its own and the first workgroups of every grid -- those with
+// tiles -- start first.
 template <typename real, int TX, int TY, int NT, int LIM>
 __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step_grids(const Args<real>* grids, int n, int G) {
     const int q = blockIdx.x / NSEG, grid = q % n;
@@ -1643,7 +1655,8 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step_grids(const
 // partials.  Needs only a 1-cell ring.  Workgroups stride over the tiles (at
 // most PREPARE_GRID of them, a multiple of NSEG) and send one speed maximum
 // each: the maxima go to one address, where atomics serialise at 11 ns, so
-// one per tile was most of the 143 us on 16 384 tiles.
+// one per tile was most of the 143 us on 16 384 FP32 tiles; so 105 us, 3.2 TB/s
+// of the five fields, the square roots and divisions of the speed beside them.
 constexpr int PREPARE_GRID = 1024;
 template <typename real, int TX, int TY, int NT>
 __global__ __launch_bounds__(NT) void k_prepare(Args<real> a) {
@@ -1826,6 +1839,9 @@ struct BatchArgs {
     int slot;                 // list slot read by this step
 };
 
+// Bound as the step of a grid with the same number of tiles.  20 floods with
+// 1340 tiles together, FP32: 79 -> 52.8 us, the scenarios' arguments through
+// scalar loads and no fence per workgroup besides what the tile gained.
 template <typename real, int TX, int TY, int NT, int LIM>
 __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_batch_step(BatchArgs<real> ba) {
     constexpr int NWAVE = NT / 64;

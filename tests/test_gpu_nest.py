@@ -234,6 +234,20 @@ def test_grids_share_a_launch(n, boxes, skip):
     _compare(G, O, 64, label="n=%d" % n)
 
 
+@pytest.mark.parametrize("r", [3, 5])
+def test_fine_blocks_of_odd_refinement(r):
+    """The fine cells of a covered cell and the taps of a face are summed in
+    batches (16 cells, 4 taps): 9 and 25 cells, 3 and 5 taps leave ragged
+    ones.  FP64 against the oracle, the module's bars."""
+    sc = S.random_state(30, 26, seed=37, wet_frac=0.7, precision=64)
+    nest = S.nest(sc, [(7, 6, 9, 7)], r=r, detail=0.3)
+    O = OracleNest(nest["coarse"], nest["patches"], r=r)
+    G = swe.Nest(nest)
+    G.run(9)
+    O.run(9)
+    _compare(G, O, 64, label="r=%d" % r)
+
+
 def test_full_size_nest_first_coarse_steps_match_oracle():
     """The nested-grid benchmark workload at its full size (2048^2 coarse
     grid at 50 m with two 2048^2 patches at 12.5 m, dry-tile skipping) for

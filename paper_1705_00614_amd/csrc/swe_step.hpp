@@ -428,13 +428,17 @@ __device__ __forceinline__ real cfl_speed(const Args<real>& a, real H, real cf, 
     return rmax(us, rmax(upx, upy));
 }
 
-// Raise the layer's maximum speed (v >= 0); returns its bits from before.
-__device__ __forceinline__ unsigned long long atomic_max_prep(Ctrl* c, float v) {
-    return atomicMax((unsigned int*)&c->prep_speed, __float_as_uint(v));
+// Raise the layer's maximum speed (v >= 0).
+__device__ __forceinline__ void atomic_max_prep(Ctrl* c, float v) {
+    atomicMax((unsigned int*)&c->prep_speed, __float_as_uint(v));
 }
-__device__ __forceinline__ unsigned long long atomic_max_prep(Ctrl* c, double v) {
-    return atomicMax(&c->prep_speed, (unsigned long long)__double_as_longlong(v));
+__device__ __forceinline__ void atomic_max_prep(Ctrl* c, double v) {
+    atomicMax(&c->prep_speed, (unsigned long long)__double_as_longlong(v));
 }
+// Wait until every memory operation of this wave has been performed, atomics
+// without a result among them (flat ones count on both counters); nothing is
+// moved across.
+__device__ __forceinline__ void drain_memory() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
 __device__ __forceinline__ double prep_speed(const Ctrl* c, float) {
     return (double)__uint_as_float(*(const unsigned int*)&c->prep_speed);
 }
@@ -1860,7 +1864,6 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_batch_step(Batch
     const int count = off[NSEG];
     const int gen = (int)lc->step + 2;
     long long ncells = 0;
-    unsigned long long ack = 0, pend = 0;   // thread 0: results of the speed and error atomics
 
     for (int p = blockIdx.x; p < count; p += G) {
         const int e = __builtin_amdgcn_readfirstlane(list_entry(off, ba.lists, ba.list_cap, ba.slot, p));
@@ -1902,11 +1905,9 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_batch_step(Batch
             }
             a.mass[tile] = ms;
             a.ledger[tile] = led + ls * a.h_d * a.h_d;
-            // their results are waited for a tile later (or below)
-            ack |= pend;
-            pend = 0;
-            if (vm > real(0)) pend = atomic_max_prep(c, vm);
-            if (bb & 128) ack |= (unsigned long long)(unsigned)atomicCAS(&c->err, 0, -4);
+            // (both are waited for before the arrival below)
+            if (vm > real(0)) atomic_max_prep(c, vm);
+            if (bb & 128) atomicCAS(&c->err, 0, -4);
         }
         if (a.skip && wv == NWAVE - 1) {
             int bb = 0;
@@ -1925,23 +1926,21 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_batch_step(Batch
     }
 
     // ---- completion, as in k_step: every contribution is an atomic that has
-    // returned before the arrival is counted, so no workgroup writes back its
-    // L2; the last workgroup finalises every scenario
-    if (tid == 0) ack |= pend;
-    // the acknowledgements (never all ones: a speed is no NaN of that bit
-    // pattern) are only there to be waited for
-    const bool sent = ack != ~0ull;
+    // been performed before the arrival is counted, so no workgroup writes back
+    // its L2; the last workgroup finalises every scenario.  The barrier has the
+    // last wave's appends performed (each uses its atomics' results); thread 0
+    // issues the speeds and errors and drains them itself -- their results are
+    // not used, so nothing else would wait for them.
     __syncthreads();
     if (tid == 0) {
         unsigned long long* const h64 = reinterpret_cast<unsigned long long*>(ba.hot);
         const int in_grp = (G - grp + NSEG - 1) / NSEG, ngrp = G < NSEG ? G : NSEG;
         bool last = false;
-        if (sent) {
-            const unsigned long long old =
-                atomicAdd(&h64[hot_cnt(grp) / 2], ((unsigned long long)ncells << CNT_BITS) | 1ull);
-            if ((int)(old & ((1ull << CNT_BITS) - 1)) == in_grp - 1)
-                last = atomicAdd((unsigned*)&ba.hot[hot_done(NSEG)], 1u) == (unsigned)(ngrp - 1);
-        }
+        drain_memory();
+        const unsigned long long old =
+            atomicAdd(&h64[hot_cnt(grp) / 2], ((unsigned long long)ncells << CNT_BITS) | 1ull);
+        if ((int)(old & ((1ull << CNT_BITS) - 1)) == in_grp - 1)
+            last = atomicAdd((unsigned*)&ba.hot[hot_done(NSEG)], 1u) == (unsigned)(ngrp - 1);
         s_last = last;
     }
     __syncthreads();

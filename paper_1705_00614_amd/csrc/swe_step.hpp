@@ -649,6 +649,34 @@ __host__ __device__ constexpr bool short_div_exact(int n, int b) {
 }
 __device__ __forceinline__ int short_div(int a, int b) { return (int)(__umul24((unsigned)a, short_div_mul(b)) >> 16); }
 
+// Product of the low 24 bits of a and b, as the 24-bit multiplier gives it.
+__host__ __device__ __forceinline__ unsigned mul24(unsigned a, unsigned b) {
+#ifdef __HIP_DEVICE_COMPILE__
+    return __umul24(a, b);
+#else
+    return (a & 0xFFFFFFu) * (b & 0xFFFFFFu);
+#endif
+}
+
+// Global index of cell (x, y) of an inner tile whose cell (0, -HALO) has index
+// org: one 24-bit multiply-add (full rate; a 32-bit product takes four times
+// as long), exact for nx < 2^24.
+__host__ __device__ __forceinline__ int inner_cell(int org, int x, int y, int nx) {
+    return org + (int)(mul24((unsigned)(y + HALO), (unsigned)nx) + (unsigned)x);
+}
+
+// Whether the tile at (tx0, ty0) takes the step's general (EDGE) form: its
+// window leaves the grid, or the grid is too wide for inner_cell.  A tile with
+// rows beside it on both sides is in a grid of at least three tile rows, hence
+// of at most MAX_COLS columns; only the 64-wide tiles' grids reach 2^24.
+template <int TX> constexpr int MAX_COLS = ((1 << TILE_BITS) - 1) / 3 * TX;
+template <int TX, int TY>
+__host__ __device__ __forceinline__ bool edge_tile(int tx0, int ty0, int nx, int ny) {
+    bool e = tx0 < HALO || ty0 < HALO || tx0 + TX + HALO > nx || ty0 + TY + HALO > ny;
+    if constexpr (MAX_COLS<TX> >= 1 << 24) e = e || nx >= 1 << 24;
+    return e;
+}
+
 // ---------------------------------------------------------------- LDS of a tile
 
 // Row pitch is odd so that lanes walking down a column hit distinct banks.
@@ -874,14 +902,11 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
     const bool src_here = PER ? a.ni > 0
                               : tx0 - HALO < a.i0 + a.ni && a.i0 < tx0 + TX + HALO && ty0 - HALO < a.j0 + a.nj &&
                                     a.j0 < ty0 + TY + HALO;
-    // global index of tile cell (x, y).  A tile away from the edges has a
-    // second row of tiles beside it, so its grid has fewer than 2^24 columns:
-    // one 24-bit multiply-add (full rate; a 32-bit product takes four times
-    // as long).
+    // global index of tile cell (x, y)
     const int org = (ty0 - HALO) * nx + tx0;
     auto cell = [&](int x, int y) {
         if constexpr (EDGE) return (ty0 + y) * nx + tx0 + x;
-        else return org + (int)(__umul24((unsigned)(y + HALO), (unsigned)nx) + (unsigned)x);
+        else return inner_cell(org, x, y, nx);
     };
     auto source = [&](int x, int y) { return src_here && is_src(a, wrapx(tx0 + x), wrapy(ty0 + y)); };
     auto inside = [&](int x, int y) {
@@ -1471,7 +1496,7 @@ __device__ __forceinline__ void step_grid(const Args<real>& a, int b0, int G) {
                                               : entry_tile(list_entry(off, a.lists, a.ntiles, a.slot, p));
         const int tx0 = (tile % a.ntx) * TX, ty0 = (tile / a.ntx) * TY;
         ncells += (long long)min(TX, nx - tx0) * min(TY, ny - ty0);
-        const bool edge = tx0 < HALO || ty0 < HALO || tx0 + TX + HALO > nx || ty0 + TY + HALO > ny;
+        const bool edge = edge_tile<TX, TY>(tx0, ty0, nx, ny);
         constexpr bool FLD = MODE == MODE_FIELD;
         real vmax = real(0);
         bool bad = false;
@@ -1875,7 +1900,7 @@ __global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_batch_step(Batch
         const int nx = a.nx, ny = a.ny;
         const int tx0 = (tile % a.ntx) * TX, ty0 = (tile / a.ntx) * TY;
         ncells += (long long)min(TX, nx - tx0) * min(TY, ny - ty0);
-        const bool edge = tx0 < HALO || ty0 < HALO || tx0 + TX + HALO > nx || ty0 + TY + HALO > ny;
+        const bool edge = edge_tile<TX, TY>(tx0, ty0, nx, ny);
         real vt = real(0);
         bool bad = false;
         double msum = 0.0, lsum = 0.0, fnone = 0.0;   // scenarios of a batch carry no rate field

@@ -2234,23 +2234,32 @@ int lc_put_crops(swe_lc_t* c, LcHold& io, int n, const double* x, const double* 
     const int fit = (int)std::min<size_t>(slot / per, (size_t)n), even = (n + threads - 1) / threads;
     const int cp = fit < even ? fit : even, pieces = (n + cp - 1) / cp;
     double part[XFER_SLOTS] = {};
-    const hipError_t e = xfer_parallel(pieces, threads, [&](int q, int t) -> hipError_t {
-        const size_t c0 = (size_t)q * cp, m = std::min<size_t>(cp, n - c0);
-        float* hx = (float*)(io.base + t * slot);
-        float* hy = hx + m * px * 6;
-        float* hm = hy + m * py;
-        if (q >= threads) {   // the slot's previous piece has been read
-            const hipError_t s = hipStreamSynchronize(c->stream);
-            if (s != hipSuccess) return s;
-        }
-        for (size_t k = 0; k < m * px * 6; ++k) hx[k] = (float)x[c0 * px * 6 + k];
-        for (size_t k = 0; k < m * py; ++k) hy[k] = (float)y[c0 * py + k];
-        for (size_t k = 0; k < m * py; ++k) { hm[k] = (float)mask[c0 * py + k]; part[t] += mask[c0 * py + k]; }
-        hipLaunchKernelGGL(L_::k_crops_in, dim3(grid_for((long long)m * px, 256)), dim3(256), 0, c->stream, hx, m * px,
-                           hy, hm, m * py, c->act[0] + c0 * px * 16, c->y + c0 * py, c->mask + c0 * py);
-        return hipGetLastError();
-    });
-    HIPCHK(e);
+    for (int q0 = 0; q0 < pieces; q0 += threads) {
+        if (q0) HIPCHK(hipStreamSynchronize(c->stream));   // the slots' previous pieces have been read
+        auto at = [&](int t, size_t* c0, size_t* m) {
+            *c0 = (size_t)(q0 + t) * cp;
+            *m = std::min<size_t>(cp, n - *c0);
+            return (float*)(io.base + t * slot);
+        };
+        const hipError_t e = xfer_team(
+            std::min(threads, pieces - q0),
+            [&](int t) {
+                size_t c0, m;
+                float *const hx = at(t, &c0, &m), *const hy = hx + m * px * 6, *const hm = hy + m * py;
+                for (size_t k = 0; k < m * px * 6; ++k) hx[k] = (float)x[c0 * px * 6 + k];
+                for (size_t k = 0; k < m * py; ++k) hy[k] = (float)y[c0 * py + k];
+                for (size_t k = 0; k < m * py; ++k) { hm[k] = (float)mask[c0 * py + k]; part[t] += mask[c0 * py + k]; }
+                return hipSuccess;
+            },
+            [&](int t) {
+                size_t c0, m;
+                const float *const hx = at(t, &c0, &m), *const hy = hx + m * px * 6, *const hm = hy + m * py;
+                hipLaunchKernelGGL(L_::k_crops_in, dim3(grid_for((long long)m * px, 256)), dim3(256), 0, c->stream, hx,
+                                   m * px, hy, hm, m * py, c->act[0] + c0 * px * 16, c->y + c0 * py, c->mask + c0 * py);
+                return hipGetLastError();
+            });
+        HIPCHK(e);
+    }
     if (cnt) {
         *cnt = 0.0;
         for (double v : part) *cnt += v;

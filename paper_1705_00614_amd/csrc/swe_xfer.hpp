@@ -10,6 +10,11 @@
 // threads convert pieces while others are on the way.  Transfers of less than
 // XFER_THREADED bytes take one launch, one wait and the calling thread.
 //
+// The handle of the caller's stream may name another stream in every thread
+// (hipStreamPerThread).  So where other threads launch pieces, the calling one
+// first waits for what it has queued, and each thread waits for its own pieces;
+// where pieces are only queued, the calling thread launches all of them.
+//
 // The pinned memory is one pool per process, at most XFER_SLOTS slots of
 // XFER_SLOT bytes, taken by one transfer at a time (a mutex), allocated when a
 // transfer first needs it and given back when the last handle is destroyed.
@@ -146,35 +151,46 @@ struct XferHold {
     }
 };
 
-// Run job(chunk, slot) for every chunk on up to `threads` <= XFER_SLOTS host
-// threads (the caller is one of them), thread t taking chunks t, t + T, ...
-// and slot t.  Returns the first error.
-template <class Job>
-hipError_t xfer_parallel(int chunks, int threads, Job job) {
+// Run job(t) for every t < T <= XFER_SLOTS on host threads (the caller is
+// number 0) and, on the calling thread and in order, then(t) once job(t) is
+// done.  Returns the first error; nothing is run after one of its own.
+template <class Job, class Then>
+hipError_t xfer_team(int T, Job job, Then then) {
     int dev = 0;
     const hipError_t e0 = hipGetDevice(&dev);
     if (e0 != hipSuccess) return e0;
-    const int T = chunks < threads ? chunks : threads;
-    hipError_t err[XFER_SLOTS] = {};
-    auto work = [&](int t) {
-        for (int c = t; c < chunks && err[t] == hipSuccess; c += T) err[t] = job(c, t);
-    };
+    hipError_t err[XFER_SLOTS] = {}, e = hipSuccess;
     std::thread th[XFER_SLOTS];
     int started = 1;
     try {
         for (; started < T; ++started)
             th[started] = std::thread([&, t = started] {
                 err[t] = hipSetDevice(dev);
-                if (err[t] == hipSuccess) work(t);
+                if (err[t] == hipSuccess) err[t] = job(t);
             });
     } catch (const std::system_error&) {   // no more threads: the caller takes the rest
     }
-    work(0);
-    for (int t = started; t < T; ++t) work(t);
-    for (int t = 1; t < started; ++t) th[t].join();
-    for (int t = 0; t < T; ++t)
-        if (err[t] != hipSuccess) return err[t];
-    return hipSuccess;
+    for (int t = 0; t < T; ++t) {
+        if (t > 0 && t < started) th[t].join();
+        else err[t] = job(t);
+        if (e == hipSuccess) e = err[t] == hipSuccess ? then(t) : err[t];
+    }
+    return e;
+}
+
+// Run job(chunk, slot) for every chunk on up to `threads` <= XFER_SLOTS host
+// threads, thread t taking chunks t, t + T, ... and slot t.
+template <class Job>
+hipError_t xfer_parallel(int chunks, int threads, Job job) {
+    const int T = chunks < threads ? chunks : threads;
+    return xfer_team(
+        T,
+        [&](int t) {
+            hipError_t e = hipSuccess;
+            for (int c = t; c < chunks && e == hipSuccess; c += T) e = job(c, t);
+            return e;
+        },
+        [](int) { return hipSuccess; });
 }
 
 inline int xfer_grid(size_t cells) {
@@ -260,7 +276,8 @@ hipError_t xfer_get(hipStream_t st, const swe::Ctrl* ctrl, real* const (&a)[3], 
         for (int k = 0; k < nf; ++k) convert(out[want[k]], base + k * n, n);
         return hipSuccess;
     }
-    e = xfer_parallel(nf * pl.per, pl.threads, [&](int c, int t) -> hipError_t {
+    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    return xfer_parallel(nf * pl.per, pl.threads, [&](int c, int t) -> hipError_t {
         const int q = want[c / pl.per];
         const size_t first = (size_t)(c % pl.per) * pl.piece, cnt = n - first < pl.piece ? n - first : pl.piece;
         real* slot = (real*)(pl.base + t * pl.slot);
@@ -272,10 +289,9 @@ hipError_t xfer_get(hipStream_t st, const swe::Ctrl* ctrl, real* const (&a)[3], 
         xfer_populate(out[q] + first, cnt * sizeof(double));   // while the piece is on its way
         if (s == hipSuccess) s = hipEventSynchronize(pl.ev[t]);
         if (s == hipSuccess) convert(out[q] + first, slot, cnt);
+        else (void)hipStreamSynchronize(st);   // no piece is under way when the pool is let go
         return s;
     });
-    if (e != hipSuccess) (void)hipStreamSynchronize(st);   // no piece is under way when the pool is let go
-    return e;
 }
 
 // Fields of n cells each from fill(q, first, cnt, dst), which writes cells
@@ -298,7 +314,8 @@ hipError_t xfer_put(hipStream_t st, int nf, const swe::FieldPair<real>* f, size_
         if ((e = hipGetLastError()) != hipSuccess) return e;
         return hipStreamSynchronize(st);
     }
-    e = xfer_parallel(nf * pl.per, pl.threads, [&](int c, int t) -> hipError_t {
+    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    return xfer_parallel(nf * pl.per, pl.threads, [&](int c, int t) -> hipError_t {
         const int q = c / pl.per;
         const size_t first = (size_t)(c % pl.per) * pl.piece, cnt = n - first < pl.piece ? n - first : pl.piece;
         real* slot = (real*)(pl.base + t * pl.slot);
@@ -307,10 +324,10 @@ hipError_t xfer_put(hipStream_t st, int nf, const swe::FieldPair<real>* f, size_
         hipLaunchKernelGGL((swe::k_import<real, 1>), dim3(xfer_grid(cnt)), dim3(256), 0, st, x, first, cnt);
         hipError_t s = hipGetLastError();
         if (s == hipSuccess) s = hipEventRecord(pl.ev[t], st);
-        return s == hipSuccess ? hipEventSynchronize(pl.ev[t]) : s;
+        if (s == hipSuccess) s = hipEventSynchronize(pl.ev[t]);
+        if (s != hipSuccess) (void)hipStreamSynchronize(st);
+        return s;
     });
-    if (e != hipSuccess) (void)hipStreamSynchronize(st);
-    return e;
 }
 
 // Whether every x[i], i < n, lies in [lo, hi] (false for NaN), on host threads

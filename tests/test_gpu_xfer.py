@@ -100,3 +100,16 @@ def test_transfers_of_several_threads():
     for t in th:
         t.join()
     assert not failed, failed
+
+
+def test_per_thread_stream_orders_transfers_after_queued_steps():
+    """On hipStreamPerThread a state read after queued steps is theirs, though
+    several host threads move it (the handle names another stream in each)."""
+    per_thread = 2   # hipStreamPerThread
+    sc = S.dam_break(900, 700, x_dam=450.0, precision=32)
+    g, ref = swe.Solver(sc, stream=per_thread), swe.Solver(sc, stream=None)
+    for steps in (1, 7):
+        g.enqueue(steps)
+        ref.run(steps)
+        assert all(np.array_equal(a, b) for a, b in zip(g.state(), ref.state()))
+    g.close()

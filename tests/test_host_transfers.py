@@ -1,0 +1,30 @@
+"""The library's host path on a stub of the HIP runtime (host_runtime.cpp),
+one scenario each, no GPU: ordering of transfers on the caller's stream."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_1705_00614_amd import build, swe
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    swe.load()   # builds the library if it is not there
+    exe = str(tmp_path_factory.mktemp("host") / "host_runtime")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-pthread", "-rdynamic", "-I", os.path.join(ROCM, "include"),
+                    os.path.join(HERE, "host_runtime.cpp"), build.LIB, "-ldl", "-Wl,--allow-shlib-undefined",
+                    "-Wl,-rpath," + os.path.dirname(build.LIB), "-o", exe], check=True)
+    return exe
+
+
+@pytest.mark.parametrize("scenario", ["per_thread_stream"])
+def test_host_path(program, scenario):
+    res = subprocess.run([program, scenario], capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0, res.stdout + res.stderr

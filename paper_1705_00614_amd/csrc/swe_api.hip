@@ -2221,7 +2221,38 @@ struct LcHold {
 // Host FP64 crops (n, Sin, Sin, 6) -> bf16 act[0] with 16 channels; with y,
 // labels and mask (n, So, So, 6) and the sum of the mask.  Rounded to FP32
 // into pinned memory by host threads, a crop range each, and expanded on the
-// device; queued on the stream, the pool stays held in `io`.
+// device; queued on the stream, the pool stays held in `io`.  Without pinned
+// memory the crops are expanded by the calling thread and copied one by one.
+int lc_put_crops_pageable(swe_lc_t* c, int n, const double* x, const double* y, const double* mask, double* cnt) {
+    const size_t px = (size_t)lc_in(c, 0) * lc_in(c, 0), py = y ? (size_t)c->So * c->So * 6 : 0;
+    const XferHeap<unsigned short> h(px * 16);
+    const XferHeap<float> hy(py), hm(py);
+    if (!h.p || !hy.p || !hm.p) { set_err("swe_lc: out of host memory"); return SWE_ENOMEM; }
+    double sum = 0.0;
+    for (size_t b = 0; b < (size_t)n; ++b) {
+        for (size_t p = 0; p < px; ++p)
+            for (int k = 0; k < 16; ++k) {
+                const float f = k < 6 ? (float)x[(b * px + p) * 6 + k] : 0.f;
+                unsigned u;
+                std::memcpy(&u, &f, 4);
+                u += 0x7FFFu + ((u >> 16) & 1u);
+                h.p[p * 16 + k] = (unsigned short)(u >> 16);
+            }
+        for (size_t k = 0; k < py; ++k) {
+            hy.p[k] = (float)y[b * py + k];
+            hm.p[k] = (float)mask[b * py + k];
+            sum += mask[b * py + k];
+        }
+        HIPCHK(hipMemcpyAsync(c->act[0] + b * px * 16, h.p, px * 32, hipMemcpyHostToDevice, c->stream));
+        if (py) {
+            HIPCHK(hipMemcpyAsync(c->y + b * py, hy.p, py * sizeof(float), hipMemcpyHostToDevice, c->stream));
+            HIPCHK(hipMemcpyAsync(c->mask + b * py, hm.p, py * sizeof(float), hipMemcpyHostToDevice, c->stream));
+        }
+        HIPCHK(hipStreamSynchronize(c->stream));
+    }
+    if (cnt) *cnt = sum;
+    return 0;
+}
 int lc_put_crops(swe_lc_t* c, LcHold& io, int n, const double* x, const double* y, const double* mask, double* cnt) {
     const size_t px = (size_t)lc_in(c, 0) * lc_in(c, 0), py = y ? (size_t)c->So * c->So * 6 : 0;
     const size_t per = (px * 6 + 2 * py) * sizeof(float), all = n * per;
@@ -2229,7 +2260,7 @@ int lc_put_crops(swe_lc_t* c, LcHold& io, int n, const double* x, const double* 
     int threads = 1;
     if (all > XFER_THREADED) threads = (int)std::min<size_t>(XFER_SLOTS, (all >> 20) + 1);
     if (size / threads < per) threads = 1;
-    if (size < per) { set_err("swe_lc: no pinned memory for a crop"); return SWE_ENOMEM; }
+    if (size < per) return lc_put_crops_pageable(c, n, x, y, mask, cnt);
     const size_t slot = size / threads / 16 * 16;
     const int fit = (int)std::min<size_t>(slot / per, (size_t)n), even = (n + threads - 1) / threads;
     const int cp = fit < even ? fit : even, pieces = (n + cp - 1) / cp;
@@ -2373,8 +2404,13 @@ int swe_lc_set_params(swe_lc_t* c, const double* params) {
 
 static int lc_read_floats(swe_lc_t* c, const float* src, double* dst, size_t n) {
     LcHold io(c->stream);
-    const size_t room = io.hold.get(std::min(n * sizeof(float), XFER_SLOT), &io.base) / sizeof(float);
-    if (!room) { set_err("swe_lc: no pinned memory"); return SWE_ENOMEM; }
+    size_t room = io.hold.get(std::min(n * sizeof(float), XFER_SLOT), &io.base) / sizeof(float);
+    const XferHeap<float> heap(room ? 0 : std::min(n, XFER_PAGEABLE));
+    if (!room) {
+        if (!heap.p) { set_err("swe_lc: out of host memory"); return SWE_ENOMEM; }
+        io.base = (unsigned char*)heap.p;
+        room = std::min(n, XFER_PAGEABLE);
+    }
     for (size_t k0 = 0; k0 < n; k0 += room) {
         const size_t m = std::min(room, n - k0);
         HIPCHK(hipMemcpyAsync(io.base, src + k0, sizeof(float) * m, hipMemcpyDeviceToHost, c->stream));
@@ -2464,9 +2500,11 @@ int swe_lc_train_step(swe_lc_t* c, int n, const double* x, const double* y, cons
     if (rc) return rc;
     if ((rc = lc_opt_step(c, n, cnt, lr, c->loss))) return rc;
     // (the crops' pinned memory is read before the loss is written)
-    HIPCHK(hipMemcpyAsync(io.base, c->loss, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    double value = 0.0;
+    void* const to = io.base ? (void*)io.base : (void*)&value;
+    HIPCHK(hipMemcpyAsync(to, c->loss, sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
-    if (loss) std::memcpy(loss, io.base, sizeof(double));
+    if (loss) std::memcpy(loss, to, sizeof(double));
     return 0;
 }
 

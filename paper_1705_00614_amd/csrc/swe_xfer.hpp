@@ -8,7 +8,9 @@
 // (it picks the current layer of a ping-pong pair from the step count itself,
 // so that no round trip for the control block comes first), and several host
 // threads convert pieces while others are on the way.  Transfers of less than
-// XFER_THREADED bytes take one launch, one wait and the calling thread.
+// XFER_THREADED bytes take one launch, one wait and the calling thread.  Where
+// the system gives no pinned memory, fields are copied to and from ordinary
+// memory in pieces instead.
 //
 // The handle of the caller's stream may name another stream in every thread
 // (hipStreamPerThread).  So where other threads launch pieces, the calling one
@@ -27,6 +29,7 @@
 #include <climits>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <system_error>
 #include <thread>
 
@@ -100,6 +103,7 @@ namespace {
 constexpr int XFER_SLOTS = 8;                    // pieces in flight = host threads of a large transfer
 constexpr size_t XFER_SLOT = size_t(4) << 20;
 constexpr size_t XFER_THREADED = size_t(2) << 20;
+constexpr size_t XFER_PAGEABLE = size_t(1) << 20;   // elements of a piece without pinned memory
 
 struct XferPool {
     std::mutex mu;              // held for the length of a transfer
@@ -210,8 +214,17 @@ inline void xfer_populate(void* p, size_t bytes) {
 #endif
 }
 
+// Ordinary host memory for a transfer that gets no pinned memory.
+template <typename T> struct XferHeap {
+    T* p;
+    explicit XferHeap(size_t n) : p(new (std::nothrow) T[n ? n : 1]) {}
+    ~XferHeap() { delete[] p; }
+    XferHeap(const XferHeap&) = delete;
+};
+
 // A transfer of nf fields of n cells through the pool: in one piece where
-// that is small, else split over threads with an event each.
+// that is small, else split over threads with an event each; without pinned
+// memory neither (base stays null).
 struct XferPlan {
     XferHold hold;
     unsigned char* base = nullptr;
@@ -226,7 +239,7 @@ struct XferPlan {
             return hipSuccess;
         }
         const size_t size = hold.get(XFER_SLOTS * XFER_SLOT, &base);
-        if (!size) return hipErrorOutOfMemory;
+        if (!size) return hipSuccess;
         slot = size < XFER_SLOT ? size : XFER_SLOT;
         threads = (int)(size / slot);
         piece = (n * nf + threads - 1) / threads;   // about one piece a thread, at least 32768 cells, at most a slot
@@ -246,6 +259,56 @@ struct XferPlan {
     }
 };
 
+// xfer_get and xfer_put without pinned memory, in pieces of about
+// XFER_PAGEABLE cells, each copied and waited for.
+template <typename real, class Convert>
+hipError_t xfer_get_pageable(hipStream_t st, const swe::Ctrl* ctrl, real* const (&a)[3], real* const (&b)[3], int pitch,
+                             int x0, int y0, int w, int h, double* const (&out)[3], Convert convert) {
+    long long step = 0;
+    hipError_t e = hipMemcpyAsync(&step, &ctrl->step, sizeof step, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return e;
+    const size_t n = (size_t)w * h;
+    // whole rows of a rectangle, any cells of a whole layer
+    const size_t rows = XFER_PAGEABLE / w > 1 ? XFER_PAGEABLE / w : 1, most = w == pitch ? XFER_PAGEABLE : rows * w;
+    XferHeap<real> buf(n < most ? n : most);
+    if (!buf.p) return hipErrorOutOfMemory;
+    for (int q = 0; q < 3; ++q) {
+        if (!out[q]) continue;
+        const real* src = ((step & 1) ? b[q] : a[q]) + (size_t)y0 * pitch + x0;
+        for (size_t first = 0; first < n; first += most) {
+            const size_t cnt = n - first < most ? n - first : most;
+            if (w == pitch)
+                e = hipMemcpyAsync(buf.p, src + first, cnt * sizeof(real), hipMemcpyDeviceToHost, st);
+            else
+                e = hipMemcpy2DAsync(buf.p, w * sizeof(real), src + first / w * pitch, pitch * sizeof(real),
+                                     w * sizeof(real), cnt / w, hipMemcpyDeviceToHost, st);
+            const hipError_t s = hipStreamSynchronize(st);
+            if (e == hipSuccess) e = s;
+            if (e != hipSuccess) return e;
+            convert(out[q] + first, buf.p, cnt);
+        }
+    }
+    return hipSuccess;
+}
+template <typename real, class Fill>
+hipError_t xfer_put_pageable(hipStream_t st, int nf, const swe::FieldPair<real>* f, size_t n, Fill fill) {
+    XferHeap<real> buf(n < XFER_PAGEABLE ? n : XFER_PAGEABLE);
+    if (!buf.p) return hipErrorOutOfMemory;
+    for (int q = 0; q < nf; ++q)
+        for (size_t first = 0; first < n; first += XFER_PAGEABLE) {
+            const size_t cnt = n - first < XFER_PAGEABLE ? n - first : XFER_PAGEABLE;
+            fill(q, first, cnt, buf.p);
+            hipError_t e = hipMemcpyAsync(f[q].a + first, buf.p, cnt * sizeof(real), hipMemcpyHostToDevice, st);
+            if (e == hipSuccess && f[q].b != f[q].a)
+                e = hipMemcpyAsync(f[q].b + first, buf.p, cnt * sizeof(real), hipMemcpyHostToDevice, st);
+            const hipError_t s = hipStreamSynchronize(st);
+            if (e == hipSuccess) e = s;
+            if (e != hipSuccess) return e;
+        }
+    return hipSuccess;
+}
+
 // The rectangle (x0, y0, w x h) of up to three fields' current layers into
 // FP64 host arrays (null: not wanted), after everything queued on `st`.
 template <typename real>
@@ -263,6 +326,7 @@ hipError_t xfer_get(hipStream_t st, const swe::Ctrl* ctrl, real* const (&a)[3], 
     XferPlan pl;
     hipError_t e = pl.prepare(nf, n, sizeof(real));
     if (e != hipSuccess) return e;
+    if (!pl.base) return xfer_get_pageable(st, ctrl, a, b, pitch, x0, y0, w, h, out, convert);
     if (pl.whole) {
         real* base = (real*)pl.base;
         swe::XferFields<real, 3> x{};
@@ -302,6 +366,7 @@ hipError_t xfer_put(hipStream_t st, int nf, const swe::FieldPair<real>* f, size_
     XferPlan pl;
     hipError_t e = pl.prepare(nf, n, sizeof(real));
     if (e != hipSuccess) return e;
+    if (!pl.base) return xfer_put_pageable(st, nf, f, n, fill);
     if (pl.whole && nf <= 3) {
         real* base = (real*)pl.base;
         swe::XferFields<real, 3> x{};

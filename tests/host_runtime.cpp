@@ -349,7 +349,55 @@ int per_thread_stream() {
     return 0;
 }
 
+// A device array of n elements that holds exactly `want`.
+template <typename T> bool on_device(const std::vector<T>& want) {
+    std::lock_guard<std::mutex> lk(mu);
+    for (auto& m : device_mem)
+        if (m.second == want.size() * sizeof(T) && !memcmp(m.first, want.data(), m.second)) return true;
+    return false;
+}
+
+// Without any pinned memory every transfer works through ordinary memory:
+// states of one piece and of several, a patch's interior, a network's crops
+// and parameters.
+int no_pinned_memory() {
+    no_pinned = true;
+    for (int n : {64, 1500})
+        for (int precision : {32, 64}) {
+            Grid g(n, precision, nullptr);
+            EXPECT(g.s && g.get() == 0 && g.kept());
+            EXPECT(g.set() == 0 && swe_run(g.s, 3) == 0 && swe_time(g.s) == 0.0);
+            std::vector<double> only(g.b.size());
+            EXPECT(swe_get_state(g.s, nullptr, only.data(), nullptr) == 0 && only == g.Q);
+            swe_destroy(g.s);
+        }
+    {
+        const int n = 40, r = 3, cw = 9, ch = 7, w = r * cw, h = r * ch;
+        std::vector<double> b(n * n), H(n * n, 1.0), bf((w + 2 * SWE_NEST_FRAME) * (h + 2 * SWE_NEST_FRAME)), Hf(w * h), o(w * h);
+        for (size_t k = 0; k < Hf.size(); ++k) Hf[k] = 1.0 + (double)k;
+        swe_params p = params(32, nullptr, H);
+        swe_patch q = {10, 12, cw, ch, bf.data(), nullptr, Hf.data(), nullptr, nullptr};
+        swe_nest_t* s = swe_nest_create(n, n, 1.0, b.data(), nullptr, &p, r, 1, 1, &q);
+        EXPECT(s && swe_nest_get_patch(s, 0, o.data(), nullptr, nullptr) == 0 && o == Hf);
+    }
+    Crops c(16, 5, nullptr);
+    EXPECT(c.c && c.train() == 0);
+    std::vector<unsigned short> x(c.x.size() / 6 * 16);   // (the values are exact in bf16)
+    for (size_t k = 0; k < c.x.size(); ++k) {
+        const float f = (float)c.x[k];
+        unsigned u;
+        memcpy(&u, &f, 4);
+        x[k / 6 * 16 + k % 6] = (unsigned short)(u >> 16);
+    }
+    EXPECT(on_device(x) && on_device(std::vector<float>(c.m.begin(), c.m.end())));
+    EXPECT(swe_lc_forward(c.c, c.n, c.x.data(), c.o.data()) == 0 && swe_lc_infer(c.c, c.n, c.x.data(), c.o.data()) == 0);
+    std::vector<double> par(swe_lc_nparams(), 0.5), got(par.size());
+    EXPECT(swe_lc_set_params(c.c, par.data()) == 0 && swe_lc_get_params(c.c, got.data()) == 0 && got == par);
+    return 0;
+}
+
 const std::map<std::string, std::function<int()>> scenarios = {
+    {"no_pinned_memory", no_pinned_memory},
     {"per_thread_stream", per_thread_stream},
 };
 

@@ -1,5 +1,6 @@
 """The library's host path on a stub of the HIP runtime (host_runtime.cpp),
-one scenario each, no GPU: ordering of transfers on the caller's stream."""
+one scenario each, no GPU: ordering of transfers on the caller's stream, and
+transfers where there is no pinned memory."""
 import os
 import shutil
 import subprocess
@@ -24,7 +25,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["per_thread_stream"])
+@pytest.mark.parametrize("scenario", ["per_thread_stream", "no_pinned_memory"])
 def test_host_path(program, scenario):
     res = subprocess.run([program, scenario], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0, res.stdout + res.stderr

@@ -2209,7 +2209,7 @@ int lc_opt_step(swe_lc_t* c, int n, double cnt, double lr, double* loss_dev) {
     return 0;
 }
 
-// The pool for a network's host data, waited for before it is let go.
+// Pinned memory for a network's host data, waited for before it is let go.
 struct LcHold {
     hipStream_t st;
     XferHold hold;
@@ -2221,7 +2221,7 @@ struct LcHold {
 // Host FP64 crops (n, Sin, Sin, 6) -> bf16 act[0] with 16 channels; with y,
 // labels and mask (n, So, So, 6) and the sum of the mask.  Rounded to FP32
 // into pinned memory by host threads, a crop range each, and expanded on the
-// device; queued on the stream, the pool stays held in `io`.  Without pinned
+// device; queued on the stream, the buffer stays held in `io`.  Without pinned
 // memory the crops are expanded by the calling thread and copied one by one.
 int lc_put_crops_pageable(swe_lc_t* c, int n, const double* x, const double* y, const double* mask, double* cnt) {
     const size_t px = (size_t)lc_in(c, 0) * lc_in(c, 0), py = y ? (size_t)c->So * c->So * 6 : 0;

@@ -9,17 +9,20 @@
 // so that no round trip for the control block comes first), and several host
 // threads convert pieces while others are on the way.  Transfers of less than
 // XFER_THREADED bytes take one launch, one wait and the calling thread.  Where
-// the system gives no pinned memory, fields are copied to and from ordinary
+// there is no pinned memory to be had, fields are copied to and from ordinary
 // memory in pieces instead.
 //
 // The handle of the caller's stream may name another stream in every thread
-// (hipStreamPerThread).  So where other threads launch pieces, the calling one
-// first waits for what it has queued, and each thread waits for its own pieces;
-// where pieces are only queued, the calling thread launches all of them.
+// (hipStreamPerThread).  Other threads launch pieces only after the calling one
+// has waited for what it had queued, and each waits for its own pieces; where
+// pieces are only queued, the calling thread launches all of them.
 //
-// The pinned memory is one pool per process, at most XFER_SLOTS slots of
-// XFER_SLOT bytes, taken by one transfer at a time (a mutex), allocated when a
-// transfer first needs it and given back when the last handle is destroyed.
+// The pinned memory is one pool per process: buffers leased to one transfer
+// each, allocated when none that is free is large enough and given back when
+// the last handle is destroyed; at most XFER_BUFFERS of them and XFER_TOTAL
+// bytes.  No transfer waits for another one: the pool's lock is held for the
+// bookkeeping alone, a large transfer takes its buffer only once the work
+// queued before it is done, and one that finds none left goes without.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -105,12 +108,20 @@ constexpr size_t XFER_SLOT = size_t(4) << 20;
 constexpr size_t XFER_THREADED = size_t(2) << 20;
 constexpr size_t XFER_PAGEABLE = size_t(1) << 20;   // elements of a piece without pinned memory
 
+constexpr int XFER_BUFFERS = 64;
+constexpr size_t XFER_LEAST = size_t(4) << 10;   // smallest buffer; others are powers of two times it
+constexpr size_t XFER_TOTAL = size_t(128) << 20;
+
 struct XferPool {
-    std::mutex mu;              // held for the length of a transfer
-    unsigned char* base = nullptr;
-    size_t size = 0;
-    std::mutex users_mu;
-    int users = 0;              // live handles
+    struct Buffer {
+        unsigned char* p = nullptr;   // null: none allocated (or being allocated while busy)
+        size_t size = 0;
+        bool busy = false;
+    };
+    std::mutex mu;   // held for bookkeeping only
+    Buffer buf[XFER_BUFFERS];
+    size_t total = 0;
+    int users = 0;   // live handles
 };
 XferPool& xfer_pool() {
     static XferPool* p = new XferPool;   // never destroyed: handles may be freed at process exit
@@ -118,40 +129,77 @@ XferPool& xfer_pool() {
 }
 void xfer_retain() {
     XferPool& p = xfer_pool();
-    std::lock_guard<std::mutex> lk(p.users_mu);
+    std::lock_guard<std::mutex> lk(p.mu);
     ++p.users;
 }
 void xfer_release() {
     XferPool& p = xfer_pool();
-    std::lock_guard<std::mutex> lk(p.users_mu);
-    if (--p.users > 0) return;
-    std::lock_guard<std::mutex> lm(p.mu);
-    if (p.base) (void)hipHostFree(p.base);
-    p.base = nullptr;
-    p.size = 0;
+    unsigned char* gone[XFER_BUFFERS];
+    int n = 0;
+    {
+        std::lock_guard<std::mutex> lk(p.mu);
+        if (--p.users > 0) return;
+        for (XferPool::Buffer& b : p.buf)
+            if (b.p && !b.busy) {
+                gone[n++] = b.p;
+                p.total -= b.size;
+                b = XferPool::Buffer();
+            }
+    }
+    for (int k = 0; k < n; ++k) (void)hipHostFree(gone[k]);   // (may wait for the device: not under the lock)
 }
 
-// The pool, held while this lives.
+// A buffer of the pool, leased while this lives.  The holder waits for what
+// the device does with it before letting it go.
 struct XferHold {
-    std::unique_lock<std::mutex> lk{xfer_pool().mu};
-    // pinned memory for `bytes` (at least half a slot); where the
-    // system gives no more, what there is.  Returns its size, 0 for none.
+    XferPool::Buffer* at = nullptr;
+    XferHold() {}
+    ~XferHold() { drop(); }
+    XferHold(const XferHold&) = delete;
+    void drop() {
+        if (!at) return;
+        std::lock_guard<std::mutex> lk(xfer_pool().mu);
+        at->busy = false;
+        at = nullptr;
+    }
+    // pinned memory for `bytes`; the largest piece there is where no more is
+    // to be had.  Returns its size, 0 for none.
     size_t get(size_t bytes, unsigned char** base) {
+        drop();
         XferPool& p = xfer_pool();
-        if (bytes < XFER_SLOT / 2) bytes = XFER_SLOT / 2;
-        if (p.size < bytes) {
+        size_t size = XFER_LEAST;
+        while (size < bytes) size *= 2;
+        std::unique_lock<std::mutex> lk(p.mu);
+        XferPool::Buffer *fit = nullptr, *most = nullptr, *empty = nullptr;
+        for (XferPool::Buffer& b : p.buf) {
+            if (b.busy) continue;
+            if (!b.p) { empty = &b; continue; }
+            if (b.size >= bytes && (!fit || b.size < fit->size)) fit = &b;
+            if (!most || b.size > most->size) most = &b;
+        }
+        if (!fit && empty && p.total + size <= XFER_TOTAL) {
+            empty->busy = true;
+            p.total += size;
+            lk.unlock();
             void* q = nullptr;
-            if (hipHostMalloc(&q, bytes, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) {
-                if (p.base) (void)hipHostFree(p.base);
-                p.base = (unsigned char*)q;
-                p.size = bytes;
+            const hipError_t e = hipHostMalloc(&q, size, hipHostMallocPortable | hipHostMallocMapped);
+            if (e != hipSuccess) (void)hipGetLastError();
+            lk.lock();
+            if (e == hipSuccess) {
+                empty->p = (unsigned char*)q;
+                empty->size = size;
+                fit = empty;
             } else {
-                (void)hipGetLastError();
-                if (!p.size && bytes > XFER_SLOT / 2) return get(XFER_SLOT / 2, base);
+                empty->busy = false;
+                p.total -= size;
+                if (most && most->busy) most = nullptr;   // taken meanwhile
             }
         }
-        *base = p.base;
-        return p.size;
+        at = fit ? fit : most;
+        *base = at ? at->p : nullptr;
+        if (!at) return 0;
+        at->busy = true;
+        return at->size;
     }
 };
 
@@ -323,9 +371,10 @@ hipError_t xfer_get(hipStream_t st, const swe::Ctrl* ctrl, real* const (&a)[3], 
         if constexpr (sizeof(real) == 8) std::memcpy(dst, src, cnt * 8);
         else for (size_t k = 0; k < cnt; ++k) dst[k] = (double)src[k];
     };
-    XferPlan pl;
-    hipError_t e = pl.prepare(nf, n, sizeof(real));
+    hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return e;
+    XferPlan pl;
+    if ((e = pl.prepare(nf, n, sizeof(real))) != hipSuccess) return e;
     if (!pl.base) return xfer_get_pageable(st, ctrl, a, b, pitch, x0, y0, w, h, out, convert);
     if (pl.whole) {
         real* base = (real*)pl.base;
@@ -340,7 +389,6 @@ hipError_t xfer_get(hipStream_t st, const swe::Ctrl* ctrl, real* const (&a)[3], 
         for (int k = 0; k < nf; ++k) convert(out[want[k]], base + k * n, n);
         return hipSuccess;
     }
-    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
     return xfer_parallel(nf * pl.per, pl.threads, [&](int c, int t) -> hipError_t {
         const int q = want[c / pl.per];
         const size_t first = (size_t)(c % pl.per) * pl.piece, cnt = n - first < pl.piece ? n - first : pl.piece;
@@ -363,9 +411,10 @@ hipError_t xfer_get(hipStream_t st, const swe::Ctrl* ctrl, real* const (&a)[3], 
 // pair.  Returns once the device has them.
 template <typename real, class Fill>
 hipError_t xfer_put(hipStream_t st, int nf, const swe::FieldPair<real>* f, size_t n, Fill fill) {
-    XferPlan pl;
-    hipError_t e = pl.prepare(nf, n, sizeof(real));
+    hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return e;
+    XferPlan pl;
+    if ((e = pl.prepare(nf, n, sizeof(real))) != hipSuccess) return e;
     if (!pl.base) return xfer_put_pageable(st, nf, f, n, fill);
     if (pl.whole && nf <= 3) {
         real* base = (real*)pl.base;
@@ -379,7 +428,6 @@ hipError_t xfer_put(hipStream_t st, int nf, const swe::FieldPair<real>* f, size_
         if ((e = hipGetLastError()) != hipSuccess) return e;
         return hipStreamSynchronize(st);
     }
-    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
     return xfer_parallel(nf * pl.per, pl.threads, [&](int c, int t) -> hipError_t {
         const int q = c / pl.per;
         const size_t first = (size_t)(c % pl.per) * pl.piece, cnt = n - first < pl.piece ? n - first : pl.piece;
@@ -419,20 +467,16 @@ inline bool xfer_within(const double* x, size_t n, double lo, double hi) {
     return true;
 }
 
-// A few bytes of device memory after everything queued on `st`, through the
-// pool (a pageable destination costs 9 us more); straight where the pool is
-// in use.
+// A few bytes of device memory after everything queued on `st`, through a
+// buffer of the pool (a pageable destination costs 9 us more); straight where
+// there is none.
 inline hipError_t xfer_read(void* dst, const void* src, size_t bytes, hipStream_t st) {
-    XferPool& p = xfer_pool();
-    std::unique_lock<std::mutex> lk(p.mu, std::try_to_lock);
-    hipError_t e;
-    if (!lk.owns_lock() || p.size < bytes) {
-        if ((e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-        return hipStreamSynchronize(st);
-    }
-    if ((e = hipMemcpyAsync(p.base, src, bytes, hipMemcpyDeviceToHost, st)) != hipSuccess) return e;
-    if ((e = hipStreamSynchronize(st)) != hipSuccess) return e;
-    std::memcpy(dst, p.base, bytes);
+    XferHold hold;
+    unsigned char* base = nullptr;
+    void* const to = hold.get(bytes, &base) >= bytes ? base : dst;
+    hipError_t e = hipMemcpyAsync(to, src, bytes, hipMemcpyDeviceToHost, st);
+    if (e != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess) return e;
+    if (to != dst) std::memcpy(dst, to, bytes);
     return hipSuccess;
 }
 

@@ -90,7 +90,7 @@ void queue(hipStream_t st, bool piece) {
 void wait_done(std::unique_lock<std::mutex>& lk, Stream* s, long long seq) {
     if (s->work > s->done && seq >= s->work) {
         lk.unlock();
-        std::this_thread::sleep_for(std::chrono::milliseconds(30));
+        std::this_thread::sleep_for(std::chrono::milliseconds(5));
         lk.lock();
     }
     cv.wait(lk, [&] { return !s->blocked; });
@@ -349,6 +349,74 @@ int per_thread_stream() {
     return 0;
 }
 
+// Calls that wait for one handle's queued work hold up no other handle: its
+// transfers, a network's calls and its creation go on while a hundred threads
+// wait.  What the pool pins is bounded and given back with the last handle.
+int independent_handles() {
+    auto make = [] {
+        hipStream_t st;
+        (void)hipStreamCreateWithFlags(&st, 0);
+        return st;
+    };
+    std::vector<hipStream_t> slow;
+    std::vector<std::thread> waiting;
+    std::vector<Grid*> grids;
+    int bad = 0;
+    auto wait = [&](int n, std::function<bool(Grid&)> call) {
+        slow.push_back(make());
+        Grid* g = new Grid(n, 32, slow.back());
+        grids.push_back(g);
+        EXPECT(g->s && swe_enqueue(g->s, 1) == 0);
+        block(slow.back(), true);
+        waiting.emplace_back([&, g, call] { if (!call(*g)) ++bad; });
+    };
+    Grid b(1024, 32, make()), small(48, 64, make());
+    hipStream_t net_stream = make();
+    Crops net(32, 40, net_stream), other(32, 40, make());
+    EXPECT(b.s && small.s && net.c && other.c && net.train() == 0);
+    auto goes_on = [&](const char* what) {
+        auto f = std::async(std::launch::async, [&] {
+            Grid& fresh = *new Grid(256, 32, make());
+            grids.push_back(&fresh);   // (freeing device memory waits for the device)
+            return b.set() == 0 && b.get() == 0 && b.kept() && small.set() == 0 && small.get() == 0 &&
+                   small.kept() && swe_run(b.s, 1) == 0 && swe_time(small.s) == 0.0 && other.train() == 0 && fresh.s &&
+                   fresh.get() == 0 && fresh.kept();
+        });
+        if (f.wait_for(std::chrono::seconds(20)) != std::future_status::ready) {
+            printf("held up while another handle's %s waits\n", what);
+            fflush(stdout);
+            _exit(1);
+        }
+        return f.get();
+    };
+    wait(1024, [](Grid& g) { return g.get() == 0; });
+    EXPECT(goes_on("large state read"));
+    wait(1024, [](Grid& g) { return g.set() == 0; });
+    EXPECT(goes_on("large state set"));
+    wait(64, [](Grid& g) { return g.get() == 0 && g.set() == 0; });
+    EXPECT(goes_on("small state read"));
+    wait(64, [](Grid& g) { return swe_run(g.s, 1) == 0; });
+    EXPECT(goes_on("run"));
+    block(net_stream, true);
+    slow.push_back(net_stream);
+    waiting.emplace_back([&] { if (net.train() != 0) ++bad; });
+    EXPECT(goes_on("training step"));
+    for (int k = 0; k < 100; ++k) wait(32, [](Grid& g) { return std::isfinite(swe_time(g.s)); });
+    EXPECT(goes_on("hundred clock reads"));
+    EXPECT(pinned_bytes <= (size_t(128) << 20));
+    for (hipStream_t st : slow) block(st, false);
+    for (std::thread& t : waiting) t.join();
+    EXPECT(bad == 0);
+    for (Grid* g : grids) swe_destroy(g->s);
+    swe_destroy(b.s);
+    swe_destroy(small.s);
+    swe_lc_destroy(net.c);
+    EXPECT(pinned_bytes > 0);
+    swe_lc_destroy(other.c);
+    EXPECT(pinned_bytes == 0);
+    return 0;
+}
+
 // A device array of n elements that holds exactly `want`.
 template <typename T> bool on_device(const std::vector<T>& want) {
     std::lock_guard<std::mutex> lk(mu);
@@ -397,6 +465,7 @@ int no_pinned_memory() {
 }
 
 const std::map<std::string, std::function<int()>> scenarios = {
+    {"independent_handles", independent_handles},
     {"no_pinned_memory", no_pinned_memory},
     {"per_thread_stream", per_thread_stream},
 };

@@ -1,6 +1,7 @@
 """The library's host path on a stub of the HIP runtime (host_runtime.cpp),
 one scenario each, no GPU: ordering of transfers on the caller's stream, and
-transfers where there is no pinned memory."""
+transfers where there is no pinned memory, and handles that wait beside ones
+that do not."""
 import os
 import shutil
 import subprocess
@@ -25,7 +26,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["per_thread_stream", "no_pinned_memory"])
+@pytest.mark.parametrize("scenario", ["per_thread_stream", "no_pinned_memory", "independent_handles"])
 def test_host_path(program, scenario):
     res = subprocess.run([program, scenario], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0, res.stdout + res.stderr

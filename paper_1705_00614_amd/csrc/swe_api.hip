@@ -64,7 +64,7 @@ struct Launcher {
                             hipEvent_t e1);  // displaced-particle corrector; may be null
     hipError_t (*step_per)(const void* args, int grid, hipStream_t st, hipEvent_t e0,
                            hipEvent_t e1);   // periodic domain; may be null
-    hipError_t (*step_grids)(const void* dargs, int n, int per, hipStream_t st);   // the grids of a nest; may be null
+    hipError_t (*step_grids)(const void* dargs, const swe::GridShares& shares, hipStream_t st);   // a nest's grids; may be null
     hipError_t (*batch_step)(const void* bargs, int grid, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
     hipError_t (*batch_prepare_finish)(const void* bargs, hipStream_t st);
     hipError_t (*prepare)(const void* args, int grid, hipStream_t st);
@@ -79,9 +79,9 @@ hipError_t launch_step(const void* args, int grid, hipStream_t st, hipEvent_t e0
     return hipGetLastError();
 }
 template <typename real, int TX, int TY, int NT, int LIM>
-hipError_t launch_step_grids(const void* dargs, int n, int per, hipStream_t st) {
-    hipLaunchKernelGGL((swe::k_step_grids<real, TX, TY, NT, LIM>), dim3(n * per), dim3(NT), 0, st,
-                       (const Args<real>*)dargs, n, per);
+hipError_t launch_step_grids(const void* dargs, const swe::GridShares& shares, hipStream_t st) {
+    hipLaunchKernelGGL((swe::k_step_grids<real, TX, TY, NT, LIM>), dim3(shares.groups() * swe::NSEG), dim3(NT), 0, st,
+                       (const Args<real>*)dargs, shares);
     return hipGetLastError();
 }
 template <typename real, int TX, int TY, int NT, int LIM>
@@ -1474,7 +1474,6 @@ __global__ void swe::k_sum_tiles(const double* part, int n, double* out) {
 namespace {
 
 constexpr int NEST_GRAPH_STEPS = 8;   // coarse steps per captured graph (even)
-constexpr int NEST_GROUPS = 1024;     // workgroups of a launch over a nest's grids
 
 }  // namespace
 
@@ -1499,13 +1498,13 @@ struct swe_nest_s {
     long long launched = 0;          // coarse steps launched
     hipGraphExec_t graph = nullptr;
     std::vector<unsigned char> nargs;   // NestArgs<real>
-    // step arguments on the device, [coarse parity][patch parity][coarse grid,
-    // then the patches], and the workgroups of each grid in a launch
+    // step arguments on the device, [coarse parity][patch parity][first
+    // launch's grids, then a later launch's], each in the order of its shares
     void* dargs = nullptr;
-    int per = 0;
-    const void* grid_args(int pc, int pf, int first) const {
+    swe::GridShares shares[2] = {};   // coarse grid and patches (first substep); patches
+    const void* grid_args(int pc, int pf, int later) const {
         const size_t sz = precision == 32 ? sizeof(Args<float>) : sizeof(Args<double>);
-        return (const char*)dargs + sz * ((size_t)(pc * 2 + pf) * (np + 1) + first);
+        return (const char*)dargs + sz * ((size_t)(pc * 2 + pf) * (2 * np + 1) + (later ? np + 1 : 0));
     }
 };
 
@@ -1576,12 +1575,11 @@ hipError_t nest_step_t(swe_nest_t* n) {
     // Substep 0 takes its frame from layer n alone, so the patches' first step
     // and the coarse step share one launch; later substeps need layer n+1.
     for (int s = 0; s < n->r; ++s) {
-        const int pf = (int)(n->p[0]->launched & 1), first = s == 0 ? 0 : 1;
+        const int pf = (int)(n->p[0]->launched & 1), later = s == 0 ? 0 : 1;
         hipLaunchKernelGGL(swe::k_frame<real>, dim3(blocks_for(n->max_frame, 256), n->np), dim3(256), 0, n->stream, na,
                            pf, pc, (real)((double)s / (double)n->r));
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = c->L->step_grids(n->grid_args(pc, pf, first), n->np + 1 - first, n->per, n->stream)) != hipSuccess)
-            return e;
+        if ((e = c->L->step_grids(n->grid_args(pc, pf, later), n->shares[later], n->stream)) != hipSuccess) return e;
         if (s == 0) c->launched++;
         for (swe_t* q : n->p) q->launched++;
     }
@@ -1856,20 +1854,19 @@ swe_nest_t* swe_nest_create(int nx, int ny, double dx, const double* b, const do
         if (!g) { std::string m_ = g_err; free_nest(n); delete n; g_err = m_; return nullptr; }
         n->p.push_back(g);
     }
-    // Workgroups of a grid in a launch: one per tile where the launch stays
-    // within NEST_GROUPS, twice what is resident at once (a workgroup strides
-    // over further tiles; one without a tile holds its place for a read of the
-    // control block only), and at least 64.  Two patches of 4096 tiles, about
-    // 700 tiles a launch: 215 us per coarse step, with 512 workgroups 223; four
-    // patches of 169 tiles the same with either.
-    int tiles = n->c->ntiles;
-    for (swe_t* q : n->p) tiles = std::max(tiles, q->ntiles);
-    n->per = std::min((tiles + swe::NSEG - 1) / swe::NSEG, std::max(8, NEST_GROUPS / (swe::NSEG * (npatch + 1)))) * swe::NSEG;
     std::vector<unsigned char> all;
-    for (int k = 0; k < 4; ++k) {
-        all.insert(all.end(), n->c->args[k >> 1].begin(), n->c->args[k >> 1].end());
-        for (swe_t* q : n->p) all.insert(all.end(), q->args[k & 1].begin(), q->args[k & 1].end());
-    }
+    std::vector<int> order[2], tiles;   // order: 0 for the coarse grid, 1 + k for patch k
+    for (swe_t* q : n->p) tiles.push_back(q->ntiles);
+    n->shares[1] = swe::nest_shares(tiles, order[1]);
+    for (int& k : order[1]) ++k;
+    tiles.insert(tiles.begin(), n->c->ntiles);
+    n->shares[0] = swe::nest_shares(tiles, order[0]);
+    for (int k = 0; k < 4; ++k)
+        for (const std::vector<int>& o : order)
+            for (int g : o) {
+                const auto& a = g == 0 ? n->c->args[k >> 1] : n->p[g - 1]->args[k & 1];
+                all.insert(all.end(), a.begin(), a.end());
+            }
     NK(hipMalloc(&n->dargs, all.size()));
     NK(hipMemcpyAsync(n->dargs, all.data(), all.size(), hipMemcpyHostToDevice, n->stream));
     NK(hipStreamSynchronize(n->stream));

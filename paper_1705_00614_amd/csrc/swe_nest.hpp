@@ -36,6 +36,9 @@
 // only launches.
 #pragma once
 
+#include <algorithm>
+#include <vector>
+
 #include "swe_step.hpp"
 
 namespace swe {
@@ -77,6 +80,40 @@ struct NestArgs {
     double h2;                     // h_c^2
     double hold;                   // held coarse step length (0: the CFL rule)
 };
+
+// Shares of a launch over the grids of a nest with these tile counts, and the
+// grids' order in it (nest_shares): about GROUPS groups of NSEG workgroups,
+// twice what is resident at once, in proportion to the tiles, but no more than
+// one workgroup per tile and no fewer than LEAST groups while there are tiles
+// for them (a workgroup strides over further tiles; one without a tile holds
+// its place for a read of the control block only).
+constexpr int NEST_GROUPS = 128, NEST_LEAST = 8;
+inline GridShares nest_shares(const std::vector<int>& tiles, std::vector<int>& order) {
+    const int n = (int)tiles.size();
+    long long sum = 0;
+    for (int t : tiles) sum += t;
+    std::vector<int> m(n);
+    for (int k = 0; k < n; ++k)
+        m[k] = std::min((tiles[k] + NSEG - 1) / NSEG,
+                        std::max(NEST_LEAST, (int)((long long)NEST_GROUPS * tiles[k] / sum)));
+    order.resize(n);
+    for (int k = 0; k < n; ++k) order[k] = k;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return m[a] > m[b]; });
+    GridShares s{};
+    for (int step = 1;; step *= 2) {   // rounded up until there are at most LEVELS different shares
+        int l = 0, below = 0;
+        s = GridShares{};
+        for (int k = n - 1; k >= 0; --k) {   // from the smallest share up
+            const int v = (m[order[k]] + step - 1) / step * step;
+            if (v == below) continue;
+            if (l == GridShares::LEVELS) { l = -1; break; }
+            s.grids[l] = k + 1;
+            s.width[l++] = v - below;
+            below = v;
+        }
+        if (l >= 0) return s;
+    }
+}
 
 __host__ __device__ constexpr int nest_frame_cells(int nxe, int nye) {
     return 2 * NEST_FRAME * (nxe + nye - 2 * NEST_FRAME);

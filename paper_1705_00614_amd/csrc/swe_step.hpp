@@ -1664,19 +1664,54 @@ __device__ __forceinline__ Args<real> scalar_args(const Args<real>* scen, int si
     return u.a;
 }
 
-// One step of each of n independent grids (a nest's coarse grid and patches,
-// or its patches), G workgroups each: one launch instead of one per grid on
-// streams forked and joined around it, where each fork and join cost 5 to 10
-// us between 20 us steps (512 x 512 cells with 4 patches of 394 x 394, FP32:
-// 195 -> 126 us per coarse step of 4 substeps).  Groups of NSEG workgroups go
-// to the grids in turn, so that a grid's workgroup b runs on XCD b % NSEG as
-// in a launch of its own and the first workgroups of every grid -- those with
-// tiles -- start first.
+// How the workgroups of one launch are shared among its grids, in groups of
+// NSEG: the grids stand in descending order of their groups, and level l of
+// at most LEVELS gives `width[l]` more groups to each of the first `grids[l]`.
+// Level by level, and within one round by round, each group goes to the next
+// of those grids, so that a grid's workgroup b runs on XCD b % NSEG as in a
+// launch of its own and the first workgroups of every grid -- those with tiles
+// -- start first.
+struct GridShares {
+    static constexpr int LEVELS = 8;
+    int grids[LEVELS], width[LEVELS];
+    // grid, its groups before group t and in all
+    __host__ __device__ __forceinline__ void at(int t, int& grid, int& before, int& all) const {
+        int g = 0, w = 0, rounds = 0;
+        bool found = false;
+        grid = before = all = 0;
+#pragma unroll
+        for (int l = 0; l < LEVELS; ++l) {
+            g = grids[l];
+            w = width[l];
+            if (!found && t < g * w) {
+                found = true;
+                grid = t % g;
+                before = rounds + t / g;
+            }
+            t -= found ? 0 : g * w;
+            rounds += w;
+        }
+#pragma unroll
+        for (int l = 0; l < LEVELS; ++l) all += grid < grids[l] ? width[l] : 0;
+    }
+    int groups() const {
+        int n = 0;
+        for (int l = 0; l < LEVELS; ++l) n += grids[l] * width[l];
+        return n;
+    }
+};
+
+// One step of each of several independent grids (a nest's coarse grid and
+// patches, or its patches): one launch instead of one per grid on streams
+// forked and joined around it, where each fork and join cost 5 to 10 us between
+// 20 us steps (512 x 512 cells with 2 patches of 394 x 394, FP32: 195 -> 126 us
+// per coarse step of 4 substeps).
 template <typename real, int TX, int TY, int NT, int LIM>
-__global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step_grids(const Args<real>* grids, int n, int G) {
-    const int q = blockIdx.x / NSEG, grid = q % n;
+__global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step_grids(const Args<real>* grids, GridShares shares) {
+    int grid, before, all;
+    shares.at(blockIdx.x / NSEG, grid, before, all);
     const Args<real> a = scalar_args(grids, grid);
-    step_grid<real, TX, TY, NT, LIM, MODE_TAP>(a, (q / n) * NSEG + blockIdx.x % NSEG, G);
+    step_grid<real, TX, TY, NT, LIM, MODE_TAP>(a, before * NSEG + blockIdx.x % NSEG, all * NSEG);
 }
 
 // ---------------------------------------------------------------- preparation kernel

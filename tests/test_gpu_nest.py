@@ -267,3 +267,16 @@ def test_full_size_nest_first_coarse_steps_match_oracle():
     assert abs(G.query()["time"] - O.time()) <= 1e-12 * O.time()
     for k in range(2):
         assert (G.patch_state(k)[0] > 0).any()   # the patches hold water
+
+
+@pytest.mark.parametrize("skip", [True, False])
+def test_grids_of_unequal_shares(skip):
+    """Grids of 1 to 30 tiles take one to four groups of a launch's
+    workgroups.  FP64 against the oracle, the module's bars."""
+    sc = S.random_state(76, 72, seed=41, wet_frac=0.7, precision=64)
+    nest = S.nest(sc, [(6, 6, 3, 2), (20, 6, 24, 10), (8, 24, 12, 30), (34, 34, 36, 32)], r=2, seed=5, detail=0.3)
+    O = OracleNest(nest["coarse"], nest["patches"], r=2)
+    G = swe.Nest(nest, skip_dry=skip)
+    G.run(3)
+    O.run(3)
+    _compare(G, O, 64, label="skip=%s" % skip)

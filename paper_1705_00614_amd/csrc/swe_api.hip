@@ -2253,7 +2253,7 @@ int lc_put_crops_pageable(swe_lc_t* c, int n, const double* x, const double* y, 
 int lc_put_crops(swe_lc_t* c, LcHold& io, int n, const double* x, const double* y, const double* mask, double* cnt) {
     const size_t px = (size_t)lc_in(c, 0) * lc_in(c, 0), py = y ? (size_t)c->So * c->So * 6 : 0;
     const size_t per = (px * 6 + 2 * py) * sizeof(float), all = n * per;
-    size_t size = io.hold.get(all <= XFER_THREADED ? all : XFER_SLOTS * XFER_SLOT, &io.base);
+    const size_t size = io.hold.get(std::min(all, XFER_SLOTS * XFER_SLOT), &io.base);
     int threads = 1;
     if (all > XFER_THREADED) threads = (int)std::min<size_t>(XFER_SLOTS, (all >> 20) + 1);
     if (size / threads < per) threads = 1;

@@ -109,7 +109,9 @@ constexpr size_t XFER_THREADED = size_t(2) << 20;
 constexpr size_t XFER_PAGEABLE = size_t(1) << 20;   // elements of a piece without pinned memory
 
 constexpr int XFER_BUFFERS = 64;
-constexpr size_t XFER_LEAST = size_t(4) << 10;   // smallest buffer; others are powers of two times it
+// smallest buffer (others are powers of two times it): a 128^2 grid's state, so
+// that a small grid allocates one (each allocation takes some 30 us)
+constexpr size_t XFER_LEAST = size_t(256) << 10;
 constexpr size_t XFER_TOTAL = size_t(128) << 20;
 
 struct XferPool {
@@ -286,14 +288,18 @@ struct XferPlan {
             whole = true;
             return hipSuccess;
         }
-        const size_t size = hold.get(XFER_SLOTS * XFER_SLOT, &base);
-        if (!size) return hipSuccess;
-        slot = size < XFER_SLOT ? size : XFER_SLOT;
-        threads = (int)(size / slot);
+        const size_t most = XFER_SLOTS * XFER_SLOT, size = hold.get(all < most ? all : most, &base);
+        threads = XFER_SLOTS;
+        slot = size / threads / (1024 * rsize) * (1024 * rsize);
+        if (!slot) {   // none, or too little to split
+            hold.drop();
+            base = nullptr;
+            return hipSuccess;
+        }
         piece = (n * nf + threads - 1) / threads;   // about one piece a thread, at least 32768 cells, at most a slot
         if (piece < 32768) piece = 32768;
-        if (piece > slot / rsize) piece = slot / rsize;
         piece = (piece + 1023) / 1024 * 1024;
+        if (piece > slot / rsize) piece = slot / rsize;
         per = (int)((n + piece - 1) / piece);
         for (int t = 0; t < threads; ++t) {
             const hipError_t e = hipEventCreateWithFlags(&ev[t], hipEventDisableTiming);

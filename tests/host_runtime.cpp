@@ -464,7 +464,26 @@ int no_pinned_memory() {
     return 0;
 }
 
+// Pinned memory is asked for as a transfer needs it: little for small grids
+// and networks, the whole of a large transfer only for a large one, once.
+int memory_by_need() {
+    Grid small(64, 32, nullptr);
+    EXPECT(small.s && swe_run(small.s, 1) == 0 && small.get() == 0);
+    EXPECT(pinned_bytes <= (size_t(256) << 10));
+    Crops c(32, 24, nullptr);   // 2.2 MB of crops, labels and mask
+    EXPECT(c.c && c.train() == 0 && c.train() == 0);
+    EXPECT(pinned_bytes <= (size_t(256) << 10) + (size_t(4) << 20));
+    const size_t before = pinned_bytes;
+    Grid large(2048, 32, nullptr);
+    EXPECT(large.s && large.get() == 0 && large.kept() && large.set() == 0);
+    Grid odd(1500, 64, nullptr);
+    EXPECT(odd.s && odd.get() == 0 && odd.kept());
+    EXPECT(pinned_bytes <= before + (size_t(32) << 20));
+    return 0;
+}
+
 const std::map<std::string, std::function<int()>> scenarios = {
+    {"memory_by_need", memory_by_need},
     {"independent_handles", independent_handles},
     {"no_pinned_memory", no_pinned_memory},
     {"per_thread_stream", per_thread_stream},

@@ -15,7 +15,8 @@
 // The handle of the caller's stream may name another stream in every thread
 // (hipStreamPerThread).  Other threads launch pieces only after the calling one
 // has waited for what it had queued, and each waits for its own pieces; where
-// pieces are only queued, the calling thread launches all of them.
+// pieces are only queued, the calling thread launches all of them on that
+// handle.
 //
 // The pinned memory is one pool per process: buffers leased to one transfer
 // each, allocated when none that is free is large enough and given back when

@@ -2048,7 +2048,7 @@ struct swe_lc_s {
     unsigned short* g[swe::lc::NL] = {};     // dL/dz of each layer (bf16)
     float* y = nullptr;                // labels and mask of a training batch
     float* mask = nullptr;
-    float* part = nullptr;             // weight-gradient partials of every layer
+    float* part[swe::lc::NL] = {};     // weight-gradient partials of each layer (one allocation)
     int nblk[swe::lc::NL] = {};        // partials of the last backward
     double* loss_part = nullptr;
     int loss_blocks = 0;
@@ -2079,7 +2079,7 @@ constexpr int NET_NTH = 512;  // its threads per workgroup
 constexpr int LC_RING = 256;  // optimisation steps queued between two host waits
 
 void free_lc(swe_lc_t* c) {
-    void* ptrs[] = {c->params, c->grads, c->m1, c->m2, c->wf, c->wb, c->out, c->y, c->mask, c->part, c->loss_part,
+    void* ptrs[] = {c->params, c->grads, c->m1, c->m2, c->wf, c->wb, c->out, c->y, c->mask, c->part[0], c->loss_part,
                     c->loss, c->dscale, c->dX, c->dY, c->dM, c->dT, c->dmc, c->idx};
     for (void* q : ptrs) if (q) (void)hipFree(q);
     for (int l = 0; l < L_::NL; ++l) {
@@ -2139,6 +2139,23 @@ hipError_t lc_infer(swe_lc_t* c, int n, const int* cnt_dev, hipStream_t st) {
     return hipGetLastError();
 }
 
+// The partials of a training step, as many as the largest batch has (32-cell
+// tiles: 9 MB for one crop, 57 MB from 8 on).  Allocated with the network: by
+// the first training step it made that step 70 us longer and the network's
+// creation 40 us shorter.
+hipError_t lc_alloc_part(swe_lc_t* c) {
+    size_t off[L_::NL + 1] = {0};
+    for (int l = 0; l < L_::NL; ++l) {
+        const long long so = lc_in(c, l) - 2;
+        off[l + 1] = off[l] + (size_t)L_::part_blocks(c->max_crops * so * so) * L_::part_elems(l);
+    }
+    float* p = nullptr;
+    const hipError_t e = hipMalloc((void**)&p, sizeof(float) * off[L_::NL]);
+    if (e != hipSuccess) return e;
+    for (int l = 0; l < L_::NL; ++l) c->part[l] = p + off[l];
+    return hipSuccess;
+}
+
 // Backward of the last forward (n crops) from g[3] (dL/dz of the last layer),
 // into the block partials of the weight gradients (k_opt sums them).
 hipError_t lc_backward(swe_lc_t* c, int n) {
@@ -2168,9 +2185,9 @@ hipError_t lc_backward(swe_lc_t* c, int n) {
         w.a[l] = c->act[l];
         w.chunk[l] = chunk;
         w.nblk[l] = c->nblk[l] = (int)((total + chunk - 1) / chunk);
+        w.part[l] = c->part[l];
         grid += w.nblk[l];
     }
-    w.part = c->part;
     w.Sin0 = lc_in(c, 0);
     w.n = n;
     hipLaunchKernelGGL(L_::k_conv_bwd_w, dim3(grid), dim3(L_::WG_NTH), 0, c->stream, w);
@@ -2189,8 +2206,7 @@ int lc_opt_step(swe_lc_t* c, int n, double cnt, double lr, double* loss_dev) {
     HIPCHK(hipGetLastError());
     HIPCHK(lc_backward(c, n));
     L_::OptArgs a{};
-    a.part = c->part;
-    for (int l = 0; l < L_::NL; ++l) a.nblk[l] = c->nblk[l];
+    for (int l = 0; l < L_::NL; ++l) { a.part[l] = c->part[l]; a.nblk[l] = c->nblk[l]; }
     a.params = c->params; a.grads = c->grads; a.m = c->m1; a.v = c->m2; a.wf = c->wf; a.wb = c->wb;
     a.loss_part = c->loss_part; a.loss_blocks = c->loss_blocks; a.loss = loss_dev;
     if (lr > 0.0) {
@@ -2367,7 +2383,7 @@ swe_lc_t* swe_lc_create(int tile, int max_crops, const double* in_scale, const d
     LK(hipMalloc((void**)&c->out, sizeof(float) * (size_t)max_crops * c->So * c->So * 16));
     LK(hipMalloc((void**)&c->y, sizeof(float) * (size_t)max_crops * c->So * c->So * 6));
     LK(hipMalloc((void**)&c->mask, sizeof(float) * (size_t)max_crops * c->So * c->So * 6));
-    LK(hipMalloc((void**)&c->part, sizeof(float) * L_::part_off(L_::NL)));
+    LK(lc_alloc_part(c));
     c->loss_blocks = 1024;
     LK(hipMalloc((void**)&c->loss_part, sizeof(double) * c->loss_blocks));
     LK(hipMalloc((void**)&c->loss, sizeof(double) * LC_RING));

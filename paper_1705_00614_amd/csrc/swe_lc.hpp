@@ -53,16 +53,13 @@ __host__ __device__ constexpr int wb_off(int l) {
     return o;
 }
 constexpr int NWB = wb_off(NL);
-// block partials of the weight gradients: layer l holds PART_BLOCKS of
-// part_elems(l) floats ([tap][COUT][CIN], then [COUT]) from part_off(l) on
+// block partials of the weight gradients: layer l has at most PART_BLOCKS of
+// part_elems(l) floats ([tap][COUT][CIN], then [COUT]), of at least 16 pixels
+// each; part_blocks(px) is the most that batches of up to px pixels have
 constexpr int PART_BLOCKS = 512;
+inline int part_blocks(long long px) { return (int)((px + 15) / 16 < PART_BLOCKS ? (px + 15) / 16 : PART_BLOCKS); }
 __host__ __device__ constexpr int part_elems_of(int ci, int co) { return 9 * co * ci + co; }
 __host__ __device__ constexpr int part_elems(int l) { return part_elems_of(CIN[l], COUT[l]); }
-__host__ __device__ constexpr size_t part_off(int l) {
-    size_t o = 0;
-    for (int q = 0; q < l; ++q) o += (size_t)PART_BLOCKS * part_elems(q);
-    return o;
-}
 
 __device__ __forceinline__ unsigned short to_bf16(float f) {
     unsigned u = __float_as_uint(f);
@@ -665,7 +662,7 @@ __device__ __forceinline__ void wgrad_chunk(WgLds& L, const unsigned short* __re
 struct WgradArgs {
     const unsigned short* g[NL];
     const unsigned short* a[NL];
-    float* part;
+    float* part[NL];
     int nblk[NL], chunk[NL];
     int Sin0, n;               // input side of layer 0, crops
 };
@@ -673,15 +670,15 @@ __global__ __launch_bounds__(WG_NTH) void k_conv_bwd_w(WgradArgs w) {
     __shared__ WgLds L;
     int b = blockIdx.x;
     if (b < w.nblk[1])
-        return wgrad_chunk<32, 32>(L, w.g[1], w.a[1], w.part + part_off(1), w.Sin0 - 2, w.n, w.chunk[1], b);
+        return wgrad_chunk<32, 32>(L, w.g[1], w.a[1], w.part[1], w.Sin0 - 2, w.n, w.chunk[1], b);
     b -= w.nblk[1];
     if (b < w.nblk[2])
-        return wgrad_chunk<32, 32>(L, w.g[2], w.a[2], w.part + part_off(2), w.Sin0 - 4, w.n, w.chunk[2], b);
+        return wgrad_chunk<32, 32>(L, w.g[2], w.a[2], w.part[2], w.Sin0 - 4, w.n, w.chunk[2], b);
     b -= w.nblk[2];
     if (b < w.nblk[0])
-        return wgrad_chunk<16, 32>(L, w.g[0], w.a[0], w.part + part_off(0), w.Sin0, w.n, w.chunk[0], b);
+        return wgrad_chunk<16, 32>(L, w.g[0], w.a[0], w.part[0], w.Sin0, w.n, w.chunk[0], b);
     b -= w.nblk[0];
-    wgrad_chunk<32, 16>(L, w.g[3], w.a[3], w.part + part_off(3), w.Sin0 - 6, w.n, w.chunk[3], b);
+    wgrad_chunk<32, 16>(L, w.g[3], w.a[3], w.part[3], w.Sin0 - 6, w.n, w.chunk[3], b);
 }
 
 // ------------------------------------------------------------------ parameters
@@ -709,8 +706,8 @@ __host__ __device__ constexpr int opt_blocks(int l) { return (part_elems(l) + OP
 constexpr int OPT_GRID = opt_blocks(0) + opt_blocks(1) + opt_blocks(2) + opt_blocks(3) + 1;
 
 struct OptArgs {
-    const float* part;          // block partials
-    int nblk[NL];               // partials of each layer
+    const float* part[NL];      // block partials of each layer
+    int nblk[NL];               // and their number
     float *params, *grads, *m, *v;
     unsigned short *wf, *wb;    // bf16 weight copies [tap][out][in] and [tap][in][out]
     const double* loss_part;    // loss partials of the batch, their count, and the loss
@@ -755,12 +752,12 @@ __global__ __launch_bounds__(OPT_NTH) void k_opt(OptArgs a) {
         return;
     }
     int co_p = 0, ci_p = 0, co_r = 0, ci_r = 0, po = 0, wo = 0, nb = 0;
-    const float* part = a.part;
+    const float* part = nullptr;
 #pragma unroll
     for (int q = 0; q < NL; ++q)
         if (l == q) {
             co_p = COUT[q]; ci_p = CIN[q]; co_r = COUT_REAL[q]; ci_r = CIN_REAL[q];
-            po = p_off(q); wo = wb_off(q); nb = a.nblk[q]; part += part_off(q);
+            po = p_off(q); wo = wb_off(q); nb = a.nblk[q]; part = a.part[q];
         }
     const int wcount = 9 * co_p * ci_p, per = wcount + co_p;
     const int e = blk * OPT_E + lane;

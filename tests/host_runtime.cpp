@@ -482,7 +482,22 @@ int memory_by_need() {
     return 0;
 }
 
+// A network holds the partials of as large a training step as it can take.
+int network_memory() {
+    Crops one(32, 1, nullptr);
+    EXPECT(one.c && device_bytes <= (size_t(12) << 20));
+    const size_t created = device_bytes;
+    EXPECT(one.train() == 0 && one.train() == 0 && device_bytes == created);
+    Crops many(32, 64, nullptr);
+    EXPECT(many.c && many.train() == 0);
+    swe_lc_destroy(many.c);
+    swe_lc_destroy(one.c);
+    EXPECT(device_bytes == 0);
+    return 0;
+}
+
 const std::map<std::string, std::function<int()>> scenarios = {
+    {"network_memory", network_memory},
     {"memory_by_need", memory_by_need},
     {"independent_handles", independent_handles},
     {"no_pinned_memory", no_pinned_memory},

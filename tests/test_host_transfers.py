@@ -27,7 +27,7 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["per_thread_stream", "no_pinned_memory", "independent_handles",
-                                      "memory_by_need"])
+                                      "memory_by_need", "network_memory"])
 def test_host_path(program, scenario):
     res = subprocess.run([program, scenario], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0, res.stdout + res.stderr

@@ -32,9 +32,9 @@
 
 #include <climits>
 #include <cstring>
+#include <exception>
 #include <mutex>
 #include <new>
-#include <system_error>
 #include <thread>
 
 #include "swe_step.hpp"
@@ -223,7 +223,7 @@ hipError_t xfer_team(int T, Job job, Then then) {
                 err[t] = hipSetDevice(dev);
                 if (err[t] == hipSuccess) err[t] = job(t);
             });
-    } catch (const std::system_error&) {   // no more threads: the caller takes the rest
+    } catch (const std::exception&) {   // no more threads, or no memory for one: the caller takes the rest
     }
     for (int t = 0; t < T; ++t) {
         if (t > 0 && t < started) th[t].join();

@@ -141,10 +141,20 @@ void carry(const std::string& name, unsigned fields, void** args) {
             memcpy(f[2 * N + q] + k * size, f[2 * q] + ((y0 + (first + k) / w) * pitch + x0 + (first + k) % w) * size, size);
 }
 
+thread_local bool no_memory = false;   // operator new throws in this thread
+
 struct Config { dim3 grid, block; size_t shared; hipStream_t stream; };
 thread_local std::vector<Config> configs;
 
 }  // namespace
+
+void* operator new(size_t n) {
+    void* p = no_memory ? nullptr : malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
 
 extern "C" {
 
@@ -496,7 +506,20 @@ int network_memory() {
     return 0;
 }
 
+// Where a thread cannot be started for want of memory, the calling one does
+// its share.
+int no_memory_for_threads() {
+    Grid g(1024, 32, nullptr);
+    EXPECT(g.s);
+    no_memory = true;
+    const int get = g.get(), set = g.set(), again = g.get();
+    no_memory = false;
+    EXPECT(get == 0 && set == 0 && again == 0 && g.kept());
+    return 0;
+}
+
 const std::map<std::string, std::function<int()>> scenarios = {
+    {"no_memory_for_threads", no_memory_for_threads},
     {"network_memory", network_memory},
     {"memory_by_need", memory_by_need},
     {"independent_handles", independent_handles},

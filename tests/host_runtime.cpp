@@ -141,7 +141,12 @@ void carry(const std::string& name, unsigned fields, void** args) {
             memcpy(f[2 * N + q] + k * size, f[2 * q] + ((y0 + (first + k) / w) * pitch + x0 + (first + k) % w) * size, size);
 }
 
-thread_local bool no_memory = false;   // operator new throws in this thread
+thread_local bool no_memory = false;   // operator new throws in this thread, but for the stub's own
+struct StubsOwn {
+    const bool was = no_memory;
+    StubsOwn() { no_memory = false; }
+    ~StubsOwn() { no_memory = was; }
+};
 
 struct Config { dim3 grid, block; size_t shared; hipStream_t stream; };
 thread_local std::vector<Config> configs;
@@ -159,6 +164,7 @@ void operator delete(void* p, size_t) noexcept { free(p); }
 extern "C" {
 
 hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shared, hipStream_t stream) {
+    const StubsOwn own;
     configs.push_back({grid, block, shared, stream});
     return hipSuccess;
 }
@@ -169,6 +175,7 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shared, hi
     return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, hipStream_t st) {
+    const StubsOwn own;
     Dl_info info;
     const std::string name = dladdr(f, &info) && info.dli_sname ? info.dli_sname : "";
     const bool piece = name.find("k_export") != std::string::npos || name.find("k_import") != std::string::npos ||
@@ -253,6 +260,7 @@ hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t st) {
 hipError_t hipGraphDestroy(hipGraph_t g) { delete reinterpret_cast<int*>(g); return hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t e) { delete reinterpret_cast<int*>(e); return hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
+    const StubsOwn own;
     Event* v = new Event;
     v->device = current_device;
     *e = reinterpret_cast<hipEvent_t>(v);
@@ -518,7 +526,21 @@ int no_memory_for_threads() {
     return 0;
 }
 
+// A handle's transfers work whichever device is current, and leave it so.
+int another_device() {
+    for (int n : {64, 1024}) {
+        Grid g(n, 32, nullptr);
+        EXPECT(g.s);
+        (void)hipSetDevice(1);
+        EXPECT(g.get() == 0 && g.kept() && g.set() == 0 && g.get() == 0 && g.kept());
+        EXPECT(current_device == 1);
+        (void)hipSetDevice(0);
+    }
+    return 0;
+}
+
 const std::map<std::string, std::function<int()>> scenarios = {
+    {"another_device", another_device},
     {"no_memory_for_threads", no_memory_for_threads},
     {"network_memory", network_memory},
     {"memory_by_need", memory_by_need},

@@ -206,6 +206,24 @@ struct XferHold {
     }
 };
 
+// The stream's device as the current one while this lives: events belong to
+// the device that is current when they are made, and are recorded only on
+// streams of that device.
+struct XferDevice {
+    int was = -1;
+    explicit XferDevice(hipStream_t st) {
+        int now = 0;
+        hipDevice_t dev = 0;
+        if (hipGetDevice(&now) == hipSuccess && hipStreamGetDevice(st, &dev) == hipSuccess && (int)dev != now &&
+            hipSetDevice((int)dev) == hipSuccess)
+            was = now;
+    }
+    ~XferDevice() {
+        if (was >= 0) (void)hipSetDevice(was);
+    }
+    XferDevice(const XferDevice&) = delete;
+};
+
 // Run job(t) for every t < T <= XFER_SLOTS on host threads (the caller is
 // number 0) and, on the calling thread and in order, then(t) once job(t) is
 // done.  Returns the first error; nothing is run after one of its own.
@@ -378,6 +396,7 @@ hipError_t xfer_get(hipStream_t st, const swe::Ctrl* ctrl, real* const (&a)[3], 
         if constexpr (sizeof(real) == 8) std::memcpy(dst, src, cnt * 8);
         else for (size_t k = 0; k < cnt; ++k) dst[k] = (double)src[k];
     };
+    const XferDevice current(st);
     hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return e;
     XferPlan pl;
@@ -418,6 +437,7 @@ hipError_t xfer_get(hipStream_t st, const swe::Ctrl* ctrl, real* const (&a)[3], 
 // pair.  Returns once the device has them.
 template <typename real, class Fill>
 hipError_t xfer_put(hipStream_t st, int nf, const swe::FieldPair<real>* f, size_t n, Fill fill) {
+    const XferDevice current(st);
     hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return e;
     XferPlan pl;

@@ -1,7 +1,8 @@
 """The library's host path on a stub of the HIP runtime (host_runtime.cpp),
 one scenario each, no GPU: ordering of transfers on the caller's stream, and
 transfers where there is no pinned memory, handles that wait beside ones that
-do not, the memory that is asked for, and threads that cannot be started."""
+do not, the memory that is asked for, threads that cannot be started, and another
+current device."""
 import os
 import shutil
 import subprocess
@@ -27,7 +28,8 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["per_thread_stream", "no_pinned_memory", "independent_handles",
-                                      "memory_by_need", "network_memory", "no_memory_for_threads"])
+                                      "memory_by_need", "network_memory", "no_memory_for_threads",
+                                      "another_device"])
 def test_host_path(program, scenario):
     res = subprocess.run([program, scenario], capture_output=True, text=True, timeout=120)
     assert res.returncode == 0, res.stdout + res.stderr

@@ -291,7 +291,7 @@ template <typename T> struct XferHeap {
     XferHeap(const XferHeap&) = delete;
 };
 
-// A transfer of nf fields of n cells through the pool: in one piece where
+// A transfer of nf <= 3 fields of n cells through the pool: in one piece where
 // that is small, else split over threads with an event each; without pinned
 // memory neither (base stays null).
 struct XferPlan {
@@ -303,15 +303,15 @@ struct XferPlan {
     hipEvent_t ev[XFER_SLOTS] = {};
     hipError_t prepare(int nf, size_t n, size_t rsize) {
         const size_t all = nf * n * rsize;
-        if (all <= XFER_THREADED && hold.get(all, &base) >= all) {
-            whole = true;
+        if (all <= XFER_THREADED) {
+            whole = hold.get(all, &base) >= all;
+            if (!whole) base = nullptr;
             return hipSuccess;
         }
         const size_t most = XFER_SLOTS * XFER_SLOT, size = hold.get(all < most ? all : most, &base);
         threads = XFER_SLOTS;
         slot = size / threads / (1024 * rsize) * (1024 * rsize);
         if (!slot) {   // none, or too little to split
-            hold.drop();
             base = nullptr;
             return hipSuccess;
         }
@@ -397,8 +397,9 @@ hipError_t xfer_get(hipStream_t st, const swe::Ctrl* ctrl, real* const (&a)[3], 
         else for (size_t k = 0; k < cnt; ++k) dst[k] = (double)src[k];
     };
     const XferDevice current(st);
-    hipError_t e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    // (a small one is queued behind it: on a new stream this wait takes 20 us)
+    if (nf * n * sizeof(real) > XFER_THREADED && (e = hipStreamSynchronize(st)) != hipSuccess) return e;
     XferPlan pl;
     if ((e = pl.prepare(nf, n, sizeof(real))) != hipSuccess) return e;
     if (!pl.base) return xfer_get_pageable(st, ctrl, a, b, pitch, x0, y0, w, h, out, convert);
@@ -438,12 +439,13 @@ hipError_t xfer_get(hipStream_t st, const swe::Ctrl* ctrl, real* const (&a)[3], 
 template <typename real, class Fill>
 hipError_t xfer_put(hipStream_t st, int nf, const swe::FieldPair<real>* f, size_t n, Fill fill) {
     const XferDevice current(st);
-    hipError_t e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    // (a small one is queued behind it: on a new stream this wait takes 20 us)
+    if (nf * n * sizeof(real) > XFER_THREADED && (e = hipStreamSynchronize(st)) != hipSuccess) return e;
     XferPlan pl;
     if ((e = pl.prepare(nf, n, sizeof(real))) != hipSuccess) return e;
     if (!pl.base) return xfer_put_pageable(st, nf, f, n, fill);
-    if (pl.whole && nf <= 3) {
+    if (pl.whole) {
         real* base = (real*)pl.base;
         swe::XferFields<real, 3> x{};
         for (int q = 0; q < nf; ++q) {

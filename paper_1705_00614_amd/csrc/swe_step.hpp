@@ -1433,8 +1433,13 @@ __device__ void tile_step(const Args<real>& a, Lds<real, TX, TY>& L, int tx0, in
 #ifndef SWE_WAVES_PER_SIMD_F64
 #define SWE_WAVES_PER_SIMD_F64 4
 #endif
-template <typename real> constexpr int waves_per_simd() {
-    return sizeof(real) == 4 ? SWE_WAVES_PER_SIMD_F32 : SWE_WAVES_PER_SIMD_F64;
+// No more than the workgroups whose tiles fit a CU's LDS have (four SIMDs):
+// one of 90 KB for 32 x 16 FP64 cells, so two waves.
+constexpr int LDS_BYTES = 160 * 1024;
+template <typename real, int TX, int TY, int NT> constexpr int waves_per_simd() {
+    const int ask = sizeof(real) == 4 ? SWE_WAVES_PER_SIMD_F32 : SWE_WAVES_PER_SIMD_F64;
+    const int fit = LDS_BYTES / (int)sizeof(Lds<real, TX, TY>) * (NT / 64) / 4;
+    return ask < fit ? ask : fit;
 }
 
 // One step of a grid by workgroup b0 of its G.
@@ -1644,7 +1649,7 @@ __device__ __forceinline__ void step_grid(const Args<real>& a, int b0, int G) {
 }
 
 template <typename real, int TX, int TY, int NT, int LIM, int MODE>
-__global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step(Args<real> a) {
+__global__ __launch_bounds__(NT, (waves_per_simd<real, TX, TY, NT>())) void k_step(Args<real> a) {
     step_grid<real, TX, TY, NT, LIM, MODE>(a, blockIdx.x, gridDim.x);
 }
 
@@ -1707,7 +1712,7 @@ struct GridShares {
 // 20 us steps (512 x 512 cells with 2 patches of 394 x 394, FP32: 195 -> 126 us
 // per coarse step of 4 substeps).
 template <typename real, int TX, int TY, int NT, int LIM>
-__global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_step_grids(const Args<real>* grids, GridShares shares) {
+__global__ __launch_bounds__(NT, (waves_per_simd<real, TX, TY, NT>())) void k_step_grids(const Args<real>* grids, GridShares shares) {
     int grid, before, all;
     shares.at(blockIdx.x / NSEG, grid, before, all);
     const Args<real> a = scalar_args(grids, grid);
@@ -1907,7 +1912,7 @@ struct BatchArgs {
 // 1340 tiles together, FP32: 79 -> 52.8 us, the scenarios' arguments through
 // scalar loads and no fence per workgroup besides what the tile gained.
 template <typename real, int TX, int TY, int NT, int LIM>
-__global__ __launch_bounds__(NT, waves_per_simd<real>()) void k_batch_step(BatchArgs<real> ba) {
+__global__ __launch_bounds__(NT, (waves_per_simd<real, TX, TY, NT>())) void k_batch_step(BatchArgs<real> ba) {
     constexpr int NWAVE = NT / 64;
     __shared__ Lds<real, TX, TY> L;
     __shared__ double red_d[2][NWAVE];

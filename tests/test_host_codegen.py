@@ -23,20 +23,20 @@ CONTRIBUTION = re.compile(r"\s(global|flat)_atomic_(umax|cmpswap)\S*\s")   # spe
 ARRIVAL = re.compile(r"\s(global|flat)_atomic_add_x2\s")                   # the group's 64-bit arrival word
 
 
-def _assembly(tmp_path, kernel):
+def _compile(tmp_path, kernel):
     src, asm = tmp_path / "k.hip", tmp_path / "k.s"
     src.write_text('#include "%s"\ntemplate __global__ void swe::%s;\n'
                    % (os.path.join(build.CSRC, "swe_nest.hpp"), kernel))
     flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
-    subprocess.run(["hipcc"] + flags + ["--cuda-device-only", "-S", "-o", str(asm), str(src)], check=True,
-                   capture_output=True)
-    return [line.split(";")[0] for line in asm.read_text().split("\n")]
+    res = subprocess.run(["hipcc"] + flags + ["--cuda-device-only", "-S", "-o", str(asm), str(src)], check=True,
+                         capture_output=True, text=True)
+    return [line.split(";")[0] for line in asm.read_text().split("\n")], res.stderr
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
 @pytest.mark.parametrize("name", sorted(KERNELS))
 def test_contributions_are_waited_for_before_the_arrival(tmp_path, name):
-    lines = _assembly(tmp_path, KERNELS[name])
+    lines, _ = _compile(tmp_path, KERNELS[name])
     arrivals = [k for k, line in enumerate(lines) if ARRIVAL.search(line)]
     contributions = [k for k, line in enumerate(lines) if CONTRIBUTION.search(line)]
     assert len(arrivals) == 1 and contributions, (arrivals, contributions)
@@ -51,3 +51,11 @@ def test_contributions_are_waited_for_before_the_arrival(tmp_path, name):
 
     for k in contributions:
         assert drained(barrier, arrivals[0]) or (" sc0" in lines[k] and drained(k, barrier)), lines[k]
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+@pytest.mark.parametrize("tile", ["double, 16, 16, 512", "double, 32, 16, 512", "float, 64, 16, 512", "float, 16, 16, 256"])
+def test_kernels_ask_for_waves_that_fit(tmp_path, tile):
+    """The waves per SIMD a step kernel is compiled for fit its tile's LDS."""
+    _, said = _compile(tmp_path, "k_step<%s, 0, 0>(swe::Args<%s>)" % (tile, tile.split(",")[0]))
+    assert "failed to meet occupancy" not in said, said

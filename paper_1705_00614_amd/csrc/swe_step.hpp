@@ -38,10 +38,12 @@
 // lake's 2900 tiles, is far below.  FP32, before and after the reconstruction
 // once per cell, DPP reductions, band-wise ghosts, early loads and 24-bit
 // index arithmetic: 2048^2 lake 107.3 -> 87.5 us, 4096^2 flood with about 500
-// tiles 35.6 -> 28.9 us, 4096^2 fully wet 637 -> 500 us.  1024 threads per 32 x 32
-// tile (one workgroup per CU, whose barriers then idle it) took 118.6 and 37.4
-// us on the first two; an LDS pitch of 45, 93.2 us on the lake; the next tile's
-// fields prefetched into registers, 94.9 us; P1 by runs of 4, 88.5 us.
+// tiles 35.6 -> 28.9 us, 4096^2 fully wet 637 -> 490 us (kernel traces, whose
+// durations add up to 6 % more than a whole call takes without one).  1024
+// threads per 32 x 32 tile (one workgroup per CU, whose barriers then idle it)
+// took 118.6 and 37.4 us on the first two; an LDS pitch of 45, 93.2 us on the
+// lake; the next tile's fields prefetched into registers, 94.9 us; P1 by runs of
+// 4, 88.5 us.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -1724,8 +1726,11 @@ __global__ __launch_bounds__(NT, (waves_per_simd<real, TX, TY, NT>())) void k_st
 // partials.  Needs only a 1-cell ring.  Workgroups stride over the tiles (at
 // most PREPARE_GRID of them, a multiple of NSEG) and send one speed maximum
 // each: the maxima go to one address, where atomics serialise at 11 ns, so
-// one per tile was most of the 143 us on 16 384 FP32 tiles; so 105 us, 3.2 TB/s
+// one per tile was most of the 143 us on 16 384 FP32 tiles; so 106 us, 3.2 TB/s
 // of the five fields, the square roots and divisions of the speed beside them.
+// 512, 1024 or 2048 of them: a whole step without allocation takes 31, 31 and
+// 32 us on 512^2 FP32 cells, 57, 59 and 59 on 1024^2, 150, 150 and 156 on 2048^2,
+// 571, 576 and 569 on 4096^2, and 432, 425 and 420 on 2048^2 FP64 cells.
 constexpr int PREPARE_GRID = 1024;
 template <typename real, int TX, int TY, int NT>
 __global__ __launch_bounds__(NT) void k_prepare(Args<real> a) {
@@ -1909,7 +1914,7 @@ struct BatchArgs {
 };
 
 // Bound as the step of a grid with the same number of tiles.  20 floods with
-// 1340 tiles together, FP32: 79 -> 52.8 us, the scenarios' arguments through
+// 1340 tiles together, FP32: 79 -> 52.6 us, the scenarios' arguments through
 // scalar loads and no fence per workgroup besides what the tile gained.
 template <typename real, int TX, int TY, int NT, int LIM>
 __global__ __launch_bounds__(NT, (waves_per_simd<real, TX, TY, NT>())) void k_batch_step(BatchArgs<real> ba) {

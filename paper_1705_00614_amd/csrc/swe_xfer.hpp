@@ -226,7 +226,7 @@ struct XferDevice {
 
 // Run job(t) for every t < T <= XFER_SLOTS on host threads (the caller is
 // number 0) and, on the calling thread and in order, then(t) once job(t) is
-// done.  Returns the first error; nothing is run after one of its own.
+// done.  Returns the first error, after which the caller starts no more.
 template <class Job, class Then>
 hipError_t xfer_team(int T, Job job, Then then) {
     int dev = 0;
@@ -245,7 +245,7 @@ hipError_t xfer_team(int T, Job job, Then then) {
     }
     for (int t = 0; t < T; ++t) {
         if (t > 0 && t < started) th[t].join();
-        else err[t] = job(t);
+        else if (e == hipSuccess) err[t] = job(t);
         if (e == hipSuccess) e = err[t] == hipSuccess ? then(t) : err[t];
     }
     return e;

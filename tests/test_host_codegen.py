@@ -17,6 +17,7 @@ KERNELS = {
     "batch_f64": "k_batch_step<double, 16, 16, 512, 0>(swe::BatchArgs<double>)",
     "step_f32": "k_step<float, 32, 32, 512, 0, 0>(swe::Args<float>)",
     "step_f64": "k_step<double, 16, 16, 512, 0, 0>(swe::Args<double>)",
+    "step_grids": "k_step_grids<float, 32, 32, 512, 0>(const swe::Args<float>*, swe::GridShares)",
     "nest_close": "k_nest_close<float>(swe::Args<float>, swe::NestArgs<float>, const int*, const int*, int, int, int)",
 }
 CONTRIBUTION = re.compile(r"\s(global|flat)_atomic_(umax|cmpswap)\S*\s")   # speeds and errors

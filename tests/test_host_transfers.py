@@ -19,7 +19,7 @@ pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 
 @pytest.fixture(scope="module")
 def program(tmp_path_factory):
-    swe.load()   # builds the library if it is not there
+    swe.load()   # (raises where the library is not built)
     exe = str(tmp_path_factory.mktemp("host") / "host_runtime")
     subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-pthread", "-rdynamic", "-I", os.path.join(ROCM, "include"),
                     os.path.join(HERE, "host_runtime.cpp"), build.LIB, "-ldl", "-Wl,--allow-shlib-undefined",
